@@ -61,7 +61,8 @@ def listed():
         dict(_case("davidson", "cyl8x4", 1024, matvecs=4), name="davidson_f64_cyl8x4_m1024"),
         # the truncation of a two-site tensor, split and merged again as at the bonds that regions share
         dict(_case("svd", "cyl8x4", 1024), name="svd_cyl8x4_m1024"),
-        dict(_case("svd", "cyl24x8", 2000), name="svd_cyl24x8_m2000"),
+        # (on the 24 x 8 cylinder the charge fluctuates over about as many sites as a chain of 32 has: blocks of 750 rows)
+        dict(_case("svd", "cyl24x8", 2000, span=32), name="svd_cyl24x8_m2000"),
         # the backward direction: gradient of the energy with respect to one MPO tensor
         dict(_case("grad", "cyl24x8", 777, site=90), name="grad_cyl24x8_m777"),
         # the whole path on the smallest workload: canonical form, one sweep to the right and back, and the
@@ -92,6 +93,8 @@ def draw(rng):
         return _case(kind, lattice, m, site, dir=rng.choice([1, -1]))
     if kind == "davidson":
         return _case(kind, lattice, m, site, matvecs=rng.randint(2, 6))
+    if kind == "svd" and n > 32:
+        return _case(kind, lattice, m, span=rng.randrange(24, 73, 2))
     return _case(kind, lattice, m, site)
 
 
@@ -112,7 +115,11 @@ def _size(lattice):
 
 
 def _bond(case, l):
-    return synth.binomial_bond(_size(case["lattice"]), l, case["m"])
+    """Sectors of the bond after l sites; with a span, those of a chain of so many sites at the same distance from
+    its centre."""
+    n = _size(case["lattice"])
+    span = case.get("span", n)
+    return synth.binomial_bond(span, l - n // 2 + span // 2, case["m"])
 
 
 def _words(nsites):
@@ -186,8 +193,9 @@ def _env(bond, deltas, side, gen):
 
 
 def _grade(bond, m):
-    """Square roots of the Schmidt values of a bond's states: exp(-0.2 ln(1 + rank)^2), rank among all sectors."""
-    return {q: torch.exp(-0.1 * torch.log1p(torch.arange(n, dtype=F64, device="cuda") * (m / n)) ** 2)
+    """Weights of a bond's states by their rank among all sectors; a random core between the weights of two bonds has
+    a spectrum like theirs that falls to about 1e-5 at rank m = 1000 to 2000."""
+    return {q: torch.exp(-0.15 * torch.log1p(torch.arange(n, dtype=F64, device="cuda") * (m / n)) ** 2)
             for q, n in bond.items()}
 
 
