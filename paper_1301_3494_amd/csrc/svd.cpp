@@ -3,8 +3,8 @@
 //
 // Psi viewed as the (m d) x (d m) matrix is block-diagonal in the middle
 // charge; each block M (rows (s1, a), columns (s2, b)) is gathered densely and
-// decomposed M = U Lambda Vt by one-sided block Jacobi (svd.hip); at the top
-// level, blocks of at least 64 rows are first ordered by row norm and QR
+// decomposed M = U Lambda Vt by block Jacobi sweeps on the Gram matrix of its
+// rows (svd.hip); at the top level, blocks of at least 64 rows are first ordered by row norm and QR
 // factored, and the iteration runs on the triangular factor (qr_factor,
 // qr_right_factor: about half the sweeps on graded blocks).  Appendix
 // recursion: for the singular values of a block below eps * lambda_1 (indices
@@ -25,7 +25,6 @@ namespace pdmrg {
 
 namespace {
 
-constexpr int kJacBlock = 8;
 constexpr int kMaxSweeps = 60;
 constexpr int kMaxDepth = 8;
 // Smallest matrix (rows of W) that takes the QR preconditioning by default:
@@ -77,6 +76,14 @@ void run_copies(const std::vector<CopyTask> &tasks, hipStream_t s) {
     HIP_OK(hipStreamSynchronize(s));   // d is freed on return
 }
 
+// One matrix of the Jacobi iteration: W (nv rows of length len, packed) and
+// the accumulated rotation Z (nv x nv, row stride ldz).
+struct JacMat {
+    double *W, *Z;
+    double tol;
+    int nv, len, ldz;
+};
+
 // Householder QR preconditioning of the Jacobi iteration (depth 0).  The rows
 // of a matrix's W (nv x len) are put in order of decreasing norm (P), the
 // len x nv matrix X = (P W)^T is factored X = Q R, and the Jacobi iteration
@@ -91,6 +98,7 @@ struct QrState {
     std::vector<int32_t> idx;        // P then P^-1 per preconditioned matrix
     DevBuf d_idx, d_items, d_panels, d_trail, d_back;
     std::vector<QrItem> qitems;
+    std::vector<int> who;            // matrix of each QrItem
     std::vector<QrPanel> panels;
     std::vector<QrApply> trail, back;
     std::vector<int> panel_off, trail_off, back_off, panel_span;
@@ -98,7 +106,7 @@ struct QrState {
     int64_t max_elems = 0;
 };
 
-void qr_factor(const std::vector<Mat> &mats, std::vector<JacItem> &items, const std::vector<char> &pre,
+void qr_factor(const std::vector<Mat> &mats, const std::vector<JacMat> &items, const std::vector<char> &pre,
                const std::vector<double *> &qa, const std::vector<double *> &qm, const std::vector<double *> &qt,
                QrState &qs, hipStream_t s) {
     const int nm = (int)items.size();
@@ -159,7 +167,9 @@ void qr_factor(const std::vector<Mat> &mats, std::vector<JacItem> &items, const 
             npan = std::max(npan, (items[i].nv + kQrPanel - 1) / kQrPanel);
             qs.max_nv = std::max(qs.max_nv, items[i].nv);
             qs.max_elems = std::max<int64_t>(qs.max_elems, (int64_t)items[i].nv * qs.len[i]);
-            qs.qitems.push_back(QrItem{qa[i], items[i].Z, items[i].W, qm[i], items[i].nv, qs.len[i]});
+            qs.qitems.push_back(QrItem{qa[i], items[i].Z, items[i].W, qm[i], items[i].nv, qs.len[i], items[i].len,
+                                       items[i].ldz});
+            qs.who.push_back(i);
         }
     for (int pn = 0; pn < npan; ++pn) {
         const int j0 = pn * kQrPanel;
@@ -200,13 +210,143 @@ void qr_factor(const std::vector<Mat> &mats, std::vector<JacItem> &items, const 
     HIP_OK(hipStreamSynchronize(s));   // d_refs, d_norm, d_cp are freed on return
 }
 
-void qr_right_factor(QrState &qs, hipStream_t s) {
+void qr_right_factor(QrState &qs, const std::vector<JacMat> &items, hipStream_t s) {
+    for (size_t k = 0; k < qs.qitems.size(); ++k) qs.qitems[k].Z = items[qs.who[k]].Z;   // where the iteration left it
+    upload(qs.d_items, qs.qitems, s);
     launch_qr_embed_z(qs.d_items.as<QrItem>(), (int)qs.qitems.size(), qs.max_elems, s);
     for (int pn = (int)qs.panel_span.size() - 1; pn >= 0; --pn)
         launch_qr_apply(qs.d_back.as<QrApply>() + qs.back_off[pn], qs.back_off[pn + 1] - qs.back_off[pn], s);
 }
 
-// One-sided block Jacobi on every matrix; returns sorted factors in `arena`.
+// Block Jacobi sweeps (svd.hip) on the matrices of more than kJacSmall rows,
+// all in the same launches.  Every matrix has W at the same offset of two
+// planes, and Z, the next Z, Qt and the two G at the same offset of five (the
+// GEMM that applies a sweep's rotations goes from one W and Z to the other).
+struct JacBatch {
+    std::vector<int> who;                       // matrix of each item
+    std::vector<JacItem> items;
+    std::vector<size_t> woff, zoff;
+    size_t nw = 0, nz = 0, npair = 0;           // plane sizes, pairs of 32-row blocks
+    double *W[2] = {}, *Z[2] = {}, *Qt = nullptr, *G = nullptr, *Qr = nullptr, *Gd = nullptr;
+
+    void add(int i, const JacMat &m) {
+        const int np = (m.nv + 63) / 64 * 64;
+        who.push_back(i);
+        woff.push_back(nw);
+        zoff.push_back(nz);
+        nw += round32((size_t)m.nv * m.len);
+        nz += (size_t)np * np;
+        JacItem it{};
+        it.tol = m.tol;
+        it.nv = m.nv;
+        it.np = np;
+        items.push_back(it);
+        npair += np / 64;
+    }
+    size_t doubles() const { return 2 * nw + 5 * nz + 4 * npair * 4096 + 12 * 32; }
+    // Takes the planes from the arena and points the matrices into the first ones.
+    void place(Arena &ar, std::vector<JacMat> &mats) {
+        for (int h = 0; h < 2; ++h) W[h] = ar.take(nw), Z[h] = ar.take(nz);
+        Qt = ar.take(nz);
+        G = ar.take(2 * nz);
+        Qr = ar.take(2 * npair * 4096);
+        Gd = ar.take(2 * npair * 4096);
+        for (size_t k = 0; k < who.size(); ++k) mats[who[k]].W = W[0] + woff[k], mats[who[k]].Z = Z[0] + zoff[k];
+    }
+    // Runs the sweeps, points the matrices at their final W and Z; returns the
+    // number of matrices that did not converge.
+    int run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream_t s);
+};
+
+int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream_t s) {
+    const int n = (int)who.size();
+    if (n == 0) return 0;
+    launch_fill(G, 0.0, (int64_t)(2 * nz), s);   // the padding
+    // slots: 0 W, 1 next W, 2 Z, 3 next Z, 4 Qt, 5 G
+    GemmList gG, gWZ;
+    gG.tb = true;
+    std::vector<JacTask> eig, upd, begt;
+    size_t pair0 = 0;
+    for (int k = 0; k < n; ++k) {
+        JacItem &it = items[k];
+        const int len = mats[who[k]].len, nb = it.np / 64;
+        it.G[0] = G + zoff[k];
+        it.G[1] = G + nz + zoff[k];
+        it.Qt = Qt + zoff[k];
+        it.Qr = Qr + 2 * pair0 * 4096;
+        it.Gd = Gd + 2 * pair0 * 4096;
+        pair0 += nb;
+        for (int a = 0; a < nb; ++a) {
+            eig.push_back(JacTask{k, a, 0, 0});
+            for (int b = a; b < nb; ++b) {
+                for (int c = 0; c < 4; ++c) upd.push_back(JacTask{k, a, b, c});
+                begt.push_back(JacTask{k, a, b, 0});
+            }
+            for (int c = 0; c < 4 * nb; ++c) upd.push_back(JacTask{k, a, -1, c});
+            // rows 64 a .. of G from their diagonal block on
+            const int m = std::min(64, it.nv - 64 * a), cols = it.nv - 64 * a;
+            gG.add_item(5, zoff[k] + (size_t)64 * a * it.np + 64 * a, m, cols, it.np);
+            gG.add_seg(0, woff[k] + (size_t)64 * a * len, len, 0, woff[k] + (size_t)64 * a * len, len, len);
+        }
+        gWZ.add_item(1, woff[k], it.nv, len, len);
+        gWZ.add_seg(4, zoff[k], it.np, 0, woff[k], len, it.nv);
+        gWZ.add_item(3, zoff[k], it.nv, it.nv, it.np);
+        gWZ.add_seg(4, zoff[k], it.np, 2, zoff[k], it.np, it.nv);
+    }
+    for (GemmList *g : {&gG, &gWZ}) {
+        g->pick_tile();
+        g->finish(s);
+    }
+    std::vector<JacTask> tasks = eig;
+    tasks.insert(tasks.end(), upd.begin(), upd.end());
+    tasks.insert(tasks.end(), begt.begin(), begt.end());
+    DevBuf d_items, d_tasks, d_active, d_off;
+    upload(d_items, items, s);
+    upload(d_tasks, tasks, s);
+    const JacTask *t_eig = d_tasks.as<JacTask>(), *t_upd = t_eig + eig.size(), *t_beg = t_upd + upd.size();
+    d_off.ensure(n * sizeof(double));
+    std::vector<int32_t> active(n, 1);
+    std::vector<double> off(n);
+    int cur = 0;
+    for (int sweep = 0;; ++sweep) {
+        Slots sl{};
+        sl.p[0] = W[cur];
+        sl.p[1] = W[cur ^ 1];
+        sl.p[2] = Z[cur];
+        sl.p[3] = Z[cur ^ 1];
+        sl.p[4] = Qt;
+        sl.p[5] = G;
+        gG.launch(GemmPrec::F64, true, sl, s);
+        upload(d_active, active, s);
+        launch_fill(d_off.as<double>(), 0.0, n, s);
+        launch_jac_begin(d_items.as<JacItem>(), t_beg, (int)begt.size(), d_active.as<int32_t>(),
+                         d_off.as<unsigned long long>(), s);
+        if (sweep == 0) HIP_OK(hipMemcpyAsync(Z[0], Qt, nz * sizeof(double), hipMemcpyDeviceToDevice, s));   // I
+        HIP_OK(hipMemcpyAsync(off.data(), d_off.ptr, n * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIP_OK(hipStreamSynchronize(s));
+        int ract = 0;   // rounds of the largest matrix that is not done
+        for (int k = 0; k < n; ++k) {
+            if (active[k] && off[k] <= items[k].tol) active[k] = 0;
+            if (active[k]) ract = std::max(ract, items[k].np / 32 - 1);
+        }
+        if (ract == 0 || sweep == kMaxSweeps) break;
+        sweeps = sweep + 1;
+        rounds += ract;
+        upload(d_active, active, s);
+        for (int r = 0; r <= ract; ++r)
+            launch_jac_round(d_items.as<JacItem>(), t_eig, r < ract ? (int)eig.size() : 0, t_upd, (int)upd.size(), r,
+                             d_active.as<int32_t>(), s);
+        // a converged matrix has Qt = I: its W and Z are carried over as they are
+        gWZ.launch(GemmPrec::F64, true, sl, s);
+        cur ^= 1;
+    }
+    for (int k = 0; k < n; ++k) mats[who[k]].W = W[cur] + woff[k], mats[who[k]].Z = Z[cur] + zoff[k];
+    int bad = 0;
+    for (int k = 0; k < n; ++k) bad += active[k] ? 1 : 0;
+    return bad;
+}
+
+// Block Jacobi on every matrix; returns sorted factors in `arena`.
 // floor (one per matrix, used from depth 1 on): values below it are rounding
 // noise of the block at depth 0, where the recursion stops.  n_unconv is
 // incremented by the number of blocks (at any depth) whose Jacobi iteration
@@ -228,38 +368,49 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
     }
     Arena ar;
     size_t need = 64;
+    std::vector<JacMat> items(nm);
+    JacBatch batch;
     for (int i = 0; i < nm; ++i) {
         const Mat &m = mats[i];
         const size_t nv = std::min(m.nr, m.nc), len = std::max(m.nr, m.nc);
-        need += round32(nv * len) + round32(nv * nv) + round32(nv * m.nr) + round32(nv * m.nc) + round32(nv) + 96;
-        if (pre[i]) need += round32(nv * len) + round32(nv * nv) + round32((nv + kQrPanel - 1) / kQrPanel * 256) + 96;
-    }
-    ar.reserve(need);
-    std::vector<JacItem> items(nm);
-    std::vector<CopyTask> cp;
-    // per preconditioned matrix: A (QR storage), the copy of M (later Y), R, T
-    std::vector<double *> qa(nm, nullptr), qm(nm, nullptr), qt(nm, nullptr);
-    for (int i = 0; i < nm; ++i) {
-        const Mat &m = mats[i];
-        const bool wide = m.nr <= m.nc;
-        const int nv = std::min(m.nr, m.nc), len = std::max(m.nr, m.nc);
-        // the Jacobi kernel addresses W and Z with 32-bit byte offsets
+        // the kernels address W and Z with 32-bit byte offsets
         PD_REQUIRE((int64_t)nv * len * 8 < (int64_t(1) << 31), PDMRG_EINVAL, "svd: block too large");
-        items[i].nv = nv;
-        items[i].len = pre[i] ? nv : len;
+        items[i].nv = (int)nv;
+        items[i].len = (int)(pre[i] ? nv : len);
         // each matrix on its own tolerance, so a matrix's rotations do not
         // depend on which others share its launches
         items[i].tol = std::max(1e-14, 8.0 * 2.220446049250313e-16 * std::sqrt((double)items[i].len));
-        double *wm = ar.take((size_t)nv * len);
-        if (pre[i]) {
-            qm[i] = wm;
+        need += round32(nv * m.nr) + round32(nv * m.nc) + 64;
+        if (pre[i]) need += 2 * round32(nv * len) + round32((nv + kQrPanel - 1) / kQrPanel * 256) + 96;
+        if ((int)nv > kJacSmall) {
+            items[i].ldz = (int)((nv + 63) / 64 * 64);
+            batch.add(i, items[i]);
+        } else {
+            items[i].ldz = (int)nv;
+            need += round32(nv * items[i].len) + round32(nv * nv) + 64;
+        }
+    }
+    ar.reserve(need + batch.doubles());
+    batch.place(ar, items);
+    std::vector<CopyTask> cp;
+    // per preconditioned matrix: A (QR storage), the copy of M (later Y), T
+    std::vector<double *> qa(nm, nullptr), qm(nm, nullptr), qt(nm, nullptr);
+    std::vector<JacSmall> small;
+    for (int i = 0; i < nm; ++i) {
+        const Mat &m = mats[i];
+        const bool wide = m.nr <= m.nc;
+        const int nv = items[i].nv, len = std::max(m.nr, m.nc);
+        if (nv <= kJacSmall) {
+            items[i].W = ar.take((size_t)nv * items[i].len);
+            items[i].Z = ar.take((size_t)nv * nv);
+            small.push_back(JacSmall{items[i].W, items[i].Z, items[i].tol, nv, items[i].len});
+        }
+        double *wm = items[i].W;
+        if (pre[i]) {   // W receives the rows of R
+            wm = qm[i] = ar.take((size_t)nv * len);
             qa[i] = ar.take((size_t)nv * len);
             qt[i] = ar.take((size_t)(nv + kQrPanel - 1) / kQrPanel * 256);
-            items[i].W = ar.take((size_t)nv * nv);   // rows of R
-        } else {
-            items[i].W = wm;
         }
-        items[i].Z = ar.take((size_t)nv * nv);
         out[i].nr = m.nr;
         out[i].nc = m.nc;
         out[i].k = nv;
@@ -278,72 +429,25 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
     run_copies(cp, s);
     QrState qs;
     if (any_pre) qr_factor(mats, items, pre, qa, qm, qt, qs, s);
-    DevBuf d_items;
-    upload(d_items, items, s);
-    int max_nv = 0;
-    for (auto &it : items) max_nv = std::max(max_nv, it.nv);
-    launch_identity(d_items.as<JacItem>(), nm, max_nv, s);
-
-    // circle schedule over blocks of 8 rows
-    std::vector<int> nblk(nm);
-    int rmax = 0;
-    for (int i = 0; i < nm; ++i) {
-        int nb = std::max(2, (items[i].nv + kJacBlock - 1) / kJacBlock);
-        if (nb % 2) ++nb;
-        nblk[i] = nb;
-        rmax = std::max(rmax, nb - 1);
-    }
-    std::vector<std::vector<JacPair>> rounds(rmax);
-    for (int i = 0; i < nm; ++i) {
-        const int nb = nblk[i], real = (items[i].nv + kJacBlock - 1) / kJacBlock;
-        for (int r = 0; r < nb - 1; ++r)
-            for (int l = 0; l < nb / 2; ++l) {
-                const int p = (l == 0) ? nb - 1 : (r + l) % (nb - 1);
-                const int q = (r - l + (nb - 1)) % (nb - 1);
-                if (p >= real && q >= real) continue;
-                rounds[r].push_back(JacPair{i, std::min(p, q), std::max(p, q), 0});
-            }
-    }
-    std::vector<JacPair> flat;
-    std::vector<int> roff(rmax + 1, 0);
-    for (int r = 0; r < rmax; ++r) {
-        roff[r] = (int)flat.size();
-        flat.insert(flat.end(), rounds[r].begin(), rounds[r].end());
-    }
-    roff[rmax] = (int)flat.size();
-    DevBuf d_pairs, d_active, d_off;
-    upload(d_pairs, flat, s);
-    std::vector<int32_t> active(nm, 1);
-    d_off.ensure(std::max(nm, 1) * sizeof(unsigned long long));
-
     int sweeps_done = 0, nrounds = 0;
-    for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-        sweeps_done = sweep + 1;
-        upload(d_active, active, s);
-        launch_fill(d_off.as<double>(), 0.0, nm, s);
-        // rounds past every active matrix's last hold only pairs of converged
-        // matrices, which do nothing: not launched
-        int ract = 0;
-        for (int i = 0; i < nm; ++i)
-            if (active[i]) ract = std::max(ract, nblk[i] - 1);
-        nrounds += ract;
-        for (int r = 0; r < ract; ++r)
-            launch_jac_round(d_items.as<JacItem>(), d_pairs.as<JacPair>() + roff[r], roff[r + 1] - roff[r],
-                             d_active.as<int32_t>(), d_off.as<unsigned long long>(), s);
-        std::vector<double> off(nm);
-        HIP_OK(hipMemcpyAsync(off.data(), d_off.ptr, nm * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_OK(hipStreamSynchronize(s));
-        bool any = false;
-        for (int i = 0; i < nm; ++i) {
-            if (active[i] && off[i] <= items[i].tol) active[i] = 0;
-            any = any || active[i];
+    DevBuf d_small, d_done;
+    std::vector<int32_t> done(small.size(), 0);
+    if (!small.empty()) {
+        // by size, one launch per size class of the kernel
+        std::stable_sort(small.begin(), small.end(), [](const JacSmall &a, const JacSmall &b) { return a.nv < b.nv; });
+        upload(d_small, small, s);
+        d_done.ensure(small.size() * sizeof(int32_t));
+        for (size_t a = 0, b = 0; a < small.size(); a = b) {
+            const int top = small[a].nv <= 16 ? 16 : small[a].nv <= 32 ? 32 : kJacSmall;
+            while (b < small.size() && small[b].nv <= top) ++b;
+            launch_jac_small(d_small.as<JacSmall>() + a, (int)(b - a), top, kMaxSweeps, d_done.as<int32_t>() + a, s);
         }
-        if (!any) break;
+        HIP_OK(hipMemcpyAsync(done.data(), d_done.ptr, small.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     }
     // blocks whose rows were not orthogonal to tol after kMaxSweeps sweeps:
     // still an exact rotation of the block (absolute accuracy), reported
-    for (int i = 0; i < nm; ++i) n_unconv += active[i] ? 1 : 0;
-    if (any_pre) qr_right_factor(qs, s);
+    n_unconv += batch.run(items, sweeps_done, nrounds, s);
+    if (any_pre) qr_right_factor(qs, items, s);
     if (ctx->verbose >= 2) {
         int big = 0, npre = 0;
         for (int i = 0; i < nm; ++i) {
@@ -371,6 +475,7 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
     if (!refs.empty())
         HIP_OK(hipMemcpyAsync(norms.data(), d_norm.ptr, refs.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
+    for (int32_t d : done) n_unconv += d < 0 ? 1 : 0;
 
     // sorted factors: wide Ut = Z rows, Vt = W rows / lambda; tall the reverse
     std::vector<double> scales;
@@ -388,7 +493,7 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
             const double l = norms[first[i] + perm[j]];
             out[i].lam[j] = l;
             const double *wrow = items[i].W + (size_t)perm[j] * items[i].len;
-            const double *zrow = items[i].Z + (size_t)perm[j] * nv;
+            const double *zrow = items[i].Z + (size_t)perm[j] * items[i].ldz;
             const double inv = l > 0.0 ? 1.0 / l : 0.0;
             if (pre[i]) {
                 // X P = Q R with R = Z^T D: the D row (W side) scattered back

@@ -1,32 +1,26 @@
-// Batched one-sided block-Jacobi SVD kernels (FP64) for the truncation step.
+// Batched block-Jacobi SVD kernels (FP64) for the truncation step.
 //
-// Each matrix is stored as nv row vectors of length len (W, row-major).  One
-// Jacobi round rotates disjoint pairs of 8-row blocks: a workgroup forms the
-// 16 x 16 Gram matrix of its two blocks, applies one cyclic Jacobi sweep to it
-// in LDS and replaces the rows by the resulting combinations, sorted by
-// decreasing norm; the same rotation is applied to the accumulator Z (nv x nv,
-// starts at I).  Rounds follow the circle schedule, so every block pair meets
-// once per sweep.  When no pair of a sweep needed a rotation (relative
-// off-diagonal |G_ij| / sqrt(G_ii G_jj) <= tol) the rows are orthogonal:
-// W = Z M, row norms are the singular values.
+// Each matrix is stored as nv row vectors of length len (W, row-major); Z (nv x
+// nv, starts at I) accumulates the rotations.  An outer sweep forms the Gram
+// matrix G = W W^T afresh (grouped GEMM), runs one cyclic two-sided
+// block-Jacobi sweep on G, accumulating its rotations in Qt, and applies them,
+// W <- Qt W and Z <- Qt Z (one grouped GEMM launch).  When a fresh G has |G_ij|
+// <= tol sqrt(G_ii G_jj) everywhere the rows are orthogonal and their norms
+// are the singular values.  Convergence is only ever judged on a fresh G, and
+// Qt is a product of rotations orthogonal to working precision, so nothing of
+// a sweep's updated G goes into the result.  (W = Z W0 in place of W <- Qt W
+// saves a product but loses the small rows of a badly ordered graded block.)
 //
-// Rows of W and Z are staged in LDS in 512-column chunks, both first chunks
-// fetched at entry with all loads in flight; global accesses are raw buffer
-// operations whose out-of-range offsets read zero / drop the store, so rows
-// absent from the matrix need no branches.  The Gram matrix and the row
-// rotations are 16 x 16 x K products on the FP64 matrix cores
-// (v_mfma_f64_16x16x4).  A round of the inner sweep applies its 8 disjoint
-// rotations J as A <- J^T A J, Q <- Q J from the previous round's copy
-// (double buffer), one barrier per round: every wave computes the 8 angles
-// itself (one pair per lane) and hands them to the lanes that use them by
-// cross-lane shuffles while the operands of the update are already being
-// read, since a round's partner indices follow from the schedule alone.
-//
-// Measured alternatives: 16-row blocks (32 x 32 inner problem) halve the
-// rounds per sweep but cost more than twice as much per round; up to three
-// inner sweeps per meeting save fewer outer rounds than they cost; 8 waves
-// (W and Z rotated by separate halves at once) and the inner sweep in one
-// wave without workgroup barriers are no faster.
+// A sweep has np / 32 - 1 rounds (circle schedule over blocks of 32 rows, np =
+// nv padded to a multiple of 64) and one launch more (jac_round_kernel): per
+// pair of blocks one cyclic Jacobi sweep of the 64 x 64 sub-matrix of G in one
+// workgroup, and beside it the previous round's G <- J^T G J and Qt <- J^T Qt
+// on the FP64 matrix cores.  What bounds it is the chain of inner rotation
+// rounds: a sweep takes about 2 nv of them whatever the block size, so the
+// time goes down with the cost of one inner round and with the launches and
+// loads around them.  Blocks of 32 rows have a quarter of the launches of
+// blocks of 8 and need fewer sweeps.
+// Matrices of at most 64 rows run whole in one workgroup (jac_small_kernel).
 //
 // Also here: the Householder QR that preconditions the iteration (panel and
 // reflector-application kernels, below) and the copy / norm helpers.
@@ -39,12 +33,11 @@ namespace pdmrg {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
-constexpr int JB = 8;            // rows per block
-constexpr int J2 = 2 * JB;       // rows of a pair
-constexpr int M = J2 - 1;        // circle schedule modulus
-constexpr int JT = 256;          // 4 waves; one 16 x 16 entry per thread
-constexpr int CH = 512;          // columns staged in LDS at a time
+constexpr int J2 = 16;           // target rows of a reflector application
+constexpr int JT = 256;          // its threads (4 waves)
+constexpr int CH = 512;          // its columns staged in LDS at a time
 constexpr int U = J2 * CH / JT;  // staged elements per thread and chunk
 static_assert(J2 * CH % JT == 0 && CH % 16 == 0, "chunk must split evenly over the threads and 16-column steps");
 constexpr unsigned kOut = 0x80000000u;   // buffer offset past every record
@@ -68,267 +61,708 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned off, d
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, 0, 0);
 }
 
-// Circle schedule on J2 = M + 1 positions, round r: position M meets r, every
-// other position i meets (2 r - i) mod M.  Pair l (0 <= l < J2 / 2) is
-// {M, r} for l = 0 and {(r + l) mod M, (r - l) mod M} otherwise.
-__device__ __forceinline__ int sched_partner(int i, int r) {
-    if (i == M) return r;
-    if (i == r) return M;
-    return (2 * r - i + 2 * M) % M;
-}
-__device__ __forceinline__ int sched_pair(int i, int r) {
-    if (i == M || i == r) return 0;
-    const int d = (i - r + M) % M;
-    return d <= M / 2 ? d : M - d;
-}
-
-// Rotation that zeroes a_pq of the symmetric 2 x 2 block (app, apq, aqq),
-// p < q: column p becomes c col_p - s col_q, column q becomes s col_p + c col_q,
-// with t = tan(angle) = 2 a_pq / (d + sign(d) sqrt(d^2 + 4 a_pq^2)),
-// d = a_qq - a_pp (the root of smaller magnitude, |t| <= 1), c = 1 / sqrt(1 + t^2),
-// s = t c.  d and 2 a_pq are first scaled by a power of two so the larger
-// magnitude lies in [1/2, 1); then u = d^2 + 4 a_pq^2 lies in [1/4, 2],
-// |d| + sqrt(u) in [1/2, 3] and 1 + t^2 in [1, 2], so hardware reciprocal and
-// reciprocal square root estimates refined by Newton-type steps give full
-// precision without range handling.
-// The angle only decides how well a_pq is annihilated; the rotation is
-// orthogonal to working precision whatever t is, because c and s follow from
-// t.  Skipped (c = 1, s = 0) when a_pq^2 <= 1e-32 |a_pp a_qq| (the relative
-// rule that resolves the small eigenvalues of a graded Gram matrix).
-__device__ __forceinline__ void jacobi_angle(double app, double apq, double aqq, double &c, double &s) {
-    const double d0 = aqq - app;
-    const double big = fmax(fabs(d0), fabs(2.0 * apq));
-    const int e = big > 0.0 ? __builtin_amdgcn_frexp_exp(big) : 0;
-    const double d = __builtin_amdgcn_ldexp(d0, -e), a2 = __builtin_amdgcn_ldexp(2.0 * apq, -e);
-    // h = sqrt(u): Goldschmidt iteration from the reciprocal square root estimate
-    const double u = fma(d, d, a2 * a2);
-    const double y0 = __builtin_amdgcn_rsq(u);
-    double g = u * y0, hh = 0.5 * y0;
-    const double r = fma(-hh, g, 0.5);
-    g = fma(g, r, g);
-    hh = fma(hh, r, hh);
-    const double h = fma(fma(-g, g, u), hh, g);
-    // t = a2 / den: reciprocal estimate and two Newton steps
-    const double den = d >= 0.0 ? d + h : d - h;
-    double q = __builtin_amdgcn_rcp(den);
-    q = fma(q, fma(-den, q, 1.0), q);
-    q = fma(q, fma(-den, q, 1.0), q);
-    const double t = a2 * q;
-    // c = (1 + t^2)^(-1/2): estimate y, w = 1 - v y^2, c = y (1 + w / 2 + 3 w^2 / 8)
-    const double v = fma(t, t, 1.0);
+// Rotation that zeroes a_pq of the symmetric 2 x 2 block (app, apq, aqq):
+// column p becomes c col_p - s col_q, column q becomes s col_p + c col_q.  With
+// d = a_qq - a_pp, h = sqrt(d^2 + 4 a_pq^2), y = 1 / h: the smaller angle has
+// c^2 = (1 + |d| y) / 2, s = sign(d) a_pq y / c, t = s / c, so the chain holds
+// two reciprocal square roots and no division.  d and 2 a_pq are first scaled
+// by a power of two so the larger magnitude lies in [1/2, 1); then u = h^2
+// lies in [1/4, 2] and c^2 in [1/2, 1], and hardware estimates with one
+// third-order step each give full precision without range handling.  Skipped
+// (c = 1, s = 0) when a_pq^2 <= 1e-32 |a_pp a_qq| (the relative rule that
+// resolves the small eigenvalues of a graded Gram matrix).
+__device__ __forceinline__ double rsqrt_full(double v) {
     const double y = __builtin_amdgcn_rsq(v);
-    const double w = fma(-v * y, y, 1.0);
-    const double ct = fma(y * w, fma(w, 0.375, 0.5), y);
-    const bool skip = apq == 0.0 || apq * apq <= 1e-32 * fabs(app * aqq);
-    c = skip ? 1.0 : ct;
-    s = skip ? 0.0 : t * ct;
+    const double e = fma(-v * y, y, 1.0);              // y sqrt(v) = (1 - e)^(1/2)
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ void jacobi_angle(double app, double apq, double aqq, double &c, double &s, double &t,
+                                             bool &skip) {
+    const double d0 = aqq - app, b0 = 2.0 * apq;
+    const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(d0), fabs(b0)));
+    const double d = __builtin_amdgcn_ldexp(d0, e), b = __builtin_amdgcn_ldexp(b0, e);
+    const double y = rsqrt_full(fma(d, d, b * b));
+    const double c2 = fma(0.5 * fabs(d), y, 0.5);
+    const double z = rsqrt_full(c2);
+    const double h = copysign(0.5, d) * b * y;         // s c
+    skip = apq == 0.0 || apq * apq <= 1e-32 * fabs(app * aqq);
+    c = skip ? 1.0 : c2 * z;
+    s = skip ? 0.0 : h * z;
+    t = skip ? 0.0 : h * (z * z);
 }
 
-__global__ __launch_bounds__(JT) void jac_pair_kernel(const JacItem *__restrict__ items,
-                                                      const JacPair *__restrict__ pairs,
-                                                      const int32_t *__restrict__ active,
-                                                      unsigned long long *__restrict__ offmax) {
-    const JacPair pr = pairs[blockIdx.x];
-    const JacItem it = items[pr.item];
-    if (!active[pr.item]) return;
-    __shared__ double wrows[J2][CH + 1];   // W rows, current chunk
-    __shared__ double zrows[J2][CH + 1];   // Z rows, current chunk
-    __shared__ double Gp[4][J2][J2 + 1];
-    __shared__ double A[2][J2][J2 + 1];
-    __shared__ double Q[2][J2][J2 + 1];
-    __shared__ int ev[J2];
-    __shared__ double wred[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r16 = lane & 15, g = lane >> 4;
-    if (tid < J2) ev[tid] = tid;
-    // rows of the pair present in the matrix form a prefix 0..n-1 (only the
-    // last block of a matrix is partial, and a pair never holds two blocks
-    // past it)
-    const int n = min(max(it.nv - pr.bi * JB, 0), JB) + min(max(it.nv - pr.bj * JB, 0), JB);
-    auto grow = [&](int r) { return r < JB ? pr.bi * JB + r : pr.bj * JB + (r - JB); };
-    const __amdgpu_buffer_rsrc_t rW = rows_rsrc(it.W, (int64_t)it.nv * it.len);
-    const __amdgpu_buffer_rsrc_t rZ = rows_rsrc(it.Z, (int64_t)it.nv * it.nv);
+// ---------------------------------------------------------------------------
+// One cyclic Jacobi sweep of a symmetric matrix of 2 P rows (P = 32, 16, 8) in
+// one workgroup of 1 + NA + NQ waves.  Indices sit on 2 P positions, pair i =
+// (t_i, b_i) = positions 2 i and 2 i + 1, and move after every round (t_0
+// stays, b_0 -> t_1, t_i -> t_i+1, the last t -> the last b, b_i -> b_i-1), so
+// 2 P - 1 rounds meet every pair once and end where they began.  Position t_i
+// starts with row i, b_i with row P + i.
+//   D wave (lanes 0 .. P - 1): the diagonal blocks.  Lane i computes pair i's
+//     angle.  It takes the next round's a_pq from the block that holds it
+//     before its rotation (the entry is rotated here as well), so that angles
+//     and block rotations run side by side, one barrier a round;
+//   A waves: a thread takes some of the P (P - 1) / 2 blocks (2 x 2) of pairs i
+//     < j, rotates them from both sides and hands their entries to the blocks
+//     they move to (fixed LDS addresses);
+//   Q waves: lane = row of Q, P / NQ pairs of columns in registers; only the
+//     columns that cross to another wave go through LDS.
+// In round k the D wave computes rotation k while A and Q apply rotation k - 1.
+// The round's length is the D wave's chain (LDS read, about 25 dependent FP64
+// operations, LDS write, barrier) or, for P = 32, the LDS traffic of the A and
+// the lane broadcasts of the Q waves: 0.45 us a round with 4 A and 8 Q waves,
+// 0.30 us with the D wave alone; 0.48 with 3 and 8, 0.46 with 8 and 4.
+template <int P>
+struct EigCfg;
+template <> struct EigCfg<32> { static constexpr int NA = 4, NQ = 8, INV2 = 16; };
+template <> struct EigCfg<16> { static constexpr int NA = 2, NQ = 2, INV2 = 8; };
+template <> struct EigCfg<8> { static constexpr int NA = 1, NQ = 1, INV2 = 4; };
+constexpr int eig_threads(int p) { return p == 32 ? 64 * 13 : p == 16 ? 64 * 5 : 64 * 3; }
+// Blocks (i, j) lie in P - 1 rows of P / 2 (the circle schedule on P pairs); the
+// row stride is odd because the D wave reads blocks (i - 1, i + 1), one a row.
+template <int P>
+struct EigLds {
+    static constexpr int kRow = P / 2 + 1, kTrash = (P - 1) * kRow, kEnt = kTrash + P / 2 + 1;
+    double ex[2][4][kEnt];       // entries (2 x + y) of the off-diagonal blocks
+    d2 cs[2][P];                 // rotations (c, s) of the pairs
+    double dg[2][2 * P];         // diagonal by position
+    double qx[2][EigCfg<P>::NQ][2][64];   // columns of Q leaving a wave: its last t, its first b
+    int rank[64];                // rank of a row's eigenvalue, descending
+    int any;
+};
 
-    // Element u of this thread in a chunk: flat index e = u JT + tid of the
-    // J2 x CH chunk, row e / CH, column e % CH (consecutive threads take
-    // consecutive columns of one row).
-    auto load_chunk = [&](__amdgpu_buffer_rsrc_t rs, int len, int c0, double (&v)[U]) {
+// LDS place of block (i, j), i < j, of the circle schedule on P pairs.
+template <int P>
+__device__ __forceinline__ int eig_block(int i, int j) {
+    constexpr int M = P - 1;
+    if (j == M) return EigLds<P>::kRow * i;
+    const int r = (i + j) * EigCfg<P>::INV2 % M;
+    const int d = (i - r + M) % M;
+    return EigLds<P>::kRow * r + (d < P / 2 ? d : M - d);
+}
+template <int P>
+__device__ __forceinline__ int eig_dest(int p) {
+    if (p & 1) return p == 1 ? 2 : p - 2;
+    return p == 0 ? 0 : p == 2 * P - 2 ? 2 * P - 1 : p + 2;
+}
+// LDS index [entry][block] of the entry at positions (p, q) of different pairs.
+template <int P>
+__device__ __forceinline__ int eig_slot(int p, int q) {
+    const int lo = min(p >> 1, q >> 1), hi = max(p >> 1, q >> 1);
+    const int x = (p >> 1) < (q >> 1) ? p & 1 : q & 1, y = (p >> 1) < (q >> 1) ? q & 1 : p & 1;
+    return (2 * x + y) * EigLds<P>::kEnt + eig_block<P>(lo, hi);
+}
+
+// v of lane l, in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int l) {
+    const u2 b = __builtin_bit_cast(u2, v);
+    return __builtin_bit_cast(double, u2{(unsigned)__builtin_amdgcn_readlane((int)b.x, l),
+                                         (unsigned)__builtin_amdgcn_readlane((int)b.y, l)});
+}
+
+// at(r, c): entry (r, c) of the symmetric matrix, r and c in 0 .. 2 P - 1.  Rows
+// at and past n are absent (zero).  Returns true (uniformly) if a rotation was
+// needed; then put(o, k, v) receives row o, column k of the rotation (new row
+// o = sum_k v old row k; rows sorted by decreasing diagonal, absent ones in
+// place) and put_g(r, c, v) every entry (r, c) of the rotated matrix.  Called
+// by all eig_threads(P) threads of the workgroup.
+template <int P, class At, class Put, class PutG>
+__device__ __forceinline__ bool eig_sweep(EigLds<P> &L, int n, double tol, At at, Put put, PutG put_g) {
+    using Lds = EigLds<P>;
+    constexpr int NA = EigCfg<P>::NA, NQ = EigCfg<P>::NQ, NW = 1 + NA + NQ, R = 2 * P - 1;   // R rounds
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool isD = wave == 0, isA = !isD && wave <= NA;
+    // A: the blocks of this thread
+    constexpr int kBlk = (P * (P - 1) / 2 + 64 * NA - 1) / (64 * NA);
+    int bi[kBlk], bj[kBlk], blk[kBlk], dst[kBlk][4];
+    double a0[kBlk][4];
+    if (isA) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = u * JT + tid, r = e / CH, c = c0 + e % CH;
-            const unsigned off = (r < n && c < len) ? (unsigned)(((int64_t)grow(r) * len + c) * 8) : kOut;
-            v[u] = bload(rs, off);
-        }
-    };
-    auto store_chunk = [&](double (*dst)[CH + 1], const double (&v)[U]) {
+        for (int u = 0; u < kBlk; ++u) {
+            const int b = tid - 64 + 64 * NA * u, r = b / (P / 2), l = b % (P / 2);
+            const bool on = r < P - 1;
+            const int p = l == 0 ? P - 1 : (r + l) % (P - 1), q = (r - l + P - 1) % (P - 1);
+            bi[u] = on ? min(p, q) : 0;
+            bj[u] = on ? max(p, q) : 1;
+            blk[u] = on ? Lds::kRow * r + l : Lds::kTrash + l;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = u * JT + tid;
-            dst[e / CH][e % CH] = v[u];
+            for (int e = 0; e < 4; ++e) {
+                const int dp = eig_dest<P>(2 * bi[u] + (e >> 1)), dq = eig_dest<P>(2 * bj[u] + (e & 1));
+                // an entry that joins a diagonal block goes to an unused slot
+                dst[u][e] = !on || (dp >> 1) == (dq >> 1) ? Lds::kTrash + l : eig_slot<P>(dp, dq);
+                a0[u][e] = on ? at(bi[u] + P * (e >> 1), bj[u] + P * (e & 1)) : 0.0;
+                L.ex[0][e][blk[u]] = a0[u][e];
+            }
         }
-    };
-    {
-        double v[U], z[U];
-        load_chunk(rW, it.len, 0, v);
-        load_chunk(rZ, it.nv, 0, z);
-        store_chunk(wrows, v);
-        store_chunk(zrows, z);
     }
+    // D: pair i of this lane (the lanes past P repeat it)
+    const int di = lane % P;
+    double app = 0, aqq = 0, apq = 0;
+    if (isD) {
+        app = at(di, di);
+        aqq = at(P + di, P + di);
+        apq = at(di, P + di);
+        if (lane < P) {
+            L.dg[0][2 * di] = app;
+            L.dg[0][2 * di + 1] = aqq;
+        }
+        L.rank[lane] = lane < n ? 0 : lane;
+        if (lane == 0) L.any = 0;
+    }
+    __syncthreads();
+    // whether any relative off-diagonal exceeds tol
+    bool big = false;
+    auto rel = [&](double a, int p, int q) {
+        const double dd = L.dg[0][p] * L.dg[0][q];
+        big = big || (dd > 0.0 && a * a > tol * tol * dd);
+    };
+    if (isA)
+#pragma unroll
+        for (int u = 0; u < kBlk; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rel(a0[u][e], 2 * bi[u] + (e >> 1), 2 * bj[u] + (e & 1));
+    if (isD) rel(apq, 2 * di, 2 * di + 1);
+    if (__ballot(big) && lane == 0) L.any = 1;
+    __syncthreads();
+    if (!L.any) return false;
 
-    // ---- Gram matrix G = Wp Wp^T (Wp: the 16 rows).  MFMA j of a 16-wide K
-    // step takes k = kk + 4 g + j from lane group g; A and B operands are the
-    // same element Wp[r16][k]; the four waves split K and their partial tiles
-    // are summed in a fixed order.
-    const int nch = (it.len + CH - 1) / CH;
-    {
-        d4 acc = {0.0, 0.0, 0.0, 0.0};
-        for (int ch = 0; ch < nch; ++ch) {
-            const int c0 = ch * CH;
-            if (ch > 0) {
-                double v[U];
-                load_chunk(rW, it.len, c0, v);
-                __syncthreads();
-                store_chunk(wrows, v);
+    // Every role runs its own loop of the R + 1 iterations (one barrier each),
+    // so no wave carries another role's registers through the loop.
+    constexpr int NP = P / NQ;
+    const int qw = wave - 1 - NA;
+    double qt[NP], qb[NP];   // Q: columns of pairs NP qw .., lane = row
+    if (isA) {
+        double *e0 = &L.ex[0][0][0], *e1 = &L.ex[1][0][0];
+        auto step = [&](const double *from, double *to, const d2 *cs) {
+            double x[kBlk][4];
+            d2 ri[kBlk], rj[kBlk];
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) {
+                ri[u] = cs[bi[u]];
+                rj[u] = cs[bj[u]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[u][e] = from[e * Lds::kEnt + blk[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < kBlk; ++u) {
+                const double u00 = ri[u].x * x[u][0] - ri[u].y * x[u][2], u01 = ri[u].x * x[u][1] - ri[u].y * x[u][3];
+                const double u10 = ri[u].y * x[u][0] + ri[u].x * x[u][2], u11 = ri[u].y * x[u][1] + ri[u].x * x[u][3];
+                to[dst[u][0]] = rj[u].x * u00 - rj[u].y * u01;
+                to[dst[u][1]] = rj[u].y * u00 + rj[u].x * u01;
+                to[dst[u][2]] = rj[u].x * u10 - rj[u].y * u11;
+                to[dst[u][3]] = rj[u].y * u10 + rj[u].x * u11;
+            }
+        };
+        __syncthreads();
+        for (int k = 1; k < R; k += 2) {
+            step(e0, e1, L.cs[0]);
+            __syncthreads();
+            step(e1, e0, L.cs[1]);
+            __syncthreads();
+        }
+        step(e0, e1, L.cs[0]);   // k = R: the final state, in ex[1]
+        __syncthreads();
+    } else if (isD) {
+        // where a_pq of the next round stands before its rotation, and where
+        // this pair's rotated diagonal and (zeroed) off-diagonal entry go
+        const int st = di == 0 ? 0 : di == 1 ? 1 : 2 * di - 2, sb = di == P - 1 ? 2 * P - 2 : 2 * di + 3;
+        const int sP = st >> 1, sQ = sb >> 1, sBlk = eig_block<P>(sP, sQ);
+        const bool sx = st & 1, sy = sb & 1;
+        const int dT = eig_dest<P>(2 * di), dB = eig_dest<P>(2 * di + 1), rslot = eig_slot<P>(dT, dB);
+        double resid = 0.0;
+        auto rotate = [&](int cur) {
+            double c, s, t;
+            bool skip;
+            jacobi_angle(app, apq, aqq, c, s, t, skip);
+            resid = skip ? apq : 0.0;
+            if (lane < P) {
+                L.cs[cur][di] = d2{c, s};
+                L.dg[cur ^ 1][dT] = fma(-t, apq, app);
+                L.dg[cur ^ 1][dB] = fma(t, apq, aqq);
             }
             __syncthreads();
-            const int w = min(CH, it.len - c0);
-            for (int kk = wave * 16; kk < w; kk += 64) {
-                double v[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = wrows[r16][kk + 4 * g + j];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc = mfma_f64(v[j], v[j], acc);
-            }
+        };
+        auto fetch = [&](int cur) {
+            const int prv = cur ^ 1;
+            const double *e = &L.ex[prv][0][0];
+            const double b00 = e[sBlk], b01 = e[Lds::kEnt + sBlk], b10 = e[2 * Lds::kEnt + sBlk],
+                         b11 = e[3 * Lds::kEnt + sBlk];
+            const d2 rp = L.cs[prv][sP], rq = L.cs[prv][sQ];
+            app = L.dg[cur][2 * di];
+            aqq = L.dg[cur][2 * di + 1];
+            const double r0 = sx ? rp.y : rp.x, r1 = sx ? rp.x : -rp.y;
+            const double q0 = sy ? rq.y : rq.x, q1 = sy ? rq.x : -rq.y;
+            const double u0 = r0 * b00 + r1 * b10, u1 = r0 * b01 + r1 * b11;
+            apq = q0 * u0 + q1 * u1;
+            if (lane < P) (&L.ex[cur][0][0])[rslot] = resid;
+        };
+        __builtin_amdgcn_s_setprio(3);
+        rotate(0);
+        for (int k = 1; k < R; k += 2) {
+            fetch(1);
+            rotate(1);
+            fetch(0);
+            rotate(0);
         }
-        // v_mfma_f64_16x16x4 result: register r of lane l is row 4 r + l / 16, column l % 16
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Gp[wave][4 * r + g][r16] = acc[r];
-    }
-    __syncthreads();
-    const int ei = tid / J2, ej = tid % J2;   // this thread's entry of the 16 x 16 matrices
-    const double gij = ((Gp[0][ei][ej] + Gp[1][ei][ej]) + Gp[2][ei][ej]) + Gp[3][ei][ej];
-    A[0][ei][ej] = gij;
-    __syncthreads();
-    // ---- relative off-diagonal of this pair
-    double off = 0.0;
-    if (ei < ej && ej < n) {
-        const double dd = A[0][ei][ei] * A[0][ej][ej];
-        if (dd > 0.0) off = fabs(gij) / sqrt(dd);
-    }
-    for (int w = 32; w > 0; w >>= 1) off = fmax(off, __shfl_xor(off, w));
-    if (lane == 0) wred[wave] = off;
-    __syncthreads();
-    const double poff = fmax(fmax(wred[0], wred[1]), fmax(wred[2], wred[3]));
-    if (tid == 0) atomicMax(&offmax[pr.item], (unsigned long long)__double_as_longlong(poff));
-    if (poff <= it.tol) return;
-    // rows absent from the matrix: isolated with eigenvalue -1 (never rotated)
-    A[0][ei][ej] = (ei >= n || ej >= n) ? (ei == ej ? -1.0 : 0.0) : gij;
-    Q[0][ei][ej] = ei == ej ? 1.0 : 0.0;
-    __syncthreads();
-
-    // ---- one cyclic Jacobi sweep on the 16 x 16 Gram matrix.  A partial
-    // diagonalisation is still an exact rotation of the rows; the outer
-    // iteration measures orthogonality on fresh Gram matrices.
-    int cur = 0;
-    const int lp = lane % (J2 / 2);   // the pair whose angle this lane computes
-    for (int r = 0; r < M; ++r) {
-        const double(*Ac)[J2 + 1] = A[cur];
-        const double(*Qc)[J2 + 1] = Q[cur];
-        const int pa = lp == 0 ? M : (r + lp) % M, pb = (r - lp + M) % M;
-        const int lo = min(pa, pb), hi = max(pa, pb);
-        const double app = Ac[lo][lo], apq = Ac[lo][hi], aqq = Ac[hi][hi];
-        const int pi = sched_partner(ei, r), pj = sched_partner(ej, r);
-        const double a0 = Ac[ei][ej], a1 = Ac[ei][pj], a2 = Ac[pi][ej], a3 = Ac[pi][pj];
-        const double q0 = Qc[ei][ej], q1 = Qc[ei][pj];
-        double c, s;
-        jacobi_angle(app, apq, aqq, c, s);
-        // the lower index of a pair takes -s, the upper +s
-        const int li = sched_pair(ei, r), lj = sched_pair(ej, r);
-        const double ci = __shfl(c, li), si = __shfl(s, li);
-        const double cj = __shfl(c, lj), sj = __shfl(s, lj);
-        const double oi = ei < pi ? -si : si, oj = ej < pj ? -sj : sj;
-        A[cur ^ 1][ei][ej] = ci * (cj * a0 + oj * a1) + oi * (cj * a2 + oj * a3);
-        Q[cur ^ 1][ei][ej] = cj * q0 + oj * q1;
+        fetch(1);   // k = R: the final diagonal blocks
+        __builtin_amdgcn_s_setprio(0);
         __syncthreads();
-        cur ^= 1;
-    }
-    // rank of each present row's eigenvalue, descending (ties: lower index first)
-    if (tid < n) {
-        const double di = A[cur][tid][tid];
-        int rank = 0;
+    } else {
 #pragma unroll
-        for (int j = 0; j < J2; ++j) {
-            const double dj = A[cur][j][j];
-            rank += (j < n && (dj > di || (dj == di && j < tid))) ? 1 : 0;
+        for (int u = 0; u < NP; ++u) {
+            qt[u] = lane == NP * qw + u ? 1.0 : 0.0;
+            qb[u] = lane == P + NP * qw + u ? 1.0 : 0.0;
         }
-        ev[rank] = tid;
+        __syncthreads();
+#pragma unroll 3
+        for (int k = 1; k <= R; ++k) {
+            const int cur = k & 1, prv = cur ^ 1;
+            const d2 lr = L.cs[prv][NP * qw + (lane & (NP - 1))];
+            if (k > 1) {   // the columns that crossed after rotation k - 2
+                if (qw > 0) qt[0] = L.qx[prv][qw - 1][0][lane];
+                if (qw < NQ - 1) qb[NP - 1] = L.qx[prv][qw + 1][1][lane];
+            }
+            double nt[NP], nb[NP];
+#pragma unroll
+            for (int u = 0; u < NP; ++u) {
+                const double c = lane_value(lr.x, u), s = lane_value(lr.y, u);
+                nt[u] = c * qt[u] - s * qb[u];
+                nb[u] = s * qt[u] + c * qb[u];
+            }
+            L.qx[cur][qw][0][lane] = nt[NP - 1];
+            L.qx[cur][qw][1][lane] = nb[0];
+#pragma unroll
+            for (int u = NP - 1; u > 0; --u) qt[u] = nt[u - 1];
+            qt[0] = nt[0];                   // t_0 stays (other waves: replaced next round)
+            if (qw == 0) qt[1] = nb[0];
+#pragma unroll
+            for (int u = 0; u < NP - 1; ++u) qb[u] = nb[u + 1];
+            qb[NP - 1] = nt[NP - 1];         // last t -> last b (other waves: replaced next round)
+            __syncthreads();
+        }
+    }
+    // the last rotation wrote the final diagonal (positions as at the start) to dg[1]
+    if (lane < n) {
+        const double d = L.dg[1][2 * (lane % P) + lane / P];   // diagonal of row `lane`
+        int rk = 0;
+        for (int j = wave; j < n; j += NW) {
+            const double dj = L.dg[1][2 * (j % P) + j / P];
+            rk += (dj > d || (dj == d && j < lane)) ? 1 : 0;
+        }
+        atomicAdd(&L.rank[lane], rk);
+    }
+    const bool isQ = wave > NA;
+    if (isQ) {   // the move after the last rotation
+        if (qw > 0) qt[0] = L.qx[1][qw - 1][0][lane];
+        if (qw < NQ - 1) qb[NP - 1] = L.qx[1][qw + 1][1][lane];
     }
     __syncthreads();
-
-    // ---- new row o = sum_k Q[k][ev[o]] old row k, stored at row o of the
-    // pair, as (16 x 16) x (16 x CH) MFMA products from the staged rows.
-    double qa[4];
-    unsigned dbase[4];
+    if (isQ) {
+        if (lane < 2 * P)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) qa[j] = r16 < n ? Q[cur][4 * j + g][ev[r16]] : 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-        const __amdgpu_buffer_rsrc_t rs = pass == 0 ? rW : rZ;
-        double(*src)[CH + 1] = pass == 0 ? wrows : zrows;
-        const int len = pass == 0 ? it.len : it.nv;
+            for (int u = 0; u < NP; ++u) {
+                put(L.rank[NP * qw + u], lane, qt[u]);
+                put(L.rank[P + NP * qw + u], lane, qb[u]);
+            }
+    } else if (isA) {
+#pragma unroll
+        for (int u = 0; u < kBlk; ++u)
+            if (blk[u] < Lds::kTrash)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = L.rank[bi[u] + P * (e >> 1)], c = L.rank[bj[u] + P * (e & 1)];
+                    const double v = L.ex[1][e][blk[u]];
+                    put_g(r, c, v);
+                    put_g(c, r, v);
+                }
+    } else if (lane < P) {
+        const int r = L.rank[di], c = L.rank[P + di];
+        put_g(r, r, app);
+        put_g(c, c, aqq);
+        put_g(r, c, apq);
+        put_g(c, r, apq);
+    }
+    return true;
+}
+
+constexpr int kEigThreads = eig_threads(32), kEigWaves = kEigThreads / 64;
+
+// Blocks (of 32 rows) of pair l in round r of the circle schedule on nb (even) blocks.
+__device__ __forceinline__ void jac_blocks(int nb, int r, int l, int &bi, int &bj) {
+    const int p = l == 0 ? nb - 1 : (r + l) % (nb - 1), q = (r - l + nb - 1) % (nb - 1);
+    bi = min(p, q);
+    bj = max(p, q);
+}
+
+// Pair (of round r) that block x belongs to; hi: whether it is the larger block.
+__device__ __forceinline__ int jac_pair_of(int nb, int r, int x, bool &hi) {
+    const int d = x == nb - 1 ? 0 : (x - r + nb - 1) % (nb - 1);
+    const int l = d < nb / 2 ? d : nb - 1 - d;
+    int bi, bj;
+    jac_blocks(nb, r, l, bi, bj);
+    hi = x == bj;
+    return l;
+}
+
+// A pair's 64 x 64 rotation is stored as operand fragments: per 16 x 16 tile
+// (row tile, column tile) lane r + 16 g holds row r, columns 4 g .. 4 g + 3.
+__device__ __forceinline__ int frag_at(int o, int k) {
+    return ((o >> 4) * 4 + (k >> 4)) * 256 + ((o & 15) + 16 * ((k >> 2) & 3)) * 4 + (k & 3);
+}
+
+// Entry of G (blocks at and above the diagonal are kept) for a 16 x 16 x 16
+// step: this lane's row x (0..15 of a 16-row slab), columns 4 g .. 4 g + 3.
+__device__ __forceinline__ void load_g(const double *G, int64_t ld, int X, int x, int Y, int y, double (&a)[4]) {
+    if (X <= Y) {
+        const double *src = G + (int64_t)(32 * X + x) * ld + 32 * Y + y;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = src[j];
+    } else {
+        const double *src = G + (int64_t)(32 * Y + y) * ld + 32 * X + x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = src[j * ld];
+    }
+}
+
+// Launch k of a sweep (k = 0 .. number of rounds): the angles of round k run
+// beside the updates of round k - 1, in one launch.  G goes from buffer (k - 1)
+// & 1 to buffer k & 1; the rotations and the rotated 64 x 64 diagonal blocks
+// (Gd) of round k are in halves k & 1 of Qr and Gd.
+//   Workgroups 0 .. neig - 1, a pair of blocks (I, J) of round k each: the two
+//   diagonal blocks are in Gd, the block between them is rotated here from the
+//   old G, then one cyclic sweep (eig_sweep).
+//   The others, a wave per 64 x 16 piece: G[p, q] <- J_p^T G[p, q] J_q (pairs
+//   p <= q, from the old buffer to the new one; p = q: a copy of Gd) or Qt[p]
+//   <- J_p^T Qt[p].  The middle product's accumulators (row 4 r + g, column
+//   lane & 15) are the B operand of the second product as they are (its step
+//   j takes k = 4 j + g), so a wave needs neither LDS nor a barrier.
+// Neither fills the chip alone: the angles are a latency chain on one CU per
+// pair, the updates are FP64 MFMA work for the rest.
+__global__ __launch_bounds__(kEigThreads) void jac_round_kernel(const JacItem *__restrict__ items,
+                                                                const JacTask *__restrict__ eig, int neig,
+                                                                const JacTask *__restrict__ upd, int nupd, int k,
+                                                                const int32_t *__restrict__ active) {
+    __shared__ EigLds<32> L;
+    __shared__ double T[64][34];     // old G between the pairs of I and J, times J's rotation
+    __shared__ double B[32][33];     // the block between I and J
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cur = k & 1, prv = cur ^ 1;
+    if ((int)blockIdx.x < neig) {
+        const JacTask tk = eig[blockIdx.x];
+        const JacItem it = items[tk.item];
+        const int nb = it.np / 32, npair = nb / 2;
+        if (!active[tk.item] || k >= nb - 1) return;
+        int I, J;
+        jac_blocks(nb, k, tk.a, I, J);
+        const int n = min(max(it.nv - 32 * I, 0), 32) + min(max(it.nv - 32 * J, 0), 32);
+        const double *gi = nullptr, *gj = nullptr;   // diagonal blocks in Gd (row stride 64)
+        if (k > 0) {
+            bool hi, hj;
+            const int p = jac_pair_of(nb, k - 1, I, hi), q = jac_pair_of(nb, k - 1, J, hj);
+            const double *Qp = it.Qr + ((int64_t)prv * npair + p) * 4096 + (hi ? 2048 : 0);
+            const double *Qq = it.Qr + ((int64_t)prv * npair + q) * 4096 + (hj ? 2048 : 0);
+            gi = it.Gd + ((int64_t)prv * npair + p) * 4096 + (hi ? 32 * 65 : 0);
+            gj = it.Gd + ((int64_t)prv * npair + q) * 4096 + (hj ? 32 * 65 : 0);
+            int pb[2], qb[2];
+            jac_blocks(nb, k - 1, p, pb[0], pb[1]);
+            jac_blocks(nb, k - 1, q, qb[0], qb[1]);
+            if (w < 8) {   // T = G[p, q] Qq^T: rows 16 (w / 2), columns 16 (w % 2)
+                const int mt = w >> 1, nt = w & 1;
+                d4 acc = {0, 0, 0, 0};
+                double a[4][4], b[4][4];
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    load_g(it.G[prv], it.np, pb[mt >> 1], 16 * (mt & 1) + r16, qb[ks >> 1], 16 * (ks & 1) + 4 * g, a[ks]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) b[ks][j] = Qq[(nt * 4 + ks) * 256 + 4 * lane + j];
+                }
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc = mfma_f64(a[ks][j], b[ks][j], acc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) T[16 * mt + 4 * r + g][16 * nt + r16] = acc[r];
+            }
+            double a[4][4];
+            if (w < 4)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) a[ks][j] = Qp[((w >> 1) * 4 + ks) * 256 + 4 * lane + j];
+            __syncthreads();
+            if (w < 4) {   // B = Qp T: rows 16 (w / 2), columns 16 (w % 2)
+                d4 acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc = mfma_f64(a[ks][j], T[16 * ks + 4 * g + j][16 * (w & 1) + r16], acc);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) B[16 * (w >> 1) + 4 * r + g][16 * (w & 1) + r16] = acc[r];
+            }
+            __syncthreads();
+        }
+        auto at = [&](int r, int c) {
+            const int lo = min(r, c), hi = max(r, c);
+            if (k == 0) {
+                const int gl = lo < 32 ? 32 * I + lo : 32 * J + lo - 32, gh = hi < 32 ? 32 * I + hi : 32 * J + hi - 32;
+                return it.G[0][(int64_t)gl * it.np + gh];
+            }
+            if (hi < 32) return gi[64 * lo + hi];
+            if (lo >= 32) return gj[64 * (lo - 32) + hi - 32];
+            return B[lo][hi - 32];
+        };
+        double *Q = it.Qr + ((int64_t)cur * npair + tk.a) * 4096, *D = it.Gd + ((int64_t)cur * npair + tk.a) * 4096;
+        auto put = [&](int o, int c, double v) { Q[frag_at(o, c)] = v; };
+        auto put_g = [&](int r, int c, double v) { D[64 * r + c] = v; };
+        if (!eig_sweep<32>(L, n, it.tol, at, put, put_g))
+            for (int e = tid; e < 4096; e += kEigThreads) {
+                put(e >> 6, e & 63, (e >> 6) == (e & 63) ? 1.0 : 0.0);
+                put_g(e >> 6, e & 63, at(e >> 6, e & 63));
+            }
+        return;
+    }
+    // updates of round k - 1
+    const int t = ((int)blockIdx.x - neig) * kEigWaves + w;
+    if (k == 0 || t >= nupd) return;
+    const JacTask tk = upd[t];
+    const JacItem it = items[tk.item];
+    const int nb = it.np / 32, npair = nb / 2, p = tk.a, nt = tk.c;
+    if (!active[tk.item] || k > nb - 1) return;
+    const int64_t ld = it.np;
+    int pb[2], qb[2];
+    jac_blocks(nb, k - 1, p, pb[0], pb[1]);
+    const double *Qp = it.Qr + ((int64_t)prv * npair + p) * 4096;
+    double b[4][4];   // B operand of the second product: rows 16 ks + 4 j + g, column lane & 15
+    if (tk.b >= 0) {
+        if (k == nb - 1) return;   // the next sweep starts from a fresh G
+        const int q = tk.b;
+        jac_blocks(nb, k - 1, q, qb[0], qb[1]);
+        const int Y = qb[nt >> 1], yc = 16 * (nt & 1) + r16;
+        if (p == q) {
+            const double *D = it.Gd + ((int64_t)prv * npair + p) * 4096;
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+                if (pb[mt >> 1] <= Y)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int x = 16 * mt + 4 * r + g;
+                        it.G[cur][(int64_t)(32 * pb[mt >> 1] + (x & 31)) * ld + 32 * Y + yc] = D[64 * x + 16 * nt + r16];
+                    }
+            return;
+        }
+        const double *Qq = it.Qr + ((int64_t)prv * npair + q) * 4096 + nt * 1024;
+        d4 acc[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[mt] = d4{0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            double f[4], a[4][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = Qq[ks * 256 + 4 * lane + j];
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+                load_g(it.G[prv], ld, pb[mt >> 1], 16 * (mt & 1) + r16, qb[ks >> 1], 16 * (ks & 1) + 4 * g, a[mt]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) acc[mt] = mfma_f64(a[mt][j], f[j], acc[mt]);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[ks][j] = acc[ks][j];
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                b[ks][j] = it.Qt[(int64_t)(32 * pb[ks >> 1] + 16 * (ks & 1) + 4 * j + g) * ld + 16 * nt + r16];
+    }
+    d4 acc[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) acc[mt] = d4{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        double a[4][4];   // row r16 of tile mt, columns 16 ks + 4 j + g
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[mt][j] = Qp[(mt * 4 + ks) * 256 + (r16 + 16 * j) * 4 + g];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) acc[mt] = mfma_f64(a[mt][j], b[ks][j], acc[mt]);
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int o = 4 * r + g;
-            dbase[r] = o < n ? (unsigned)((int64_t)grow(o) * len) : kOut;
-        }
-        // W: the last chunk of the Gram pass is still staged, so go backwards;
-        // Z: chunk 0 is staged
-        const int nc = (len + CH - 1) / CH;
-        for (int i = 0; i < nc; ++i) {
-            const int ch = pass == 0 ? nc - 1 - i : i;
-            const int c0 = ch * CH;
-            if (i > 0) {
-                double v[U];
-                load_chunk(rs, len, c0, v);
-                __syncthreads();
-                store_chunk(src, v);
+            const int X = pb[mt >> 1], xr = 16 * (mt & 1) + 4 * r + g;
+            if (tk.b < 0) {
+                it.Qt[(int64_t)(32 * X + xr) * ld + 16 * nt + r16] = acc[mt][r];
+                continue;
             }
-            __syncthreads();
-            const int w = min(CH, len - c0);
-            for (int n0 = wave * 16; n0 < w; n0 += 64) {
-                const int col = n0 + r16;
-                double b[4];
+            const int Y = qb[nt >> 1], yc = 16 * (nt & 1) + r16;
+            if (X <= Y) it.G[cur][(int64_t)(32 * X + xr) * ld + 32 * Y + yc] = acc[mt][r];
+            else it.G[cur][(int64_t)(32 * Y + yc) * ld + 32 * X + xr] = acc[mt][r];
+        }
+}
+
+void launch_jac_round(const JacItem *items, const JacTask *eig, int neig, const JacTask *upd, int nupd, int k,
+                      const int32_t *active, hipStream_t s) {
+    const int grid = neig + (k > 0 ? (nupd + kEigWaves - 1) / kEigWaves : 0);
+    if (grid > 0)
+        hipLaunchKernelGGL(jac_round_kernel, dim3(grid), dim3(kEigThreads), 0, s, items, eig, neig, upd, nupd, k,
+                           active);
+}
+
+// One workgroup per 64 x 64 block (row block <= column block) of a fresh G:
+// largest |G_ij| / sqrt(G_ii G_jj) of every matrix (offmax, as the bits of a
+// non-negative double), and Qt = I.
+__global__ __launch_bounds__(256) void jac_begin_kernel(const JacItem *__restrict__ items,
+                                                        const JacTask *__restrict__ tasks,
+                                                        const int32_t *__restrict__ active,
+                                                        unsigned long long *__restrict__ offmax) {
+    __shared__ double dr[64], dc[64], red[4];
+    const JacTask tk = tasks[blockIdx.x];
+    const JacItem it = items[tk.item];
+    if (!active[tk.item]) return;
+    const int tid = threadIdx.x;
+    const int r0 = 64 * tk.a, c0 = 64 * tk.b;
+    const double *G = it.G[0];
+    double v[16];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = src[4 * j + g][col];
-                d4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < 16; ++u) v[u] = G[(int64_t)(r0 + 4 * u + (tid >> 6)) * it.np + c0 + (tid & 63)];
+    if (tid < 128) {   // 1 / norm of the block's rows and columns (0: absent or zero)
+        const int r = (tid < 64 ? r0 : c0 - 64) + tid;
+        const double d = r < it.nv ? G[(int64_t)r * it.np + r] : 0.0;
+        const double f = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
+        if (tid < 64) dr[tid] = f;
+        else dc[tid - 64] = f;
+    }
+    __syncthreads();
+    double off = 0.0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc = mfma_f64(qa[j], b[j], acc);
+    for (int u = 0; u < 16; ++u) {
+        const int i = 4 * u + (tid >> 6), j = tid & 63;
+        if (r0 + i < c0 + j) off = fmax(off, fabs(v[u]) * dr[i] * dc[j]);
+        it.Qt[(int64_t)(r0 + i) * it.np + c0 + j] = r0 + i == c0 + j ? 1.0 : 0.0;
+        if (r0 != c0) it.Qt[(int64_t)(c0 + i) * it.np + r0 + j] = 0.0;
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) off = fmax(off, __shfl_xor(off, w));
+    if ((tid & 63) == 0) red[tid >> 6] = off;
+    __syncthreads();
+    if (tid == 0) {
+        off = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+        atomicMax(&offmax[tk.item], (unsigned long long)__double_as_longlong(off));
+    }
+}
+
+void launch_jac_begin(const JacItem *items, const JacTask *tasks, int ntasks, const int32_t *active,
+                      unsigned long long *offmax, hipStream_t s) {
+    if (ntasks > 0) hipLaunchKernelGGL(jac_begin_kernel, dim3(ntasks), dim3(256), 0, s, items, tasks, active, offmax);
+}
+
+// A matrix of at most 2 P rows, whole iteration in one workgroup: Gram matrix
+// (FP64 MFMA), one cyclic sweep of it, W <- J^T W and Z <- J^T Z, until the
+// fresh Gram matrix meets the tolerance.  W and Z stay in global memory (the
+// caches); no launch, no host step between sweeps.
+template <int P>
+__global__ __launch_bounds__(eig_threads(P)) void jac_small_kernel(const JacSmall *__restrict__ items, int max_sweeps,
+                                                                   int32_t *__restrict__ sweeps) {
+    constexpr int kThreads = eig_threads(P), kWaves = kThreads / 64, kT = P / 8;   // kT: 16-row tiles
+    __shared__ EigLds<P> L;
+    __shared__ double Gs[2 * P][2 * P + 2];   // Gram matrix, then the rotation
+    const JacSmall it = items[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int e = tid; e < it.nv * it.nv; e += kThreads) it.Z[e] = (e / it.nv == e % it.nv) ? 1.0 : 0.0;
+    const int nt16 = (it.nv + 15) / 16;
+    int done = -1;
+    for (int sw = 0; sw < max_sweeps; ++sw) {
+        __syncthreads();   // rows of W (and Z) are whole
+        for (int e = tid; e < 4 * P * P; e += kThreads) Gs[e / (2 * P)][e % (2 * P)] = 0.0;
+        __syncthreads();
+        // tiles (ti <= tj) of the Gram matrix, one at a time per wave
+        for (int t = w; t < nt16 * (nt16 + 1) / 2; t += kWaves) {
+            int ti = 0, rest = t;
+            while (rest >= nt16 - ti) { rest -= nt16 - ti; ++ti; }
+            const int tj = ti + rest;
+            const int ra = 16 * ti + r16, rb = 16 * tj + r16;
+            const double *pa = it.W + (int64_t)min(ra, it.nv - 1) * it.len;
+            const double *pb = it.W + (int64_t)min(rb, it.nv - 1) * it.len;
+            d4 acc = {0, 0, 0, 0};
+            for (int k0 = 0; k0 < it.len; k0 += 16) {
+                double a[4], b[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = k0 + 4 * g + j;
+                    const bool in = k < it.len;
+                    a[j] = in && ra < it.nv ? pa[k] : 0.0;
+                    b[j] = in && rb < it.nv ? pb[k] : 0.0;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc = mfma_f64(a[j], b[j], acc);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                Gs[16 * ti + 4 * r + g][16 * tj + r16] = acc[r];
+                Gs[16 * tj + r16][16 * ti + 4 * r + g] = acc[r];
+            }
+        }
+        __syncthreads();
+        auto at = [&](int r, int c) { return Gs[min(r, c)][max(r, c)]; };
+        auto put = [&](int o, int k, double v) { Gs[o][k] = v; };
+        if (!eig_sweep<P>(L, it.nv, it.tol, at, put, [](int, int, double) {})) {
+            done = sw;
+            break;
+        }
+        __syncthreads();
+        // W <- J^T W, then Z: a wave takes 16 columns at a time
+        const int cw = (it.len + 15) / 16, cz = (it.nv + 15) / 16;
+        for (int t = w; t < cw + cz; t += kWaves) {
+            double *X = t < cw ? it.W : it.Z;
+            const int len = t < cw ? it.len : it.nv, col = 16 * (t < cw ? t : t - cw) + r16;
+            double b[kT][4];
+#pragma unroll
+            for (int ks = 0; ks < kT; ++ks)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = 16 * ks + 4 * g + j;
+                    b[ks][j] = k < it.nv && col < len ? X[(int64_t)k * len + col] : 0.0;
+                }
+            for (int ti = 0; ti < nt16; ++ti) {
+                d4 acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int ks = 0; ks < kT; ++ks)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc = mfma_f64(Gs[16 * ti + r16][16 * ks + 4 * g + j], b[ks][j], acc);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const unsigned offr = (dbase[r] != kOut && col < w) ? (dbase[r] + c0 + col) * 8u : kOut;
-                    bstore(rs, offr, acc[r]);
+                    const int o = 16 * ti + 4 * r + g;
+                    if (o < it.nv && col < len) X[(int64_t)o * len + col] = acc[r];
                 }
             }
         }
     }
+    if (tid == 0) sweeps[blockIdx.x] = done;
 }
 
-void launch_jac_round(const JacItem *items, const JacPair *pairs, int npairs, const int32_t *active,
-                      unsigned long long *offmax, hipStream_t s) {
-    if (npairs <= 0) return;
-    hipLaunchKernelGGL(jac_pair_kernel, dim3(npairs), dim3(JT), 0, s, items, pairs, active, offmax);
-}
-
-__global__ void identity_kernel(const JacItem *items) {
-    const JacItem it = items[blockIdx.y];
-    const int64_t n = (int64_t)it.nv * it.nv;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-        it.Z[e] = (e / it.nv == e % it.nv) ? 1.0 : 0.0;
-}
-
-void launch_identity(const JacItem *items, int nitems, int max_nv, hipStream_t s) {
-    if (nitems <= 0 || max_nv <= 0) return;
-    const int g = std::min(1024, (max_nv * max_nv + 255) / 256);
-    hipLaunchKernelGGL(identity_kernel, dim3(g, nitems), dim3(256), 0, s, items);
+// The narrowest instance that holds max_nv rows: for a dozen rows a sweep of
+// the 64-row one costs 30 us, that of the 16-row one 6 us.
+void launch_jac_small(const JacSmall *items, int nitems, int max_nv, int max_sweeps, int32_t *sweeps, hipStream_t s) {
+    if (nitems <= 0) return;
+    if (max_nv <= 16)
+        hipLaunchKernelGGL(jac_small_kernel<8>, dim3(nitems), dim3(eig_threads(8)), 0, s, items, max_sweeps, sweeps);
+    else if (max_nv <= 32)
+        hipLaunchKernelGGL(jac_small_kernel<16>, dim3(nitems), dim3(eig_threads(16)), 0, s, items, max_sweeps, sweeps);
+    else
+        hipLaunchKernelGGL(jac_small_kernel<32>, dim3(nitems), dim3(eig_threads(32)), 0, s, items, max_sweeps, sweeps);
 }
 
 __global__ __launch_bounds__(256) void row_norm_kernel(const RowRef *rows, double *out) {
@@ -537,8 +971,7 @@ static_assert(kQrMaxLen == 2048, "panel kernel reach");
 // Apply kernel: one workgroup of 4 waves per (panel, group of 16 target rows).
 // D = V Y^T over positions j0.. (FP64 MFMA, reflector rows masked to their
 // support with the unit entry), C = T^T D or T D, then Y -= C^T V (FP64 MFMA),
-// both through the same 512-position chunks staged in LDS as the Jacobi
-// kernel uses.
+// both through 512-position chunks staged in LDS.
 __global__ __launch_bounds__(JT) void qr_apply_kernel(const QrApply *tasks) {
     const QrApply tk = tasks[blockIdx.x];
     __shared__ double vrows[J2][CH + 1];
@@ -650,7 +1083,7 @@ __global__ void qr_extract_r_kernel(const QrItem *items) {
     const int64_t n = (int64_t)it.nv * it.nv;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
         const int i = (int)(e / it.nv), j = (int)(e % it.nv);
-        it.R[e] = j >= i ? it.A[(int64_t)j * it.len + i] : 0.0;
+        it.R[(int64_t)i * it.ldr + j] = j >= i ? it.A[(int64_t)j * it.len + i] : 0.0;
     }
 }
 
@@ -666,7 +1099,7 @@ __global__ void qr_embed_z_kernel(const QrItem *items) {
     const int64_t n = (int64_t)it.nv * it.len;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
         const int r = (int)(e / it.len), c = (int)(e % it.len);
-        it.Y[e] = c < it.nv ? it.Z[(int64_t)r * it.nv + c] : 0.0;
+        it.Y[e] = c < it.nv ? it.Z[(int64_t)r * it.ldz + c] : 0.0;
     }
 }
 

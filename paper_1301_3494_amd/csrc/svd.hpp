@@ -4,17 +4,28 @@
 
 namespace pdmrg {
 
-// One matrix: nv rows of length len (W), rotation accumulator Z (nv x nv);
-// a pair needs a rotation while its relative off-diagonal exceeds tol.
+// One matrix of a block-Jacobi sweep: two buffers of its Gram matrix G (the
+// first holds the fresh one) and the sweep's accumulated rotation Qt (np x np
+// each, np = nv padded to a multiple of 64; the padding of G is zero); per pair of 32-row blocks, for this round and the last (np / 64
+// pairs each), the 64 x 64 rotation (Qr) and the rotated diagonal block (Gd).
+// A pair needs rotations while its relative off-diagonal exceeds tol.
 struct JacItem {
+    double *G[2], *Qt, *Qr, *Gd;
+    double tol;
+    int32_t nv, np;
+};
+// eig: pair a of an item.  upd: columns 16 c of block (a, b) of G, or, b < 0,
+// columns 16 c of pair a of Qt.  begin: 64 x 64 block (a, b) of G.
+struct JacTask {
+    int32_t item, a, b, c;
+};
+// One matrix of at most kJacSmall rows, iterated in one workgroup: W (nv rows
+// of length len) and Z (nv x nv), both packed.
+constexpr int kJacSmall = 64;
+struct JacSmall {
     double *W, *Z;
     double tol;
     int32_t nv, len;
-};
-
-// One block pair (blocks of 8 rows) of one matrix in a Jacobi round.
-struct JacPair {
-    int32_t item, bi, bj, pad_;
 };
 
 struct RowRef {
@@ -59,12 +70,17 @@ struct QrApply {
 struct QrItem {
     const double *A, *Z;
     double *R, *Y;
-    int32_t nv, len;
+    int32_t nv, len, ldr, ldz;
 };
 
-void launch_jac_round(const JacItem *items, const JacPair *pairs, int npairs, const int32_t *active,
-                      unsigned long long *offmax, hipStream_t s);
-void launch_identity(const JacItem *items, int nitems, int max_nv, hipStream_t s);
+void launch_jac_begin(const JacItem *items, const JacTask *tasks, int ntasks, const int32_t *active,
+                    unsigned long long *offmax, hipStream_t s);
+// Launch k of a sweep: the angles of round k and the updates of round k - 1.
+void launch_jac_round(const JacItem *items, const JacTask *eig, int neig, const JacTask *upd, int nupd, int k,
+                      const int32_t *active, hipStream_t s);
+// Matrices of at most max_nv <= kJacSmall rows.  sweeps[i]: sweeps that item i
+// took, or -1 if max_sweeps were not enough.
+void launch_jac_small(const JacSmall *items, int nitems, int max_nv, int max_sweeps, int32_t *sweeps, hipStream_t s);
 void launch_row_norms(const RowRef *rows, int nrows, double *out, hipStream_t s);
 void launch_copies(const CopyTask *tasks, int ntasks, int64_t max_elems, hipStream_t s);
 void launch_qr_panels(const QrPanel *tasks, int ntasks, int max_span, hipStream_t s);
