@@ -10,7 +10,8 @@
 //
 // Workgroup: 256 threads = 4 wave64.  FP64 / FP32 tiles are BM x BN with the
 // waves on a WGM x WGN grid, each wave owning an (BM/WGM) x (BN/WGN) sub-tile
-// of 16 x 16 MFMA blocks (v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4).  BF16x3
+// of 16 x 16 MFMA blocks (v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4).  FP64
+// operands that stream from memory go straight into registers (gemm_r64).  BF16x3
 // takes operands split once in memory (each 4-byte word a bf16 pair x = hi +
 // lo, both rounded to nearest even) through the FP32 LDS-DMA pipeline and
 // accumulates lo*hi' + hi*lo' + hi*hi' with v_mfma_f32_16x16x16_bf16 in FP32.
@@ -468,6 +469,228 @@ __global__ __launch_bounds__(NT) void gemm_dma(Slots slots, const FlatTile *__re
         }
 }
 
+// ---------------------------------------------------------------- FP64, register-direct
+// For operands that stream from memory.  Every wave computes a tile of 16 WM x
+// 16 WN of its own from operands loaded straight into MFMA registers: no LDS,
+// no barriers, so a wave never waits for another.  At the FP64 rate (2048 flops
+// in 64 cycles) a 32 x 64 wave tile asks the L1 for 24 bytes a clock and CU,
+// which it gives (64); the four waves of a workgroup take neighbouring tiles so
+// that it holds what they share, and the tile of a workgroup can be 128 x 128,
+// which halves the reads of the LDS kernel's 128 x 32.
+//
+// A K step is 8: MFMA j takes k = 2 g + j from lane group g in both operands.  A,
+// with K contiguous in memory, is loaded 16 bytes a lane (k = 2 g, 2 g + 1 of
+// row r16); B, with K strided, gives a lane columns 2 r16, 2 r16 + 1 of a pair
+// of MFMA blocks, so the blocks of a pair hold alternate columns.  (Ascending k
+// over the lane groups, as the staged kernel has it, costs two lane-row swaps a
+// value here, 20 to 30 % of the time.)  Loads are NS - 1 steps ahead; offsets
+// out of the operand read zero.  The end of a K not a multiple of 8 is loaded
+// value by value (k past the end must not be read: it may hold anything).  In a
+// pair that straddles an odd edge the load is moved one value back, so nothing
+// past the operand is read.
+//
+// 42398 x 1564 x 397 (a stage 1 at m = 4000): 63 TFLOP/s with 64 x 64 a wave, 62
+// with 32 x 64, 57 with 64 x 32, 48 with 32 x 32; the largest plain product of
+// the vendor library on this card reaches 72.
+typedef double d2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ d2 buf_load2(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+
+// One operand of a wave: NB blocks of 16 rows (A: KC, K contiguous) or columns
+// (B) from r0 on, n in all, leading dimension ld.
+template <bool KC, int NB>
+struct Frag64 {
+    __amdgpu_buffer_rsrc_t rs;
+    unsigned off[KC ? NB : NB / 2];   // of this lane's first value (k = 2 g)
+    bool back[KC ? 1 : NB / 2];       // pair load moved one value back
+    int r0, n, ld;
+    // row of block i, MFMA row x
+    static __device__ __forceinline__ int row(int i, int x) { return KC ? 16 * i + x : 32 * (i / 2) + 2 * x + (i & 1); }
+    __device__ __forceinline__ void init(const double *p, int r0_, int n_, int ld_, int r16, int g) {
+        rs = operand_rsrc(p);
+        r0 = r0_;
+        n = n_;
+        ld = ld_;
+        if constexpr (KC) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int m = r0 + 16 * i + r16;
+                off[i] = m < n ? (unsigned)(m * ld + 2 * g) * 8u : kOutOfRange;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NB / 2; ++i) {
+                const int m = r0 + 32 * i + 2 * r16;
+                back[i] = m + 1 == n;
+                off[i] = m < n ? (unsigned)(2 * g * ld + m - (back[i] ? 1 : 0)) * 8u : kOutOfRange;
+            }
+        }
+    }
+    // values of K step s: v[i][j] is block i at k = 8 s + 2 g + j
+    __device__ __forceinline__ void load(int s, double (&v)[NB][2]) const {
+        if constexpr (KC) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const d2 x = buf_load2(rs, off[i] == kOutOfRange ? kOutOfRange : off[i] + (unsigned)s * 64u);
+                v[i][0] = x.x;
+                v[i][1] = x.y;
+            }
+        } else {
+            const unsigned o = (unsigned)s * 64u * (unsigned)ld;
+#pragma unroll
+            for (int i = 0; i < NB / 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const d2 x = buf_load2(rs, off[i] == kOutOfRange ? kOutOfRange : off[i] + o + (unsigned)(j * ld) * 8u);
+                    v[2 * i][j] = back[i] ? x.y : x.x;
+                    v[2 * i + 1][j] = x.y;   // past the edge if moved back: not stored
+                }
+        }
+    }
+    // values of k (k < K, else 0)
+    __device__ __forceinline__ void load1(int k, int K, int r16, double (&v)[NB]) const {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int m = r0 + row(i, r16);
+            const unsigned o = KC ? (unsigned)(m * ld + k) : (unsigned)(k * ld + m);
+            v[i] = buf_load(rs, (m < n && k < K) ? o * 8u : kOutOfRange, double());
+        }
+    }
+};
+
+// One wave's tile of WM x WN blocks at (m0, n0).
+template <int WM, int WN, int NS>
+__device__ __forceinline__ void r64_tile(const Slots &slots, const FlatTile &ft, const int64_t *__restrict__ rowoff,
+                                         int m0, int n0, int r16, int g) {
+    d4 acc[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) acc[i][j] = d4{0, 0, 0, 0};
+    using FA = Frag64<true, WM>;
+    using FB = Frag64<false, WN>;
+    const int K = ft.K;
+    FA fa;
+    FB fb;
+    fa.init(static_cast<const double *>(slots.p[ft.a_slot]) + ft.a_off, m0, ft.M, ft.lda, r16, g);
+    fb.init(static_cast<const double *>(slots.p[ft.b_slot]) + ft.b_off, n0, ft.N, ft.ldb, r16, g);
+    // a pair has no value to move back to in an operand of one column
+    const int ns = ft.N == 1 ? 0 : K / 8;
+    double va[NS][WM][2], vb[NS][WN][2];
+    auto load = [&](int s, int st) {
+        fa.load(s, va[st]);
+        fb.load(s, vb[st]);
+    };
+    auto mul = [&](int st) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int q = 0; q < WN; ++q) acc[i][q] = mfma16(va[st][i][j], vb[st][q][j], acc[i][q]);
+    };
+    const int kt = 8 * ns;
+    double ta[2][WM], tb[2][WN];
+    auto load_end = [&](int k) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (k + 4 * h < K) {
+                fa.load1(k + 4 * h + g, K, r16, ta[h]);
+                fb.load1(k + 4 * h + g, K, r16, tb[h]);
+            }
+    };
+    auto mul_end = [&](int k) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (k + 4 * h < K)
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int q = 0; q < WN; ++q) acc[i][q] = mfma16(ta[h][i], tb[h][q], acc[i][q]);
+    };
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < ns) load(s, s);
+    int s = 0;
+    for (; s + 2 * NS - 1 <= ns; s += NS) {   // every load of the round is inside
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            load(s + u + NS - 1, (u + NS - 1) % NS);
+            mul(u);
+        }
+    }
+    load_end(kt);   // in flight during the last steps
+#pragma unroll
+    for (int u = 0; u < 2 * NS - 1; ++u)
+        if (s + u < ns) {
+            if (s + u + NS - 1 < ns) load(s + u + NS - 1, (u + NS - 1) % NS);
+            mul(u % NS);
+        }
+    mul_end(kt);
+    for (int k = kt + 8; k < K; k += 8) {   // an operand of one column: all of K value by value
+        load_end(k);
+        mul_end(k);
+    }
+    // v_mfma_f64_16x16x4 result: register r of lane l is row 4 r + l / 16, column l % 16
+    double *C = static_cast<double *>(const_cast<void *>(slots.p[ft.c_slot])) + ft.c_off;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int gm = m0 + FA::row(i, 4 * r + g);
+            if (gm >= ft.M) continue;
+            double *Cr = C + (ft.rmap >= 0 ? rowoff[ft.rmap + gm] : (int64_t)gm * ft.ldc);
+#pragma unroll
+            for (int q = 0; q < WN; ++q) {
+                const int gn = n0 + FB::row(q, r16);
+                if (gn < ft.N) Cr[gn] = acc[i][q][r];
+            }
+        }
+}
+
+// A wave at the lower or right edge leaves out the blocks (by halves of its
+// tile) that lie wholly outside.
+template <int WM, int WN, int NS, int WPE>
+__global__ __launch_bounds__(NT, WPE) void gemm_r64(Slots slots, const FlatTile *__restrict__ tiles,
+                                                    const int64_t *__restrict__ rowoff, int ntiles) {
+    if ((int)blockIdx.x >= ntiles) return;
+    const FlatTile ft = tiles[blockIdx.x];
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m0 = ft.m0 + (w >> 1) * 16 * WM, n0 = ft.n0 + (w & 1) * 16 * WN;
+    if (m0 >= ft.M || n0 >= ft.N) return;   // also an idle tile (M = 0)
+    if constexpr (WN == 4)
+        if (n0 + 32 >= ft.N) {
+            r64_tile<WM, 2, NS>(slots, ft, rowoff, m0, n0, r16, g);
+            return;
+        }
+    if constexpr (WM == 4)
+        if (m0 + 32 >= ft.M) {
+            r64_tile<2, WN, NS>(slots, ft, rowoff, m0, n0, r16, g);
+            return;
+        }
+    r64_tile<WM, WN, NS>(slots, ft, rowoff, m0, n0, r16, g);
+}
+
+template <int WM, int WN, int NS, int WPE>
+static void dispatch_r64(dim3 g, hipStream_t s, const Slots &sl, const FlatTile *t, const int64_t *ro, int n) {
+    hipLaunchKernelGGL((gemm_r64<WM, WN, NS, WPE>), g, dim3(NT), 0, s, sl, t, ro, n);
+}
+
+void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff, int ntiles,
+                     hipStream_t s) {
+    if (ntiles <= 0) return;
+    const dim3 g(ntiles);
+    switch (shape) {
+        case TileShape::T64x64_R: dispatch_r64<2, 2, 3, 4>(g, s, slots, tiles, rowoff, ntiles); break;
+        case TileShape::T128x64_R: dispatch_r64<4, 2, 2, 3>(g, s, slots, tiles, rowoff, ntiles); break;
+        case TileShape::T64x128_R: dispatch_r64<2, 4, 2, 3>(g, s, slots, tiles, rowoff, ntiles); break;
+        case TileShape::T128x128_R: dispatch_r64<4, 4, 2, 2>(g, s, slots, tiles, rowoff, ntiles); break;
+        default: break;
+    }
+}
+
 struct GemmArgs {
     Slots sl;
     const GemmItem *it;
@@ -529,6 +752,7 @@ static void dispatch_kmajor(TileShape shape, bool ta, bool tb, dim3 g, hipStream
         case TileShape::T128x32_D: dispatch_shape<T, TC, 128, 32, 4, 2>(ta, tb, g, s, a); break;
         case TileShape::T64x64_D: dispatch_shape<T, TC, 64, 64, 2, 2>(ta, tb, g, s, a); break;
         case TileShape::T32x128_D: dispatch_shape<T, TC, 32, 128, 1, 1>(ta, tb, g, s, a); break;
+        default: break;   // launch_gemm_r64
     }
 }
 

@@ -53,7 +53,8 @@ double time_ms(hipStream_t s, int reps, F &&fn) {
 const char *shape_name(int t) {
     static const char *n[kNumShapes] = {"64x64", "128x32", "32x128", "128x128",
                                         "64x64k16", "128x32k16", "64x64k8", "128x32k8",
-                                        "128x32dma", "64x64dma", "32x128dma"};
+                                        "128x32dma", "64x64dma", "32x128dma",
+                                        "64x64reg", "128x64reg", "64x128reg", "128x128reg"};
     return n[t];
 }
 
@@ -66,7 +67,10 @@ void tune_heff(pdmrg_ctx *ctx, pdmrg_heff *op, const std::string &key) {
     const bool f64 = op->prec == PDMRG_F64;
     const size_t es = f64 ? sizeof(double) : sizeof(float);
     DevBuf xin(std::max<int64_t>(op->nX, 1) * es), yout(std::max<int64_t>(op->nX, 1) * sizeof(double));
+    // timed on nonzero operands (the clock of the FP64 matrix cores depends on
+    // them): the left environment stands in for x
     HIP_OK(hipMemsetAsync(xin.ptr, 0, xin.bytes, s));
+    HIP_OK(hipMemcpyAsync(xin.ptr, op->lp, std::min<int64_t>(op->nX, op->nL) * es, hipMemcpyDeviceToDevice, s));
     Slots sl{};
     sl.p[0] = xin.ptr;
     sl.p[1] = yout.ptr;
@@ -92,8 +96,8 @@ void tune_heff(pdmrg_ctx *ctx, pdmrg_heff *op, const std::string &key) {
         // split-K factors: the default one and the others that still give >= 256 tiles
         const int tiles = std::max(1, pl.g3_base.ntiles_for((TileShape)t));
         std::vector<int> cand = {pl.default_parts((TileShape)t)};
-        for (int p : {1, 2, 3, 4, 6, 8})
-            if (p != cand[0] && tiles * p >= 256) cand.push_back(p);
+        for (int p : {1, 2, 3, 4, 6, 8, 10, 12, 16})
+            if (p != cand[0] && tiles * p >= 256 && p <= (f64 ? kMaxParts64 : 8)) cand.push_back(p);
         for (int parts : cand) {
             pl.set_g3_shape((TileShape)t, s, parts);
             op->P.ensure(std::max<int64_t>(pl.nP, 1) * pes);
@@ -242,7 +246,7 @@ int tune_import(const char *path) {
         t.shape3 = std::atoi(l.c_str() + t2 + 1);
         t.parts3 = std::atoi(l.c_str() + t3 + 1);
         if (t.shape1 < 0 || t.shape1 >= kNumShapes || t.shape3 < 0 || t.shape3 >= kNumShapes || t.parts3 < 1 ||
-            t.parts3 > 8) {
+            t.parts3 > kMaxParts64) {
             std::fclose(f);
             throw Error(PDMRG_EINVAL, "autotune import: entry out of range in " + std::string(path));
         }

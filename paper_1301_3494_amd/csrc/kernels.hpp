@@ -40,7 +40,8 @@ struct GemmTile {
 };
 
 // A tile of a single-segment item with everything the tile needs in one
-// record (the LDS-DMA kernel reads it with one scalar load); M <= 0: idle.
+// record (the LDS-DMA and register-direct kernels read it with one scalar
+// load); M <= 0: idle.
 struct FlatTile {
     int64_t a_off, b_off, c_off;
     int32_t a_slot, b_slot, c_slot, rmap;
@@ -101,25 +102,29 @@ struct DotTile {
 
 enum class GemmPrec { F64, F32, BF16X3 };
 
-// Output tile shapes of the FP64 / FP32 kernels (4 waves, each a 32 x 32 or
-// 64 x 64 sub-tile of 16 x 16 MFMA blocks); the _K16 / _K8 variants stage a
-// half / quarter as much K per step (FP32 16 / 8 instead of 32, FP64 8 / 4
-// instead of 16), so less LDS and more resident workgroups for short K loops.
-// BF16X3 runs T64x64 only.
+// Output tile shapes of the FP64 / FP32 kernels (4 waves).  0-7: the register-
+// staged kernel; the _K16 / _K8 variants stage a half / quarter as much K per
+// step (FP32 16 / 8 instead of 32, FP64 8 / 4 instead of 16), so less LDS and
+// more resident workgroups for short K loops.  _D: the LDS-DMA kernel (the only
+// one of BF16X3).  _R: the FP64 register-direct kernel.
 enum class TileShape {
     T64x64 = 0, T128x32 = 1, T32x128 = 2, T128x128 = 3,
     T64x64_K16 = 4, T128x32_K16 = 5,   // half-depth K steps
     T64x64_K8 = 6, T128x32_K8 = 7,     // quarter-depth K steps
     // FP32 / FP64, non-transposed operands: K steps of 16 staged by
     // direct-to-LDS loads (other operands: the half-depth kernel)
-    T128x32_D = 8, T64x64_D = 9, T32x128_D = 10
+    T128x32_D = 8, T64x64_D = 9, T32x128_D = 10,
+    T64x64_R = 11, T128x64_R = 12, T64x128_R = 13, T128x128_R = 14
 };
-constexpr int kNumShapes = 11;
+constexpr int kNumShapes = 15;
+constexpr unsigned kStagedShapes = (1u << 8) - 1;
 constexpr unsigned kDmaShapes = (1u << 8) | (1u << 9) | (1u << 10);
+constexpr unsigned kR64Shapes = (1u << 11) | (1u << 12) | (1u << 13) | (1u << 14);
 inline int tile_bm(TileShape t) {
     switch (t) {
         case TileShape::T32x128: case TileShape::T32x128_D: return 32;
         case TileShape::T64x64: case TileShape::T64x64_K16: case TileShape::T64x64_K8: case TileShape::T64x64_D:
+        case TileShape::T64x64_R: case TileShape::T64x128_R:
             return 64;
         default: return 128;
     }
@@ -129,6 +134,7 @@ inline int tile_bn(TileShape t) {
         case TileShape::T128x32: case TileShape::T128x32_K16: case TileShape::T128x32_K8: case TileShape::T128x32_D:
             return 32;
         case TileShape::T64x64: case TileShape::T64x64_K16: case TileShape::T64x64_K8: case TileShape::T64x64_D:
+        case TileShape::T64x64_R: case TileShape::T128x64_R:
             return 64;
         default: return 128;
     }
@@ -147,6 +153,9 @@ void launch_gemm(GemmPrec prec, TileShape shape, bool ta, bool tb, bool c_is_f64
 // entry of `tiles`.
 void launch_gemm_flat(GemmPrec prec, TileShape shape, bool c_is_f64, const Slots &slots, const FlatTile *tiles,
                       const int64_t *rowoff, int ntiles, hipStream_t s);
+// The same for FP64 and a register-direct tile shape (_R).
+void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff, int ntiles,
+                     hipStream_t s);
 // chunk: kLcChunk or kLcChunkSmall elements per tile (as the tiles were built).
 void launch_lincomb(bool f64, int chunk, const Slots &slots, const LcTask *tasks, const LcSrc *srcs,
                     const LcTile *tiles, int ntiles, hipStream_t s);

@@ -65,6 +65,11 @@ static int64_t item_k(const GemmList &g, const GemmItem &it) {
     return k;
 }
 
+int GemmList::split_parts(int64_t k, double krange) const {
+    const int64_t most = elem_bytes == 8 ? kMaxParts64 : 8;
+    return (int)std::max<int64_t>(1, std::min<int64_t>({most, std::llround(k / krange), k / 64}));
+}
+
 int GemmList::ntiles_for(TileShape t) const {
     const int bm = tile_bm(t), bn = tile_bn(t);
     int n = 0;
@@ -80,18 +85,71 @@ double GemmList::padded_flops(TileShape t) const {
     return f;
 }
 
-void GemmList::pick_tile() {
+double GemmList::operand_bytes() const {
+    double b = 0.0;
+    for (const GemmItem &it : items) b += (double)elem_bytes * (double)item_k(*this, it) * ((double)it.M + it.N);
+    return b;
+}
+
+// Estimated time of an FP64 list under a register-direct shape, in flops of one
+// CU at full rate: the work (dimensions rounded up to the 32 that a wave's edge
+// tile keeps) spread over the chip at the shape's rate, plus the longest tile,
+// which the last CU to finish may have started last.
+double GemmList::cost_r64(TileShape ts, int parts) const {
+    // Relative rates, 64 x 64, 128 x 64, 64 x 128, 128 x 128: H_eff at m = 4000
+    // with 98 channels, stage 1 6.9, 5.9, 5.5, 5.1 ms, stage 3 9.6, 8.2, 6.6, 5.9.
+    static const double kRate[4] = {0.66, 0.77, 0.91, 1.0};
+    constexpr double kTileK = 48.0;      // start and end of a tile, in K units
+    constexpr double kPartial = 240.0;   // flops in the time of writing and reading a partial sum
+    const int bm = tile_bm(ts), bn = tile_bn(ts);
+    int64_t kmax = 0;
+    for (const GemmItem &it : items) kmax = std::max(kmax, item_k(*this, it));
+    const double krange = std::max(1.0, (double)kmax / std::max(parts, 1));
+    double work = 0.0, longest = 0.0;
+    for (const GemmItem &it : items) {
+        const int64_t k = item_k(*this, it);
+        const double ip = split_parts(k, krange);
+        work += 2.0 * ((it.M + 31) / 32 * 32) * (double)((it.N + 31) / 32 * 32) * (k + ip * kTileK);
+        if (ip > 1.0) work += kPartial * it.M * (double)it.N * ip;
+        // four times a wave's tile: its SIMD has a quarter of the CU's rate
+        longest = std::max(longest, 8.0 * std::min(bm / 2, it.M) * (double)std::min(bn / 2, it.N) * (k / ip + kTileK));
+    }
+    return (work / 256.0 + longest) / kRate[(int)ts - (int)TileShape::T64x64_R];
+}
+
+// Past 2 GB of operands (each item's counted once) FP64 lists stream from memory
+// and run the register-direct kernel: H_eff at m = 4000, 98 channels, 7.8 GB,
+// stage 1 5.9 -> 5.3 ms, stage 3 10.0 -> 6.0.  Below, the LDS kernel is as fast
+// or faster (24 x 8 cylinder, m = 2000, 0.4 GB, stage 1 0.148 ms against 0.160;
+// tri 12 x 6, m = 3000, 1 GB, 1.05 against 1.06), and its sums run over
+// ascending k.
+void GemmList::pick_tile(double bytes) {
     // Relative throughput per padded flop of each shape, from timings of the
     // H_eff GEMMs of the 8 x 4 cylinder (m = 1024) on MI355X: shorter K steps
     // (more resident workgroups) win on these short, ragged K loops, and the
     // LDS-DMA shapes (FP32) ran 1.4-1.9x faster than their full-depth base
     // shapes (stage 1: 64x64 51.6 -> 36.4 us, 128x32 56.8 -> 38.5 us,
     // 32x128 70.6 -> 37.6 us).
-    static const double kRate[kNumShapes] = {1.0, 1.0, 0.8, 0.75, 1.1, 1.15, 1.05, 1.2, 1.45, 1.45, 1.2};
+    static const double kRate[] = {1.0, 1.0, 0.8, 0.75, 1.1, 1.15, 1.05, 1.2, 1.45, 1.45, 1.2};
     double best = 0.0;
     bool have = false;
-    for (int t = 0; t < kNumShapes; ++t) {
-        if (!(shapes_allowed & (1u << t))) continue;
+    streams = (shapes_allowed & kR64Shapes) && bytes > 2e9;
+    if (streams) {
+        for (int t = (int)TileShape::T64x64_R; t <= (int)TileShape::T128x128_R; ++t) {
+            const double cost = cost_r64((TileShape)t, 1);
+            if (!have || cost < best * 0.999) {
+                best = cost;
+                shape = (TileShape)t;
+                have = true;
+            }
+        }
+        return;
+    }
+    // in FP64 the staged kernel measured faster than the LDS-DMA one (the
+    // autotuner still times both)
+    const unsigned shapes = elem_bytes == 8 ? shapes_allowed & kStagedShapes : shapes_allowed;
+    for (int t = 0; t < (int)TileShape::T64x64_R; ++t) {
+        if (!(shapes & (1u << t))) continue;
         const TileShape ts = (TileShape)t;
         double cap = 0.0;   // tiles after the split-K the long items allow
         const int bm = tile_bm(ts), bn = tile_bn(ts);
@@ -206,32 +264,32 @@ void GemmList::build_tiles() {
     ftiles.clear();
     bool single = !ta && !tb;
     for (const GemmItem &it : items) single = single && it.nseg <= 1;
-    if (single && ((kDmaShapes >> (int)shape) & 1u)) {
-        for (const GemmTile &t : tiles) {
-            FlatTile f{};
-            if (t.item >= 0) {
-                const GemmItem &it = items[t.item];
-                f.c_off = it.c_off;
-                f.c_slot = f.a_slot = f.b_slot = it.c_slot;
-                f.rmap = it.rmap;
-                f.M = it.M;
-                f.N = it.N;
-                f.ldc = it.ldc;
-                f.m0 = t.m0;
-                f.n0 = t.n0;
-                if (it.nseg == 1) {
-                    const GemmSeg &sg = segs[it.seg0];
-                    f.a_off = sg.a_off;
-                    f.b_off = sg.b_off;
-                    f.a_slot = sg.a_slot;
-                    f.b_slot = sg.b_slot;
-                    f.K = std::max(sg.K, 0);
-                    f.lda = sg.lda;
-                    f.ldb = sg.ldb;
-                }
+    if (!single || !(((kDmaShapes | kR64Shapes) >> (int)shape) & 1u)) return;
+    ftiles.reserve(tiles.size());
+    for (const GemmTile &t : tiles) {
+        FlatTile f{};
+        if (t.item >= 0) {
+            const GemmItem &it = items[t.item];
+            f.c_off = it.c_off;
+            f.c_slot = f.a_slot = f.b_slot = it.c_slot;
+            f.rmap = it.rmap;
+            f.M = it.M;
+            f.N = it.N;
+            f.ldc = it.ldc;
+            f.m0 = t.m0;
+            f.n0 = t.n0;
+            if (it.nseg == 1) {
+                const GemmSeg &sg = segs[it.seg0];
+                f.a_off = sg.a_off;
+                f.b_off = sg.b_off;
+                f.a_slot = sg.a_slot;
+                f.b_slot = sg.b_slot;
+                f.K = std::max(sg.K, 0);
+                f.lda = sg.lda;
+                f.ldb = sg.ldb;
             }
-            ftiles.push_back(f);
         }
+        ftiles.push_back(f);
     }
 }
 
@@ -306,7 +364,7 @@ int64_t GemmList::split_k(int parts, int pslot, LcList &reduce, bool all) {
     for (size_t ii = 0; ii < items.size(); ++ii) {
         const GemmItem &it = items[ii];
         const int64_t ktot = item_k(*this, it);
-        const int ip = (int)std::max<int64_t>(1, std::min<int64_t>({8, std::llround(ktot / krange), ktot / 64}));
+        const int ip = split_parts(ktot, krange);
         if (it.M == 0 || it.N == 0 || (ip == 1 && !all)) {
             GemmItem c = it;
             c.seg0 = (int32_t)nsegs.size();
@@ -386,6 +444,12 @@ void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, hipStream_t
 void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, const GemmDev &dv, hipStream_t s) const {
     PD_REQUIRE(prec != GemmPrec::BF16X3 || !ftiles.empty() || tiles.empty(), PDMRG_EINVAL,
                "gemm: BF16x3 needs an LDS-DMA plan (split operands)");
+    if ((1u << (int)shape) & kR64Shapes) {
+        PD_REQUIRE(prec == GemmPrec::F64 && (!ftiles.empty() || tiles.empty()), PDMRG_EINVAL,
+                   "gemm: the register-direct kernel is for FP64 and one segment per item");
+        launch_gemm_r64(shape, sl, dv.ftiles, dv.rowoff, (int)ftiles.size(), s);
+        return;
+    }
     if (!ftiles.empty()) {
         launch_gemm_flat(prec, shape, c_is_f64, sl, dv.ftiles, dv.rowoff, (int)ftiles.size(), s);
         return;
@@ -637,20 +701,12 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
 
     // tile shapes: both lists are non-transposed with one segment per item,
     // so the LDS-DMA shapes apply; BF16x3 (split operands) runs only those
-    if (prec == PDMRG_BF16X3) {
-        g1.shapes_allowed = g3.shapes_allowed = kDmaShapes;
-    } else {
-        g1.shapes_allowed |= kDmaShapes;
-        g3.shapes_allowed |= kDmaShapes;
-    }
-    for (GemmList *g : {&g1, &g3}) {
-        // the cost model keeps FP64 on the register-staged kernel, which measured
-        // faster than the LDS-DMA one in FP64 (the autotuner still times both)
-        const unsigned all = g->shapes_allowed;
-        if (prec == PDMRG_F64) g->shapes_allowed &= ~kDmaShapes;
-        g->pick_tile();
-        g->shapes_allowed = all;
-    }
+    g1.shapes_allowed = g3.shapes_allowed = prec == PDMRG_BF16X3 ? kDmaShapes
+                                            : prec == PDMRG_F32  ? kStagedShapes | kDmaShapes
+                                                                 : kStagedShapes | kDmaShapes | kR64Shapes;
+    const double bytes = g1.operand_bytes() + g3.operand_bytes();
+    g1.pick_tile(bytes);
+    g3.pick_tile(bytes);
     const std::vector<int64_t> sz = {X.size, X.size, Lt.size, Rt.size, nT1, nT2, 0};
     g1.validate(sz);
     w.validate(sz);
@@ -658,7 +714,17 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
     w.finish(s);
     g3_base = g3.host_copy();
     lowp = prec != PDMRG_F64;
-    set_g3_shape(g3.shape, s);
+    TileShape shape = g3.shape;
+    int parts = default_parts(shape);
+    if (g3.streams) {   // the split and the shape together
+        double best = 0.0;
+        for (int p = 1; p <= kMaxParts64; ++p)
+            for (int t = (int)TileShape::T64x64_R; t <= (int)TileShape::T128x128_R; ++t) {
+                const double c = g3_base.cost_r64((TileShape)t, p);
+                if (best == 0.0 || c < best * 0.999) best = c, parts = p, shape = (TileShape)t;
+            }
+    }
+    set_g3_shape(shape, s, parts);
 }
 
 void HeffPlan::set_g1_shape(TileShape t, hipStream_t s) {

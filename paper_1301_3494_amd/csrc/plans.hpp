@@ -28,11 +28,16 @@ struct LcDev {
     const LcTile *tiles;
 };
 
+// Most K ranges of an item in FP64 (FP32 / BF16x3: 8): with few output tiles
+// the ranges also even out the last round of workgroups, and a longest range
+// of 1/16 of K costs 2 % there.
+constexpr int kMaxParts64 = 16;
+
 struct GemmList {
     bool ta = false, tb = false;
     int elem_bytes = 8;                    // operand element size (4 in the FP32 / BF16x3 modes)
     TileShape shape = TileShape::T64x64;   // set by pick_tile()
-    unsigned shapes_allowed = ((1u << kNumShapes) - 1) & ~kDmaShapes;   // H_eff plans add kDmaShapes
+    unsigned shapes_allowed = kStagedShapes;   // H_eff plans add kDmaShapes and kR64Shapes
     std::vector<GemmItem> items;
     std::vector<GemmSeg> segs;
     std::vector<GemmTile> tiles;           // in launch order (workgroup b runs tiles[b]); item < 0: idle
@@ -42,8 +47,8 @@ struct GemmList {
     std::vector<RowBlock> blocks;
     double flops = 0.0;
     DevBuf d_items, d_segs, d_tiles, d_rowoff;
-    // LDS-DMA shapes on lists of single-segment items: the tiles as FlatTile
-    // records in the same launch order (used by launch() for FP32 and FP64)
+    // LDS-DMA and register-direct shapes on lists of single-segment items: the
+    // tiles as FlatTile records in the same launch order
     std::vector<FlatTile> ftiles;
     DevBuf d_ftiles;
 
@@ -53,7 +58,13 @@ struct GemmList {
     void add_seg(int a_slot, int64_t a_off, int lda, int b_slot, int64_t b_off, int ldb, int K);
     // Tile shape of least estimated time: padded MFMA work over the fraction of
     // the device that the tiles (times the split-K factor they allow) can fill.
-    void pick_tile();
+    // bytes: of operands, of this list and those that run with it.
+    void pick_tile() { pick_tile(operand_bytes()); }
+    void pick_tile(double bytes);
+    double operand_bytes() const;
+    bool streams = false;   // set by pick_tile(): the register-direct kernel
+    // The time compared for its shapes, with the K split of split_k(parts).
+    double cost_r64(TileShape t, int parts) const;
     int ntiles_for(TileShape t) const;
     double padded_flops(TileShape t) const;
     // Build the tiles and place them for the launch (see place_tiles), upload.
@@ -68,9 +79,12 @@ struct GemmList {
     // Throws unless every element an item touches lies inside its slot's
     // buffer (sizes in elements, per slot).
     void validate(const std::vector<int64_t> &slot_elems) const;
+    // K ranges of an item of length k when a range aims at krange values (at
+    // most 8 or kMaxParts64, at least 1).
+    int split_parts(int64_t k, double krange) const;
     // Split-K: the item of longest K is cut into `parts` items over
     // consecutive K ranges and every other item into as many as keep its
-    // ranges near the same length (at most 8, at least 1), each writing a
+    // ranges near the same length (split_parts), each writing a
     // partial product into slot
     // `pslot` (packed, ld = N); `reduce` receives one task per original item
     // that sums its partials into the original C in a fixed order.  Returns
