@@ -364,12 +364,9 @@ int env_update(pdmrg_ctx *ctx, int dir, const pdmrg_bond *bl, const pdmrg_bond *
     PD_REQUIRE(dir == 1 || dir == -1, PDMRG_EINVAL, "env_update: dir must be +1 or -1");
     PD_REQUIRE(prec == PDMRG_F64, PDMRG_EINVAL, "env_update: only FP64 environments are supported");
     EnvPlan plan;
-    plan.build(dir, Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W), ctx->stream);
-    const size_t need = (size_t)(std::max<int64_t>(plan.nU1, 1) + std::max<int64_t>(plan.nU2, 1)) * sizeof(double);
-    ctx->ws_env.ensure(need);
-    double *U1 = ctx->ws_env.as<double>();
-    double *U2 = U1 + std::max<int64_t>(plan.nU1, 1);
-    plan.run(GemmPrec::F64, env_in_dev, site_dev, env_out_dev, U1, U2, ctx->stream);
+    const MpoSite site = MpoSite::from(W);
+    plan.begin(dir, Bond::from(bl), Bond::from(br), Phys::from(phys), site);
+    plan.run(site, env_in_dev, site_dev, env_out_dev, ctx->ws_env, ctx->stream);
     HIP_OK(hipStreamSynchronize(ctx->stream));
     API_END
 }
@@ -382,8 +379,8 @@ int grad_site(pdmrg_ctx *ctx, const pdmrg_bond *bl, const pdmrg_bond *br, const 
     API_BEGIN
     PD_REQUIRE(ctx && L_dev && psi_dev && R_dev && G_dev, PDMRG_EINVAL, "grad_site: null argument");
     GradPlan plan;
-    plan.build(Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W), ctx->stream);
-    grad_site_run(ctx, plan, L_dev, psi_dev, R_dev, G_dev);
+    plan.run(Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W), L_dev, psi_dev, R_dev, ctx->ws_grad,
+             ctx->ws_grad2, G_dev, ctx->stream);
     HIP_OK(hipStreamSynchronize(ctx->stream));
     API_END
 }
@@ -393,7 +390,7 @@ int env_update_info(int dir, const pdmrg_bond *bl, const pdmrg_bond *br, const p
     API_BEGIN
     PD_REQUIRE(dir == 1 || dir == -1, PDMRG_EINVAL, "env_update_info: dir must be +1 or -1");
     EnvPlan plan;
-    plan.build(dir, Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W), nullptr, false);
+    plan.build(dir, Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W));
     if (flops) *flops = plan.g1.flops + plan.w.flops + plan.g3.flops;
     if (n_out) *n_out = plan.Eout.size;
     API_END

@@ -249,6 +249,25 @@ void launch_fill(double *x, double v, int64_t n, hipStream_t s) {
     if (n > 0) hipLaunchKernelGGL(fill_kernel, grid_for(n), dim3(256), 0, s, x, v, n);
 }
 
+// One side is across the bus: everything in flight at once, one element a lane.
+template <typename T>
+__global__ __launch_bounds__(256) void list_copy_kernel(T *__restrict__ dst, const T *__restrict__ src, unsigned n) {
+    const unsigned e = blockIdx.x * 256u + threadIdx.x;
+    if (e < n) dst[e] = src[e];
+}
+template <typename T>
+static void list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+    const unsigned v = (unsigned)(n / sizeof(T));
+    if (v > 0)
+        hipLaunchKernelGGL((list_copy_kernel<T>), dim3((v + 255) / 256), dim3(256), 0, s, static_cast<T *>(dst),
+                           static_cast<const T *>(src), v);
+}
+void launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+    const size_t bits = reinterpret_cast<size_t>(dst) | reinterpret_cast<size_t>(src) | n;
+    if (bits % sizeof(uint4) == 0) list_copy<uint4>(dst, src, n, s);
+    else list_copy<uint32_t>(dst, src, n, s);
+}
+
 __global__ void row_scale_kernel(const double *x, double *y, const int64_t *base, const int32_t *rows,
                                  const int32_t *cols, const int64_t *vbase, const double *scale) {
     const int k = blockIdx.y;

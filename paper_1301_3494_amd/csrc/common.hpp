@@ -50,10 +50,21 @@ struct Bond {
     Bond() = default;
     Bond(const std::vector<int> &qs, const std::vector<int> &dims);
     static Bond from(const pdmrg_bond *b);
-    int find(int charge) const;   // sector index or -1
+    // sector index or -1
+    int find(int charge) const {
+        if (!at_.empty()) {
+            const int64_t x = (int64_t)charge - q[0];
+            return x < 0 || x >= (int64_t)at_.size() ? -1 : at_[x];
+        }
+        auto it = std::lower_bound(q.begin(), q.end(), charge);
+        return it == q.end() || *it != charge ? -1 : (int)(it - q.begin());
+    }
     int dim_of(int charge) const { int k = find(charge); return k < 0 ? 0 : dim[k]; }
     int nsec() const { return (int)q.size(); }
     bool operator==(const Bond &o) const { return q == o.q && dim == o.dim; }
+
+private:
+    std::vector<int32_t> at_;   // sector of charge q[0] + x, where the charges lie close together
 };
 
 struct Phys {
@@ -133,6 +144,77 @@ void upload(DevBuf &buf, const std::vector<T> &v, hipStream_t s) {
     if (!v.empty()) HIP_OK(hipMemcpyAsync(buf.ptr, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
 }
 
+// Work lists of one plan on their way to the device: packed into one pinned
+// block, brought over by one kernel that reads it across the bus, into one
+// buffer.  The host arrays are free once flush() returns; the copy is ordered
+// by `s` alone, so what it brings is for kernels on that stream (data that
+// other streams read goes through upload()).
+struct ListBuf;
+class ListStage {
+public:
+    // *dst points at v's copy after flush()
+    template <class T>
+    void add(const T *&dst, const std::vector<T> &v) {
+        parts_.push_back(Part{reinterpret_cast<const void **>(&dst), v.data(), v.size() * sizeof(T), total_});
+        total_ += (v.size() * sizeof(T) + 255) & ~size_t(255);
+    }
+    void flush(DevBuf &buf, hipStream_t s);
+    void flush(ListBuf &buf, hipStream_t s);
+
+private:
+    void copy(char *dst, hipStream_t s);
+    struct Part {
+        const void **dst;
+        const void *src;
+        size_t bytes, at;
+    };
+    std::vector<Part> parts_;
+    size_t total_ = 0;
+};
+// Device memory of lists that live within one call and are read on one stream:
+// on release it is free at once for the next list on that stream (which is
+// written behind the kernels that read this one).
+struct ListBuf {
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    int dev = 0;
+    hipStream_t s = nullptr;
+    DevBuf large;   // lists past the pool's largest block
+    ListBuf() = default;
+    ~ListBuf() { release(); }
+    ListBuf(const ListBuf &) = delete;
+    ListBuf &operator=(const ListBuf &) = delete;
+    void ensure(size_t n, hipStream_t stream);
+    void release();
+    template <class T> T *as() const { return static_cast<T *>(ptr); }
+};
+template <class B, class T>
+void upload_list(B &buf, const std::vector<T> &v, hipStream_t s) {
+    const T *p;
+    ListStage st;
+    st.add(p, v);
+    st.flush(buf, s);
+}
+
+// Small results to the host: device arrays (4-byte aligned) written into a
+// pinned block by one kernel each, behind everything launched on `s`; returns
+// once they have arrived (waits for `s`).
+struct HostCopy {
+    void *dst;
+    const void *src;
+    size_t bytes;   // a multiple of 4
+};
+void read_back(const std::vector<HostCopy> &parts, hipStream_t s);
+
+// Held by every context: the pinned blocks behind ListStage and read_back and
+// the device blocks behind ListBuf are freed with the last one.
+struct StageHold {
+    StageHold();
+    ~StageHold();
+    StageHold(const StageHold &) = delete;
+    StageHold &operator=(const StageHold &) = delete;
+};
+
 // Host worker threads for independent jobs of one context (the regions of a
 // half-sweep, the merges of one merge phase, groups of correlators).  Threads
 // are created on first use and live as long as the context, so a sweep does
@@ -168,6 +250,7 @@ private:
 constexpr int kTimingEvents = 5;
 
 struct pdmrg_ctx {
+    pdmrg::StageHold stage_hold;
     int device = 0;
     hipStream_t stream = nullptr;
     // H_eff stage timing: 4 events per heff_apply (before stage 1, 2, 3, after),
@@ -179,7 +262,7 @@ struct pdmrg_ctx {
     pdmrg::DevBuf ws_env;           // environment-update intermediates
     pdmrg::DevBuf ws_merge;         // merge: V-scaled right tensor
     pdmrg::DevBuf ws_svd;           // SVD work space
-    pdmrg::DevBuf ws_grad;          // gradient intermediates
+    pdmrg::DevBuf ws_grad, ws_grad2;   // gradient intermediates
     // Tile-shape autotuning of H_eff plans: 0 cost model, 1 measured and
     // cached per block signature, 2 = 1 plus a log line per tuned plan.
     int autotune = 0;

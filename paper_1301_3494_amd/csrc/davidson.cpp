@@ -136,8 +136,7 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
     bool converged = false;
     while (true) {
         ritz_step(k);
-        HIP_OK(hipMemcpyAsync(host, w.scal, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_OK(hipStreamSynchronize(s));
+        read_back({{host, w.scal, 3 * sizeof(double)}}, s);
         theta = host[0];
         rn = std::sqrt(std::max(0.0, host[1]));
         PD_REQUIRE(std::isfinite(theta) && std::isfinite(rn), PDMRG_ENUMERIC, "davidson: NaN/Inf in H_eff");
@@ -164,8 +163,7 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
                 k = 1;
                 extend_G(0);
                 ritz_step(1);   // x = V0 (c = 1), hx = HV0
-                HIP_OK(hipMemcpyAsync(host, w.scal, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
-                HIP_OK(hipStreamSynchronize(s));
+                read_back({{host, w.scal, 3 * sizeof(double)}}, s);
                 theta = host[0];
                 rn = std::sqrt(std::max(0.0, host[1]));
                 HIP_OK(hipMemcpyAsync(w.X, w.V, n * sizeof(double), hipMemcpyDeviceToDevice, s));

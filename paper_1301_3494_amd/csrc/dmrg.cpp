@@ -82,7 +82,6 @@ struct Driver {
             sl.p[2] = out.ptr;
             mp.g.launch(GemmPrec::F64, true, sl, s());
         }
-        HIP_OK(hipStreamSynchronize(s()));
         return out;
     }
 
@@ -135,11 +134,9 @@ struct Driver {
         ensure_L(i);
         const auto t0 = std::chrono::steady_clock::now();
         EnvPlan ep;
-        ep.build(1, m->bonds[i], m->bonds[i + 1], m->p, W(i), s());
+        ep.begin(1, m->bonds[i], m->bonds[i + 1], m->p, W(i));
         DevBuf out(std::max<int64_t>(ep.Eout.size, 1) * sizeof(double));
-        ctx->ws_env.ensure((size_t)(std::max<int64_t>(ep.nU1, 1) + std::max<int64_t>(ep.nU2, 1)) * sizeof(double));
-        double *U1 = ctx->ws_env.as<double>();
-        ep.run(GemmPrec::F64, m->L[i].ptr, m->sites[i].ptr, out.ptr, U1, U1 + std::max<int64_t>(ep.nU1, 1), s());
+        ep.run(W(i), m->L[i].ptr, m->sites[i].ptr, out.ptr, ctx->ws_env, s());
         HIP_OK(hipStreamSynchronize(s()));
         m->L[i + 1] = std::move(out);
         t_env += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -149,11 +146,9 @@ struct Driver {
         ensure_R(i + 1);
         const auto t0 = std::chrono::steady_clock::now();
         EnvPlan ep;
-        ep.build(-1, m->bonds[i], m->bonds[i + 1], m->p, W(i), s());
+        ep.begin(-1, m->bonds[i], m->bonds[i + 1], m->p, W(i));
         DevBuf out(std::max<int64_t>(ep.Eout.size, 1) * sizeof(double));
-        ctx->ws_env.ensure((size_t)(std::max<int64_t>(ep.nU1, 1) + std::max<int64_t>(ep.nU2, 1)) * sizeof(double));
-        double *U1 = ctx->ws_env.as<double>();
-        ep.run(GemmPrec::F64, m->R[i + 1].ptr, m->sites[i].ptr, out.ptr, U1, U1 + std::max<int64_t>(ep.nU1, 1), s());
+        ep.run(W(i), m->R[i + 1].ptr, m->sites[i].ptr, out.ptr, ctx->ws_env, s());
         HIP_OK(hipStreamSynchronize(s()));
         m->R[i] = std::move(out);
         t_env += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -258,8 +253,7 @@ struct Driver {
             launch_reduce_partials(part.as<double>() + (size_t)k * kBlocks, kBlocks, 1, out.as<double>() + k, 1, s());
         }
         double h[3];
-        HIP_OK(hipMemcpyAsync(h, out.ptr, sizeof h, hipMemcpyDeviceToHost, s()));
-        HIP_OK(hipStreamSynchronize(s()));
+        read_back({{h, out.ptr, sizeof h}}, s());
         const double den = std::sqrt(h[1] * h[2]);
         return den > 0.0 ? std::max(0.0, 1.0 - std::fabs(h[0]) / den) : 1.0;
     }
@@ -534,7 +528,7 @@ struct Driver {
                 ct.push_back(CopyTask{blk, blk, V + b.off[k], V + b.off[j], b.dim[k], b.dim[j], b.dim[j], b.dim[j], 0, 0});
             }
         DevBuf d;
-        upload(d, ct, s());
+        upload_list(d, ct, s());
         int64_t mx = 0;
         for (auto &t : ct) mx = std::max<int64_t>(mx, (int64_t)t.rows * t.cols);
         launch_copies(d.as<CopyTask>(), (int)ct.size(), mx, s());
@@ -561,18 +555,15 @@ struct Driver {
                 Wi = W(i);
             }
             EnvPlan ep;
-            ep.build(1, m->bonds[i], m->bonds[i + 1], m->p, Wi, s());
+            ep.begin(1, m->bonds[i], m->bonds[i + 1], m->p, Wi);
             DevBuf out(std::max<int64_t>(ep.Eout.size, 1) * sizeof(double));
-            ctx->ws_env.ensure((size_t)(std::max<int64_t>(ep.nU1, 1) + std::max<int64_t>(ep.nU2, 1)) * sizeof(double));
-            double *U1 = ctx->ws_env.as<double>();
-            ep.run(GemmPrec::F64, E.ptr, m->sites[i].ptr, out.ptr, U1, U1 + std::max<int64_t>(ep.nU1, 1), s());
+            ep.run(Wi, E.ptr, m->sites[i].ptr, out.ptr, ctx->ws_env, s());
             if (m->split && m->hasV[i + 1]) scale_env_v(out, ep.Eout, m->bonds[i + 1], Wi.dr, m->Vd[i + 1].as<double>());
             HIP_OK(hipStreamSynchronize(s()));
             E = std::move(out);
         }
         double v = 0.0;
-        HIP_OK(hipMemcpyAsync(&v, E.ptr, sizeof(double), hipMemcpyDeviceToHost, s()));
-        HIP_OK(hipStreamSynchronize(s()));
+        read_back({{&v, E.ptr, sizeof(double)}}, s());
         return v;
     }
 
@@ -673,10 +664,10 @@ struct Driver {
         }
         t0.push_back((int32_t)tiles.size());
         DevBuf d_tasks, d_tiles, d_t0, d_g, partial, res;
-        upload(d_tasks, tasks, s());
-        upload(d_tiles, tiles, s());
-        upload(d_t0, t0, s());
-        upload(d_g, g_of, s());
+        upload_list(d_tasks, tasks, s());
+        upload_list(d_tiles, tiles, s());
+        upload_list(d_t0, t0, s());
+        upload_list(d_g, g_of, s());
         partial.ensure(tiles.size() * sizeof(double));
         res.ensure(tasks.size() * sizeof(double));
         launch_seg_dot_partials(d_tasks.as<SegDot>(), d_tiles.as<SegTile>(), (int)tiles.size(), partial.as<double>(),
@@ -684,8 +675,7 @@ struct Driver {
         launch_dot_reduce(partial.as<double>(), d_t0.as<int32_t>(), d_g.as<int32_t>(), (int)tasks.size(),
                           res.as<double>(), s());
         std::vector<double> h(tasks.size());
-        HIP_OK(hipMemcpyAsync(h.data(), res.ptr, h.size() * sizeof(double), hipMemcpyDeviceToHost, s()));
-        HIP_OK(hipStreamSynchronize(s()));
+        read_back({{h.data(), res.ptr, h.size() * sizeof(double)}}, s());
         for (size_t t = 0; t < tasks.size(); ++t) out[site_of[t]] += wt[t] * h[t];
     }
 
@@ -705,18 +695,16 @@ struct Driver {
             mx = std::max(mx, b0.dim[j]);
         }
         DevBuf d_sq;
-        upload(d_sq, sq, s());
+        upload_list(d_sq, sq, s());
         launch_set_identity(d_sq.as<SqBlock>(), (int)sq.size(), mx, s());
         HIP_OK(hipStreamSynchronize(s()));
         EnvLayout last;
         for (int j = i; j <= k; ++j) {
             const MpoSite &W = j == i ? Wi : (j < k ? Wm : Wk);
             EnvPlan ep;
-            ep.build(1, m->bonds[j], m->bonds[j + 1], m->p, W, s());
+            ep.begin(1, m->bonds[j], m->bonds[j + 1], m->p, W);
             DevBuf out(std::max<int64_t>(ep.Eout.size, 1) * sizeof(double));
-            ctx->ws_env.ensure((size_t)(std::max<int64_t>(ep.nU1, 1) + std::max<int64_t>(ep.nU2, 1)) * sizeof(double));
-            double *U1 = ctx->ws_env.as<double>();
-            ep.run(GemmPrec::F64, E.ptr, m->sites[j].ptr, out.ptr, U1, U1 + std::max<int64_t>(ep.nU1, 1), s());
+            ep.run(W, E.ptr, m->sites[j].ptr, out.ptr, ctx->ws_env, s());
             if (j < k) {
                 PD_REQUIRE(m->hasV[j + 1], PDMRG_EINVAL, "correlator: no V on an inner bond");
                 scale_env_v(out, ep.Eout, m->bonds[j + 1], W.dr, m->Vd[j + 1].as<double>());
@@ -730,12 +718,11 @@ struct Driver {
         for (int j = 0; j < bk.nsec(); ++j)
             if (last.rowo[j] >= 0) tr.push_back(SqBlock{E.as<double>() + last.base[j], bk.dim[j], 0});
         DevBuf d_tr, d_val;
-        upload(d_tr, tr, s());
+        upload_list(d_tr, tr, s());
         d_val.ensure(sizeof(double));
         launch_trace_sum(d_tr.as<SqBlock>(), (int)tr.size(), d_val.as<double>(), s());
         double v = 0.0;
-        HIP_OK(hipMemcpyAsync(&v, d_val.ptr, sizeof(double), hipMemcpyDeviceToHost, s()));
-        HIP_OK(hipStreamSynchronize(s()));
+        read_back({{&v, d_val.ptr, sizeof(double)}}, s());
         return v;
     }
 
@@ -748,11 +735,10 @@ struct Driver {
         init();
         for (int i = 0; i < m->N; ++i) {
             GradPlan gp;
-            gp.build(m->bonds[i], m->bonds[i + 1], m->p, W(i), s());
             ensure_L(i);
             ensure_R(i + 1);
-            grad_site_run(ctx, gp, m->L[i].as<double>(), m->sites[i].as<double>(), m->R[i + 1].as<double>(),
-                          G + goff[i]);
+            gp.run(m->bonds[i], m->bonds[i + 1], m->p, W(i), m->L[i].as<double>(), m->sites[i].as<double>(),
+                   m->R[i + 1].as<double>(), ctx->ws_grad, ctx->ws_grad2, G + goff[i], s());
             // G_i / <Psi|Psi>, the squared norm of the centre: a fixed-order
             // device reduction, then G scaled twice by 1/sqrt(norm^2)
             const int64_t n = site_layout(m->bonds[i], m->bonds[i + 1], m->p).size;
@@ -765,8 +751,7 @@ struct Driver {
             launch_scale_by_inv_sqrt(G + goff[i], nrm.as<double>(), G + goff[i], gn, s());
             launch_scale_by_inv_sqrt(G + goff[i], nrm.as<double>(), G + goff[i], gn, s());
             double nrm2 = 0.0;
-            HIP_OK(hipMemcpyAsync(&nrm2, nrm.ptr, sizeof(double), hipMemcpyDeviceToHost, s()));
-            HIP_OK(hipStreamSynchronize(s()));
+            read_back({{&nrm2, nrm.ptr, sizeof(double)}}, s());
             PD_REQUIRE(nrm2 > 0.0 && std::isfinite(nrm2), PDMRG_ENUMERIC, "grad_mpo: zero or non-finite state");
             if (i + 1 < m->N) gauge_move(i, PDMRG_ABSORB_RIGHT, 1 << 30, 1e-14);
             drop_L(i, false);
@@ -983,11 +968,11 @@ int grad_couplings(pdmrg_ctx *ctx, pdmrg_mps *m, const pdmrg_mpo *mpo, double *d
     t0.push_back((int32_t)tiles.size());
     PD_REQUIRE(nG < (int64_t(1) << 31), PDMRG_EINVAL, "grad_couplings: gradient too large");
     DevBuf d_dw, d_tasks, d_tiles, d_t0, d_g, partial, out;
-    upload(d_dw, dWall, s);
-    upload(d_tasks, tasks, s);
-    upload(d_tiles, tiles, s);
-    upload(d_t0, t0, s);
-    upload(d_g, g_of, s);
+    upload_list(d_dw, dWall, s);
+    upload_list(d_tasks, tasks, s);
+    upload_list(d_tiles, tiles, s);
+    upload_list(d_t0, t0, s);
+    upload_list(d_g, g_of, s);
     partial.ensure(std::max<size_t>(tiles.size(), 1) * sizeof(double));
     out.ensure((size_t)ncouplings * sizeof(double));
     Slots sl{};

@@ -154,8 +154,8 @@ void heff_build(pdmrg_ctx *ctx, pdmrg_heff *op, const Bond &bl, const Bond &br, 
     op->nR = pl.Rt.size;
     // diagonal preconditioner from the FP64 environments
     op->diag.ensure(std::max<int64_t>(op->nX, 1) * sizeof(double));
-    upload(op->diag_terms, pl.diag_terms, s);
-    upload(op->diag_groups, pl.diag_groups, s);
+    upload_list(op->diag_terms, pl.diag_terms, s);
+    upload_list(op->diag_groups, pl.diag_groups, s);
     {
         Slots sl{};
         sl.p[0] = op->diag.ptr;
@@ -256,15 +256,6 @@ int tune_import(const char *path) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto &r : rows) tune_cache()[r.first] = r.second;
     return (int)rows.size();
-}
-
-void grad_site_run(pdmrg_ctx *ctx, const GradPlan &plan, const double *L, const double *psi, const double *R,
-                   double *G) {
-    const size_t nU1 = std::max<int64_t>(plan.nU1, 1), nZ = std::max<int64_t>(plan.nZ, 1);
-    const size_t np = std::max<size_t>(plan.dtiles.size(), 1);
-    ctx->ws_grad.ensure((nU1 + nZ + np) * sizeof(double));
-    double *U1 = ctx->ws_grad.as<double>();
-    plan.run(L, psi, R, U1, U1 + nU1, U1 + nU1 + nZ, G, ctx->stream);
 }
 
 // The kernels of one product on stream s (no memset or copy nodes, so the

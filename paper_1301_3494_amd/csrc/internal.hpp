@@ -90,8 +90,6 @@ void noalloc_init(int device);
 
 int tune_export(const char *path);
 int tune_import(const char *path);
-void grad_site_run(pdmrg_ctx *ctx, const GradPlan &plan, const double *L, const double *psi, const double *R,
-                   double *G);
 void svd_truncate_run(pdmrg_ctx *ctx, const Bond &bl, const Bond &br, const Phys &p, const double *psi,
                       int max_m, double cutoff, double eps, int mode, SvdOut &out);
 // Several truncated SVDs in one batch: the sector blocks of all problems

@@ -1,6 +1,7 @@
 // Host bookkeeping of U(1) block-sparse tensors: sector tables and the block
 // layouts declared in include/pdmrg.h.
 #include "common.hpp"
+#include "kernels.hpp"
 
 #include <atomic>
 #include <mutex>
@@ -23,18 +24,17 @@ Bond::Bond(const std::vector<int> &qs, const std::vector<int> &dims) : q(qs), di
     }
     PD_REQUIRE(o < (1 << 30), PDMRG_EINVAL, "bond: dimension too large");
     total = (int)o;
+    const int64_t range = q.empty() ? 0 : (int64_t)q.back() - q[0] + 1;
+    if (range <= 8 * (int64_t)q.size() + 64) {
+        at_.assign((size_t)range, -1);
+        for (size_t k = 0; k < q.size(); ++k) at_[q[k] - q[0]] = (int32_t)k;
+    }
 }
 
 Bond Bond::from(const pdmrg_bond *b) {
     PD_REQUIRE(b != nullptr && b->nsec >= 0, PDMRG_EINVAL, "bond: null descriptor");
     PD_REQUIRE(b->nsec == 0 || (b->q && b->dim), PDMRG_EINVAL, "bond: null arrays");
     return Bond(std::vector<int>(b->q, b->q + b->nsec), std::vector<int>(b->dim, b->dim + b->nsec));
-}
-
-int Bond::find(int charge) const {
-    auto it = std::lower_bound(q.begin(), q.end(), charge);
-    if (it == q.end() || *it != charge) return -1;
-    return (int)(it - q.begin());
 }
 
 Phys Phys::from(const pdmrg_phys *p) {
@@ -279,6 +279,236 @@ void DevBuf::release() {
     }
     ptr = nullptr;
     bytes = 0;
+}
+
+// ---------------------------------------------------------------- work lists to the device, small results back
+// A plan's lists come to some 0.1 to 1 MB in 8 to 10 arrays.  Copied one by one
+// from pageable memory they cost 20 to 50 us each (the runtime stages them and
+// waits); packed and read by a kernel they cost one memcpy, a launch and the bus.
+// (24 x 8 cylinder, m = 2000, one environment update: 0.23 ms of copies; with the
+// lists of later products built while the first one runs, the call went from
+// 0.89 ms to 0.30, of which the kernels are 0.26.)  Results of a few words or kilobytes that the host waits for come back the
+// same way.
+//
+// Pinned blocks are reused once the event behind their last copy has passed.
+// All of them together are bounded; a list that finds no block, or is larger
+// than one, goes through the runtime's pageable copy.  The device side of lists
+// that live within one call (ListBuf) is kept by stream, also bounded: a block
+// from the allocator above would be a new one each time (75 us of hipMalloc for
+// 0.5 MB), for it has to wait for the whole device before it is used again.
+namespace {
+constexpr size_t kPinnedBytes = size_t(64) << 20, kPinnedBlock = size_t(8) << 20;
+constexpr size_t kListBytes = size_t(256) << 20, kListBlock = size_t(8) << 20;
+struct Pinned {
+    void *ptr = nullptr;
+    hipEvent_t done = nullptr;
+    int dev = 0;
+    size_t bytes = 0;
+};
+std::mutex g_pin_mu;
+struct ListBlock {
+    void *ptr;
+    size_t bytes;
+    int dev;
+    hipStream_t s;
+};
+struct PinPool {
+    std::vector<Pinned> blocks;     // not in use by a thread, oldest copy first
+    size_t bytes = 0;               // of all blocks
+    std::vector<ListBlock> lists;   // device blocks, free for lists on their stream
+    size_t list_bytes = 0;          // of all of them
+    int holders = 0;
+};
+PinPool &pins() {
+    static PinPool *p = new PinPool();
+    return *p;
+}
+
+// A block of at least n bytes whose last copy has ended, or one without ptr.
+Pinned pin_take(int dev, size_t n) {
+    size_t cls = size_t(64) << 10;
+    while (cls < n) cls <<= 2;
+    cls = std::min(cls, kPinnedBlock);
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        PinPool &p = pins();
+        int busy = 0;
+        for (size_t k = 0; k < p.blocks.size() && busy < 4; ++k) {
+            if (p.blocks[k].dev != dev || p.blocks[k].bytes != cls) continue;
+            if (hipEventQuery(p.blocks[k].done) == hipSuccess) {
+                Pinned b = p.blocks[k];
+                p.blocks.erase(p.blocks.begin() + (ptrdiff_t)k);
+                return b;
+            }
+            (void)hipGetLastError();   // not ready; the later ones hardly are
+            ++busy;
+        }
+        if (p.bytes + cls > kPinnedBytes) return Pinned{};
+        p.bytes += cls;
+    }
+    Pinned b;
+    b.dev = dev;
+    b.bytes = cls;
+    if (hipHostMalloc(&b.ptr, cls, hipHostMallocCoherent) != hipSuccess) {
+        b.ptr = nullptr;
+    } else if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipHostFree(b.ptr);
+        b.ptr = nullptr;
+    }
+    if (!b.ptr) {
+        (void)hipGetLastError();
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        pins().bytes -= cls;
+    }
+    return b;
+}
+
+void pin_free(Pinned &b) {
+    (void)hipEventSynchronize(b.done);
+    (void)hipEventDestroy(b.done);
+    (void)hipHostFree(b.ptr);
+}
+}  // namespace
+
+StageHold::StageHold() {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    ++pins().holders;
+}
+StageHold::~StageHold() {
+    std::vector<Pinned> all;
+    std::vector<ListBlock> lists;
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        PinPool &p = pins();
+        if (--p.holders > 0) return;
+        all.swap(p.blocks);
+        lists.swap(p.lists);
+        for (const Pinned &b : all) p.bytes -= b.bytes;
+        for (const ListBlock &b : lists) p.list_bytes -= b.bytes;
+    }
+    for (Pinned &b : all) pin_free(b);
+    for (ListBlock &b : lists) (void)hipFree(b.ptr);   // waits for the device
+}
+
+void ListBuf::ensure(size_t n, hipStream_t stream) {
+    if (ptr && n <= bytes && s == stream) return;
+    release();
+    int d = 0;
+    HIP_OK(hipGetDevice(&d));
+    size_t cls = size_t(4) << 10;
+    while (cls < n) cls <<= 1;
+    if (cls > kListBlock) {
+        large.ensure(n);
+        ptr = large.ptr;
+        bytes = large.bytes;
+        s = stream;
+        return;
+    }
+    bool room = false;
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        PinPool &p = pins();
+        for (size_t k = p.lists.size(); k-- > 0 && !ptr;) {
+            const ListBlock &b = p.lists[k];
+            if (b.dev != d || b.s != stream || b.bytes != cls) continue;
+            ptr = b.ptr;
+            p.lists.erase(p.lists.begin() + (ptrdiff_t)k);
+        }
+        room = ptr || p.list_bytes + cls <= kListBytes;
+        if (!ptr && room) p.list_bytes += cls;
+    }
+    if (!ptr && room && hipMalloc(&ptr, cls) != hipSuccess) {
+        (void)hipGetLastError();
+        ptr = nullptr;
+        room = false;
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        pins().list_bytes -= cls;
+    }
+    if (!room) {   // from the allocator, which gives its cache back when memory is short
+        large.ensure(cls);
+        ptr = large.ptr;
+    }
+    bytes = cls;
+    dev = d;
+    s = stream;
+}
+
+void ListBuf::release() {
+    if (ptr && !large.ptr) {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        pins().lists.push_back(ListBlock{ptr, bytes, dev, s});
+    }
+    large.release();
+    ptr = nullptr;
+    bytes = 0;
+}
+
+namespace {
+// Back to the pool; what used the block on `s` has been launched.
+void pin_give(const Pinned &b, hipStream_t s) {
+    const bool ok = hipEventRecord(b.done, s) == hipSuccess;
+    if (!ok) (void)hipStreamSynchronize(s);   // no event to wait for
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        pins().blocks.push_back(b);
+    }
+    PD_REQUIRE(ok, PDMRG_EHIP, "pinned copy: event record failed");
+}
+}  // namespace
+
+void read_back(const std::vector<HostCopy> &parts, hipStream_t s) {
+    size_t total = 0;
+    for (const HostCopy &p : parts) total += (p.bytes + 255) & ~size_t(255);
+    int dev = 0;
+    HIP_OK(hipGetDevice(&dev));
+    Pinned b;
+    if (total > 0 && total <= kPinnedBlock) b = pin_take(dev, total);
+    size_t at = 0;
+    for (const HostCopy &p : parts) {
+        if (p.bytes == 0) continue;
+        if (b.ptr) launch_list_copy(static_cast<char *>(b.ptr) + at, p.src, p.bytes, s);
+        else HIP_OK(hipMemcpyAsync(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost, s));
+        at += (p.bytes + 255) & ~size_t(255);
+    }
+    const hipError_t e = hipStreamSynchronize(s);
+    if (b.ptr) {
+        at = 0;
+        for (const HostCopy &p : parts) {
+            if (p.bytes) std::memcpy(p.dst, static_cast<char *>(b.ptr) + at, p.bytes);
+            at += (p.bytes + 255) & ~size_t(255);
+        }
+        std::lock_guard<std::mutex> lk(g_pin_mu);   // its event has passed: no copy of it is under way
+        pins().blocks.push_back(b);
+    }
+    HIP_OK(e);
+}
+
+void ListStage::flush(DevBuf &buf, hipStream_t s) {
+    buf.ensure(std::max<size_t>(total_, 16));
+    copy(buf.as<char>(), s);
+}
+void ListStage::flush(ListBuf &buf, hipStream_t s) {
+    buf.ensure(std::max<size_t>(total_, 16), s);
+    copy(buf.as<char>(), s);
+}
+
+void ListStage::copy(char *dst, hipStream_t s) {
+    int dev = 0;
+    HIP_OK(hipGetDevice(&dev));
+    Pinned b;
+    if (total_ > 0 && total_ <= kPinnedBlock) b = pin_take(dev, total_);
+    for (const Part &pt : parts_) {
+        *pt.dst = dst + pt.at;
+        if (pt.bytes == 0) continue;
+        if (b.ptr) std::memcpy(static_cast<char *>(b.ptr) + pt.at, pt.src, pt.bytes);
+        else HIP_OK(hipMemcpyAsync(dst + pt.at, pt.src, pt.bytes, hipMemcpyHostToDevice, s));
+    }
+    if (b.ptr) {
+        launch_list_copy(dst, b.ptr, total_, s);
+        pin_give(b, s);
+    }
+    parts_.clear();
+    total_ = 0;
 }
 
 void check_grid(int64_t blocks, int threads, const char *what) {

@@ -87,7 +87,7 @@ extern "C" int env_update_noalloc(pdmrg_ctx *ctx, int dir, const pdmrg_bond *bl,
         PD_REQUIRE(prec == PDMRG_F64, PDMRG_EINVAL, "env_update_noalloc: only FP64 environments are supported");
         hipStream_t s = ctx->stream;
         EnvPlan plan;   // host work lists only: nothing is uploaded
-        plan.build(dir, Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W), s, false);
+        plan.build(dir, Bond::from(bl), Bond::from(br), Phys::from(phys), MpoSite::from(W));
         plan.g1.build_tiles();
         plan.w.build_tiles();
         plan.g3.build_tiles();

@@ -77,14 +77,6 @@ int GemmList::ntiles_for(TileShape t) const {
     return n;
 }
 
-double GemmList::padded_flops(TileShape t) const {
-    const int bm = tile_bm(t), bn = tile_bn(t);
-    double f = 0.0;
-    for (const GemmItem &it : items)
-        f += 2.0 * ((it.M + bm - 1) / bm * bm) * (double)((it.N + bn - 1) / bn * bn) * (double)item_k(*this, it);
-    return f;
-}
-
 double GemmList::operand_bytes() const {
     double b = 0.0;
     for (const GemmItem &it : items) b += (double)elem_bytes * (double)item_k(*this, it) * ((double)it.M + it.N);
@@ -148,17 +140,21 @@ void GemmList::pick_tile(double bytes) {
     // in FP64 the staged kernel measured faster than the LDS-DMA one (the
     // autotuner still times both)
     const unsigned shapes = elem_bytes == 8 ? shapes_allowed & kStagedShapes : shapes_allowed;
+    std::vector<int64_t> kof(items.size());
+    for (size_t i = 0; i < items.size(); ++i) kof[i] = item_k(*this, items[i]);
     for (int t = 0; t < (int)TileShape::T64x64_R; ++t) {
         if (!(shapes & (1u << t))) continue;
         const TileShape ts = (TileShape)t;
-        double cap = 0.0;   // tiles after the split-K the long items allow
+        double cap = 0.0, padded = 0.0;   // tiles after the split-K the long items allow; MFMA work
         const int bm = tile_bm(ts), bn = tile_bn(ts);
-        for (const GemmItem &it : items) {
-            const double nt = ((it.M + bm - 1) / bm) * (double)((it.N + bn - 1) / bn);
-            cap += nt * std::max<int64_t>(1, std::min<int64_t>(8, item_k(*this, it) / 256));
+        for (size_t i = 0; i < items.size(); ++i) {
+            const GemmItem &it = items[i];
+            const int tm = (it.M + bm - 1) / bm, tn = (it.N + bn - 1) / bn;
+            cap += tm * (double)tn * std::max<int64_t>(1, std::min<int64_t>(8, kof[i] / 256));
+            padded += 2.0 * (tm * bm) * (double)(tn * bn) * (double)kof[i];
         }
         const double fill = std::min(1.0, cap / 1024.0);
-        const double cost = padded_flops(ts) / (kRate[t] * std::max(fill, 1e-3));
+        const double cost = padded / (kRate[t] * std::max(fill, 1e-3));
         if (!have || cost < best * 0.999) {
             best = cost;
             shape = ts;
@@ -237,13 +233,20 @@ static std::vector<GemmTile> place_tiles(const std::vector<GemmItem> &items, con
 
 void GemmList::finish(hipStream_t s) {
     build_tiles();
-    upload(d_items, items, s);
-    upload(d_segs, segs, s);
-    upload(d_tiles, tiles, s);
-    if (ftiles.empty()) d_ftiles.release();
-    else upload(d_ftiles, ftiles, s);
-    if (rowoff.empty()) d_rowoff.release();
-    else upload(d_rowoff, rowoff, s);
+    ListStage st;
+    stage(st);
+    st.flush(d_lists, s);
+}
+
+void GemmList::stage(ListStage &st) {
+    if (ftiles.empty()) {
+        st.add(dev.items, items);
+        st.add(dev.segs, segs);
+        st.add(dev.tiles, tiles);
+    } else {
+        st.add(dev.ftiles, ftiles);
+    }
+    st.add(dev.rowoff, rowoff);
 }
 
 void GemmList::build_tiles() {
@@ -436,9 +439,7 @@ int64_t GemmList::split_k(int parts, int pslot, LcList &reduce, bool all) {
 }
 
 void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, hipStream_t s) const {
-    GemmDev dv{d_items.as<GemmItem>(), d_segs.as<GemmSeg>(), d_tiles.as<GemmTile>(), d_ftiles.as<FlatTile>(),
-               d_rowoff.as<int64_t>()};
-    launch(prec, c_is_f64, sl, dv, s);
+    launch(prec, c_is_f64, sl, dev, s);
 }
 
 void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, const GemmDev &dv, hipStream_t s) const {
@@ -495,23 +496,27 @@ void LcList::build_tiles() {
 
 void LcList::finish(hipStream_t s) {
     build_tiles();
-    upload(d_tasks, tasks, s);
-    upload(d_srcs, srcs, s);
-    upload(d_tiles, tiles, s);
+    ListStage st;
+    stage(st);
+    st.flush(d_lists, s);
+}
+
+void LcList::stage(ListStage &st) {
+    st.add(dev.tasks, tasks);
+    st.add(dev.srcs, srcs);
+    st.add(dev.tiles, tiles);
 }
 
 void LcList::launch_f32_to_f64(const Slots &sl, hipStream_t s) const {
-    launch_lincomb_f32_f64(chunk, sl, d_tasks.as<LcTask>(), d_srcs.as<LcSrc>(), d_tiles.as<LcTile>(),
-                           (int)tiles.size(), s);
+    launch_lincomb_f32_f64(chunk, sl, dev.tasks, dev.srcs, dev.tiles, (int)tiles.size(), s);
 }
 
 void LcList::launch_split(const Slots &sl, hipStream_t s) const {
-    launch_lincomb_split(chunk, sl, d_tasks.as<LcTask>(), d_srcs.as<LcSrc>(), d_tiles.as<LcTile>(), (int)tiles.size(),
-                         s);
+    launch_lincomb_split(chunk, sl, dev.tasks, dev.srcs, dev.tiles, (int)tiles.size(), s);
 }
 
 void LcList::launch(bool f64, const Slots &sl, hipStream_t s) const {
-    launch(f64, sl, LcDev{d_tasks.as<LcTask>(), d_srcs.as<LcSrc>(), d_tiles.as<LcTile>()}, s);
+    launch(f64, sl, dev, s);
 }
 
 void LcList::launch(bool f64, const Slots &sl, const LcDev &dv, hipStream_t s) const {
@@ -539,6 +544,12 @@ std::vector<double> two_site_mpo(const MpoSite &W1, const MpoSite &W2) {
                 }
     return W12;
 }
+
+// A nonzero MPO entry: its two indices that a sum runs over, in the sum's order.
+struct Entry {
+    int x, y;
+    double c;
+};
 
 // ---------------------------------------------------------------- H_eff
 void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W1, const MpoSite &W2,
@@ -592,6 +603,14 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
 
     // stage 2: W stage
     w = LcList();
+    std::vector<std::vector<Entry>> nz((size_t)d2 * Dr);   // of (s1 s2, w2): (w, t1 t2) in order
+    for (int ww = 0; ww < Dl; ++ww)
+        for (int sg = 0; sg < d2; ++sg)
+            for (int tg = 0; tg < d2; ++tg)
+                for (int w2 = 0; w2 < Dr; ++w2) {
+                    const double c = w12(ww, sg / d, tg / d, sg % d, tg % d, w2);
+                    if (c != 0.0) nz[(size_t)sg * Dr + w2].push_back(Entry{ww, tg, c});
+                }
     for (int i = 0; i < nl; ++i)
         for (int sg = 0; sg < d2; ++sg) {
             const int64_t tb = t2base[(size_t)i * d2 + sg];
@@ -604,21 +623,17 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
                 if (ro < 0) continue;
                 const int cols = br.dim_of(qb - W2.dr[w2]);
                 w.add_task(5, tb + ro, bl.dim[i], cols, Rt.rows[k]);
-                for (int ww = 0; ww < Dl; ++ww) {
+                for (const Entry &e : nz[(size_t)sg * Dr + w2]) {
+                    const int ww = e.x, tg = e.y;
                     const int j = bl.find(bl.q[i] - W1.dl[ww]);
                     if (j < 0 || t1base[j] < 0) continue;
                     const int lro = Lt.rowo[(size_t)j * Dl + ww];
                     if (lro < 0) continue;
-                    for (int t1 = 0; t1 < d; ++t1)
-                        for (int t2 = 0; t2 < d; ++t2) {
-                            const double c = w12(ww, s1, t1, s2, t2, w2);
-                            if (c == 0.0) continue;
-                            const int co = X.colo[(size_t)j * d2 + t1 * d + t2];
-                            if (co < 0) continue;
-                            PD_REQUIRE(X.width[(size_t)j * d2 + t1 * d + t2] == cols, PDMRG_ESHAPE,
-                                       "heff: MPO entry violates charge conservation");
-                            w.add_src(4, t1base[j] + (int64_t)lro * X.cols[j] + co, X.cols[j], c);
-                        }
+                    const int co = X.colo[(size_t)j * d2 + tg];
+                    if (co < 0) continue;
+                    PD_REQUIRE(X.width[(size_t)j * d2 + tg] == cols, PDMRG_ESHAPE,
+                               "heff: MPO entry violates charge conservation");
+                    w.add_src(4, t1base[j] + (int64_t)lro * X.cols[j] + co, X.cols[j], e.c);
                 }
             }
         }
@@ -756,27 +771,23 @@ void HeffPlan::set_g3_shape(TileShape t, hipStream_t s, int parts) {
 }
 
 // ---------------------------------------------------------------- environments
-void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W, hipStream_t s,
-                    bool upload) {
+void EnvPlan::begin(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W) {
     dir = dir_;
     bl = bl_;
     br = br_;
     p = p_;
     const int d = p.d();
     PD_REQUIRE(W.d == d, PDMRG_ESHAPE, "env: MPO local dimension mismatch");
-    const int Dl = W.Dl, Dr = W.Dr;
     S = site_layout(bl, br, p);
     const int nl = bl.nsec(), nr = br.nsec();
     g1 = GemmList();
-    g3 = GemmList();
-    w = LcList();
+    nU1 = nU2 = 0;
     if (dir > 0) {
         Ein = env_l_layout(bl, W.dl);
         Eout = env_l_layout(br, W.dr);
         Aux = env_r_layout(br, W.dr);     // column structure of U2 blocks
         // E1: U1[j] = Lket[j] x A[j]
-        std::vector<int64_t> u1base(nl, -1);
-        nU1 = 0;
+        u1base.assign(nl, -1);
         for (int j = 0; j < nl; ++j) {
             const int M = Ein.rows[j], N = S.cols[j], K = bl.dim[j];
             if (M == 0 || N == 0) continue;
@@ -786,8 +797,7 @@ void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, 
             nU1 += (int64_t)M * N;
         }
         // U2 blocks (i, s): [dim(q_i) x Aux.rows[k]]
-        std::vector<int64_t> u2base((size_t)nl * d, -1);
-        nU2 = 0;
+        u2base.assign((size_t)nl * d, -1);
         for (int i = 0; i < nl; ++i)
             for (int sp = 0; sp < d; ++sp) {
                 if (S.colo[(size_t)i * d + sp] < 0) continue;
@@ -795,7 +805,51 @@ void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, 
                 u2base[(size_t)i * d + sp] = nU2;
                 nU2 += (int64_t)bl.dim[i] * Aux.rows[k];
             }
+    } else {
+        Ein = env_r_layout(br, W.dr);
+        Eout = env_r_layout(bl, W.dl);
+        // F1: Z1[(k,s)] = Rbra[k] x B[(i,s)]^T, i = q_k - q_s
+        u1base.assign((size_t)nr * d, -1);
+        g1.tb = true;
+        for (int k = 0; k < nr; ++k)
+            for (int sp = 0; sp < d; ++sp) {
+                const int i = bl.find(br.q[k] - p.q[sp]);
+                if (i < 0 || Ein.rows[k] == 0) continue;
+                u1base[(size_t)k * d + sp] = nU1;
+                g1.add_item(3, nU1, Ein.rows[k], bl.dim[i], bl.dim[i]);
+                g1.add_seg(0, Ein.base[k], br.dim[k], 1, S.base[i] + S.colo[(size_t)i * d + sp], S.cols[i],
+                           br.dim[k]);
+                nU1 += (int64_t)Ein.rows[k] * bl.dim[i];
+            }
+        // Z2 blocks (i, w): [S.cols[i'] x dim(q_i)], i' = q_i - dl_w
+        u2base.assign((size_t)nl * W.Dl, -1);
+        for (int i = 0; i < nl; ++i)
+            for (int ww = 0; ww < W.Dl; ++ww) {
+                const int ip = bl.find(bl.q[i] - W.dl[ww]);
+                if (ip < 0 || S.cols[ip] == 0) continue;
+                u2base[(size_t)i * W.Dl + ww] = nU2;
+                nU2 += (int64_t)S.cols[ip] * bl.dim[i];
+            }
+    }
+    g1.validate({Ein.size, S.size, Eout.size, nU1});
+    g1.pick_tile();
+}
+
+void EnvPlan::finish(const MpoSite &W) {
+    const int d = p.d(), Dl = W.Dl, Dr = W.Dr;
+    const int nl = bl.nsec(), nr = br.nsec();
+    g3 = GemmList();
+    w = LcList();
+    if (dir > 0) {
         // E2: U2[(i,s)][a, (w', b')] = sum W[w,s,t,w'] U1[q_i - dl_w][(w,a), (t,b')]
+        std::vector<std::vector<Entry>> nz((size_t)d * Dr);   // of (s, w'): (w, t) in order
+        for (int ww = 0; ww < Dl; ++ww)
+            for (int sp = 0; sp < d; ++sp)
+                for (int t = 0; t < d; ++t)
+                    for (int w2 = 0; w2 < Dr; ++w2) {
+                        const double c = W.at(ww, sp, t, w2);
+                        if (c != 0.0) nz[(size_t)sp * Dr + w2].push_back(Entry{ww, t, c});
+                    }
         for (int i = 0; i < nl; ++i)
             for (int sp = 0; sp < d; ++sp) {
                 const int64_t ub = u2base[(size_t)i * d + sp];
@@ -807,20 +861,17 @@ void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, 
                     if (ro < 0) continue;
                     const int cols = br.dim_of(qb - W.dr[w2]);
                     w.add_task(4, ub + ro, bl.dim[i], cols, Aux.rows[k]);
-                    for (int ww = 0; ww < Dl; ++ww) {
+                    for (const Entry &e : nz[(size_t)sp * Dr + w2]) {
+                        const int ww = e.x, t = e.y;
                         const int j = bl.find(bl.q[i] - W.dl[ww]);
                         if (j < 0 || u1base[j] < 0) continue;
                         const int lro = Ein.rowo[(size_t)j * Dl + ww];
                         if (lro < 0) continue;
-                        for (int t = 0; t < d; ++t) {
-                            const double c = W.at(ww, sp, t, w2);
-                            if (c == 0.0) continue;
-                            const int co = S.colo[(size_t)j * d + t];
-                            if (co < 0) continue;
-                            PD_REQUIRE(S.width[(size_t)j * d + t] == cols, PDMRG_ESHAPE,
-                                       "env: MPO entry violates charge conservation");
-                            w.add_src(3, u1base[j] + (int64_t)lro * S.cols[j] + co, S.cols[j], c);
-                        }
+                        const int co = S.colo[(size_t)j * d + t];
+                        if (co < 0) continue;
+                        PD_REQUIRE(S.width[(size_t)j * d + t] == cols, PDMRG_ESHAPE,
+                                   "env: MPO entry violates charge conservation");
+                        w.add_src(3, u1base[j] + (int64_t)lro * S.cols[j] + co, S.cols[j], e.c);
                     }
                 }
             }
@@ -843,36 +894,18 @@ void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, 
                 }
             }
     } else {
-        Ein = env_r_layout(br, W.dr);
-        Eout = env_r_layout(bl, W.dl);
-        // F1: Z1[(k,s)] = Rbra[k] x B[(i,s)]^T, i = q_k - q_s
-        std::vector<int64_t> z1base((size_t)nr * d, -1);
-        nU1 = 0;
-        g1.tb = true;
-        for (int k = 0; k < nr; ++k)
-            for (int sp = 0; sp < d; ++sp) {
-                const int i = bl.find(br.q[k] - p.q[sp]);
-                if (i < 0 || Ein.rows[k] == 0) continue;
-                z1base[(size_t)k * d + sp] = nU1;
-                g1.add_item(3, nU1, Ein.rows[k], bl.dim[i], bl.dim[i]);
-                g1.add_seg(0, Ein.base[k], br.dim[k], 1, S.base[i] + S.colo[(size_t)i * d + sp], S.cols[i],
-                           br.dim[k]);
-                nU1 += (int64_t)Ein.rows[k] * bl.dim[i];
-            }
-        // Z2 blocks (i, w): [S.cols[i'] x dim(q_i)], i' = q_i - dl_w
-        std::vector<int64_t> z2base((size_t)nl * Dl, -1);
-        nU2 = 0;
-        for (int i = 0; i < nl; ++i)
-            for (int ww = 0; ww < Dl; ++ww) {
-                const int ip = bl.find(bl.q[i] - W.dl[ww]);
-                if (ip < 0 || S.cols[ip] == 0) continue;
-                z2base[(size_t)i * Dl + ww] = nU2;
-                nU2 += (int64_t)S.cols[ip] * bl.dim[i];
-            }
         // F2: Z2[(i,w)][(s', b'), a] = sum W[w,s,s',w2] Z1[(k,s)][(w2,b'), a]
+        std::vector<std::vector<Entry>> nz((size_t)Dl * d);   // of (w, s'): (s, w2) in order
+        for (int ww = 0; ww < Dl; ++ww)
+            for (int sp = 0; sp < d; ++sp)
+                for (int spp = 0; spp < d; ++spp)
+                    for (int w2 = 0; w2 < Dr; ++w2) {
+                        const double c = W.at(ww, sp, spp, w2);
+                        if (c != 0.0) nz[(size_t)ww * d + spp].push_back(Entry{sp, w2, c});
+                    }
         for (int i = 0; i < nl; ++i)
             for (int ww = 0; ww < Dl; ++ww) {
-                const int64_t zb = z2base[(size_t)i * Dl + ww];
+                const int64_t zb = u2base[(size_t)i * Dl + ww];
                 if (zb < 0) continue;
                 const int ip = bl.find(bl.q[i] - W.dl[ww]);
                 for (int spp = 0; spp < d; ++spp) {
@@ -880,20 +913,17 @@ void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, 
                     if (co < 0) continue;
                     const int rows = S.width[(size_t)ip * d + spp];
                     w.add_task(4, zb + (int64_t)co * bl.dim[i], rows, bl.dim[i], bl.dim[i]);
-                    for (int sp = 0; sp < d; ++sp) {
+                    for (const Entry &e : nz[(size_t)ww * d + spp]) {
+                        const int sp = e.x, w2 = e.y;
                         const int k = br.find(bl.q[i] + p.q[sp]);
                         if (k < 0) continue;
-                        const int64_t z1 = z1base[(size_t)k * d + sp];
+                        const int64_t z1 = u1base[(size_t)k * d + sp];
                         if (z1 < 0) continue;
-                        for (int w2 = 0; w2 < Dr; ++w2) {
-                            const double c = W.at(ww, sp, spp, w2);
-                            if (c == 0.0) continue;
-                            const int ro = Ein.rowo[(size_t)k * Dr + w2];
-                            if (ro < 0) continue;
-                            PD_REQUIRE(br.dim_of(br.q[k] - W.dr[w2]) == rows, PDMRG_ESHAPE,
-                                       "env: MPO entry violates charge conservation");
-                            w.add_src(3, z1 + (int64_t)ro * bl.dim[i], bl.dim[i], c);
-                        }
+                        const int ro = Ein.rowo[(size_t)k * Dr + w2];
+                        if (ro < 0) continue;
+                        PD_REQUIRE(br.dim_of(br.q[k] - W.dr[w2]) == rows, PDMRG_ESHAPE,
+                                   "env: MPO entry violates charge conservation");
+                        w.add_src(3, z1 + (int64_t)ro * bl.dim[i], bl.dim[i], e.c);
                     }
                 }
             }
@@ -904,20 +934,43 @@ void EnvPlan::build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, 
                 if (ro < 0) continue;
                 const int ip = bl.find(bl.q[i] - W.dl[ww]);
                 g3.add_item(2, Eout.base[i] + (int64_t)ro * bl.dim[i], bl.dim[ip], bl.dim[i], bl.dim[i]);
-                const int64_t zb = z2base[(size_t)i * Dl + ww];
+                const int64_t zb = u2base[(size_t)i * Dl + ww];
                 if (zb >= 0) g3.add_seg(1, S.base[ip], S.cols[ip], 4, zb, bl.dim[i], S.cols[ip]);
             }
     }
     const std::vector<int64_t> sz = {Ein.size, S.size, Eout.size, nU1, nU2};
-    g1.validate(sz);
     w.validate(sz);
     g3.validate(sz);
-    g1.pick_tile();
     g3.pick_tile();
-    if (!upload) return;
-    g1.finish(s);
-    w.finish(s);
-    g3.finish(s);
+}
+
+void EnvPlan::run(const MpoSite &W, const void *env_in, const void *site, void *env_out, DevBuf &ws, hipStream_t s) {
+    Slots sl{};
+    sl.p[0] = env_in;
+    sl.p[1] = site;
+    sl.p[2] = env_out;
+    const size_t n1 = (size_t)std::max<int64_t>(nU1, 1);
+    ws.ensure((n1 + (size_t)std::max<int64_t>(nU2, 1)) * sizeof(double));
+    sl.p[3] = ws.as<double>();
+    sl.p[4] = ws.as<double>() + n1;
+    ListStage st;
+    g1.build_tiles();
+    g1.stage(st);
+    st.flush(d_lists1, s);
+    g1.launch(GemmPrec::F64, true, sl, s);
+    try {
+        finish(W);
+        w.build_tiles();
+        g3.build_tiles();
+        w.stage(st);
+        g3.stage(st);
+        st.flush(d_lists, s);
+    } catch (...) {
+        (void)hipStreamSynchronize(s);   // nothing left running on the caller's buffers
+        throw;
+    }
+    w.launch(true, sl, s);
+    g3.launch(GemmPrec::F64, true, sl, s);
 }
 
 void EnvPlan::run(GemmPrec prec, const void *env_in, const void *site, void *env_out, void *U1, void *U2,
@@ -934,22 +987,9 @@ void EnvPlan::run(GemmPrec prec, const void *env_in, const void *site, void *env
     g3.launch(prec, f64, sl, d3, s);
 }
 
-void EnvPlan::run(GemmPrec prec, const void *env_in, const void *site, void *env_out, void *U1, void *U2,
-                  hipStream_t s) const {
-    Slots sl{};
-    sl.p[0] = env_in;
-    sl.p[1] = site;
-    sl.p[2] = env_out;
-    sl.p[3] = U1;
-    sl.p[4] = U2;
-    const bool f64 = prec == GemmPrec::F64;
-    g1.launch(prec, f64, sl, s);
-    w.launch(f64, sl, s);
-    g3.launch(prec, f64, sl, s);
-}
-
 // ---------------------------------------------------------------- gradient
-void GradPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W, hipStream_t s) {
+void GradPlan::run(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W, const double *L,
+                   const double *psi, const double *R, DevBuf &ws, DevBuf &ws2, double *G, hipStream_t s) {
     bl = bl_;
     br = br_;
     p = p_;
@@ -973,11 +1013,51 @@ void GradPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
         g1.add_seg(0, Lt.base[j], K, 1, S.base[j], N, K);
         nU1 += (int64_t)M * N;
     }
-    // stage 2: Z blocks [b'][b] = U1^T psi, then stage-3 dot tasks
+    g1.validate({Lt.size, S.size, Rt.size, nU1});
+    g1.pick_tile();
+    Slots sl{};
+    sl.p[0] = L;
+    sl.p[1] = psi;
+    sl.p[2] = R;
+    ws.ensure((size_t)std::max<int64_t>(nU1, 1) * sizeof(double));
+    sl.p[3] = ws.ptr;
+    ListStage st;
+    g1.build_tiles();
+    g1.stage(st);
+    st.flush(d_lists1, s);
+    launch_fill(G, 0.0, (int64_t)Dl * d * d * Dr, s);
+    g1.launch(GemmPrec::F64, true, sl, s);
+    try {
+        rest(W, u1base);
+        gz.build_tiles();
+        gz.stage(st);
+        st.add(d_dots, dots);
+        st.add(d_dtiles, dtiles);
+        st.add(d_t0, t0);
+        st.add(d_gof, g_of);
+        st.flush(d_lists, s);
+        ws2.ensure((std::max<size_t>(nZ, 1) + std::max<size_t>(dtiles.size(), 1)) * sizeof(double));
+    } catch (...) {
+        (void)hipStreamSynchronize(s);   // nothing left running on the caller's buffers
+        throw;
+    }
+    double *partial = ws2.as<double>() + std::max<int64_t>(nZ, 1);
+    sl.p[4] = ws2.ptr;
+    gz.launch(GemmPrec::F64, true, sl, s);
+    launch_dot_partials(sl, 4, 2, d_dots, d_dtiles, (int)dtiles.size(), partial, s);
+    launch_dot_reduce(partial, d_t0, d_gof, (int)g_of.size(), G, s);
+}
+
+// stage 2: Z blocks [b'][b] = U1^T psi, then stage-3 dot tasks
+void GradPlan::rest(const MpoSite &W, const std::vector<int64_t> &u1base) {
+    const int d = p.d(), nl = bl.nsec();
     gz = GemmList();
     gz.ta = true;
     dots.clear();
     nZ = 0;
+    std::map<int, std::vector<int>> channels;   // of R, by charge
+    for (int w2 = 0; w2 < Dr; ++w2) channels[W.dr[w2]].push_back(w2);
+    std::vector<int> wr;
     for (int i = 0; i < nl; ++i)
         for (int w = 0; w < Dl; ++w) {
             const int j = bl.find(bl.q[i] - W.dl[w]);
@@ -994,9 +1074,11 @@ void GradPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
                     if (ct < 0) continue;
                     const int qbk = bl.q[j] + p.q[t];
                     // channels w' of R with delta = qb - qbk
-                    std::vector<int> wr;
-                    for (int w2 = 0; w2 < Dr; ++w2)
-                        if (W.dr[w2] == qb - qbk && Rt.rowo[(size_t)kb * Dr + w2] >= 0) wr.push_back(w2);
+                    const auto ch = channels.find(qb - qbk);
+                    if (ch == channels.end()) continue;
+                    wr.clear();
+                    for (int w2 : ch->second)
+                        if (Rt.rowo[(size_t)kb * Dr + w2] >= 0) wr.push_back(w2);
                     if (wr.empty()) continue;
                     const int M = br.dim_of(qbk), N = br.dim[kb], K = bl.dim[i];
                     gz.add_item(4, nZ, M, N, N);
@@ -1011,10 +1093,12 @@ void GradPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
                 }
             }
         }
-    // dot tiles grouped by output entry, tasks of one entry in build order
-    std::vector<int> order(dots.size());
-    for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return dots[a].g < dots[b].g; });
+    // dot tiles grouped by output entry, tasks of one entry in build order (a
+    // counting sort: the entries are indices of the gradient)
+    std::vector<int> order(dots.size()), first((size_t)Dl * d * d * Dr + 1, 0);
+    for (const DotTask &dt : dots) ++first[(size_t)dt.g + 1];
+    for (size_t k = 1; k < first.size(); ++k) first[k] += first[k - 1];
+    for (size_t k = 0; k < dots.size(); ++k) order[first[dots[k].g]++] = (int)k;
     dtiles.clear();
     t0.clear();
     g_of.clear();
@@ -1034,32 +1118,8 @@ void GradPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
         flops += 2.0 * dt.n;
     }
     flops += g1.flops + gz.flops;
-    const std::vector<int64_t> sz = {Lt.size, S.size, Rt.size, nU1, nZ};
-    g1.validate(sz);
-    gz.validate(sz);
-    g1.pick_tile();
+    gz.validate({Lt.size, S.size, Rt.size, nU1, nZ});
     gz.pick_tile();
-    g1.finish(s);
-    gz.finish(s);
-    upload(d_dots, dots, s);
-    upload(d_dtiles, dtiles, s);
-    upload(d_t0, t0, s);
-    upload(d_gof, g_of, s);
-}
-
-void GradPlan::run(const double *L, const double *psi, const double *R, double *U1, double *Z, double *partial,
-                   double *G, hipStream_t s) const {
-    Slots sl{};
-    sl.p[0] = L;
-    sl.p[1] = psi;
-    sl.p[2] = R;
-    sl.p[3] = U1;
-    sl.p[4] = Z;
-    launch_fill(G, 0.0, (int64_t)Dl * p.d() * p.d() * Dr, s);
-    g1.launch(GemmPrec::F64, true, sl, s);
-    gz.launch(GemmPrec::F64, true, sl, s);
-    launch_dot_partials(sl, 4, 2, d_dots.as<DotTask>(), d_dtiles.as<DotTile>(), (int)dtiles.size(), partial, s);
-    launch_dot_reduce(partial, d_t0.as<int32_t>(), d_gof.as<int32_t>(), (int)g_of.size(), G, s);
 }
 
 // ---------------------------------------------------------------- merge
@@ -1106,17 +1166,19 @@ void MergePlan::build(const Bond &bl_, const Bond &bm_, const Bond &br_, const P
         }
     g.validate({SL.size, SR.size, X.size});
     g.pick_tile();
-    g.finish(s);
-    upload(d_rs_base, rs_base, s);
-    upload(d_rs_vbase, rs_vbase, s);
-    upload(d_rs_rows, rs_rows, s);
-    upload(d_rs_cols, rs_cols, s);
+    ListStage st;
+    g.build_tiles();
+    g.stage(st);
+    st.add(d_rs_base, rs_base);
+    st.add(d_rs_vbase, rs_vbase);
+    st.add(d_rs_rows, rs_rows);
+    st.add(d_rs_cols, rs_cols);
+    st.flush(d_lists, s);
 }
 
 void MergePlan::run(const double *psiL, const double *V, const double *psiR, double *out, double *scaled,
                     hipStream_t s) const {
-    launch_row_scale(psiR, scaled, d_rs_base.as<int64_t>(), d_rs_rows.as<int32_t>(), d_rs_cols.as<int32_t>(),
-                     d_rs_vbase.as<int64_t>(), (int)rs_base.size(), rs_max, V, s);
+    launch_row_scale(psiR, scaled, d_rs_base, d_rs_rows, d_rs_cols, d_rs_vbase, (int)rs_base.size(), rs_max, V, s);
     launch_fill(out, 0.0, X.size, s);
     Slots sl{};
     sl.p[0] = psiL;

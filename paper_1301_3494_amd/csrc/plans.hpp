@@ -46,11 +46,11 @@ struct GemmList {
     std::vector<int32_t> blk0;             // per item: first RowBlock, -1 for a plain item
     std::vector<RowBlock> blocks;
     double flops = 0.0;
-    DevBuf d_items, d_segs, d_tiles, d_rowoff;
     // LDS-DMA and register-direct shapes on lists of single-segment items: the
     // tiles as FlatTile records in the same launch order
     std::vector<FlatTile> ftiles;
-    DevBuf d_ftiles;
+    GemmDev dev{};                         // set by stage() / finish()
+    DevBuf d_lists;                        // what finish() uploads
 
     int add_item(int c_slot, int64_t c_off, int M, int N, int ldc);
     // An item whose M rows stack the given output blocks (each N wide).
@@ -66,11 +66,13 @@ struct GemmList {
     // The time compared for its shapes, with the K split of split_k(parts).
     double cost_r64(TileShape t, int parts) const;
     int ntiles_for(TileShape t) const;
-    double padded_flops(TileShape t) const;
-    // Build the tiles and place them for the launch (see place_tiles), upload.
+    // Build the tiles and place them for the launch (see place_tiles), upload:
+    // build_tiles(), then stage() into a buffer of this list's own.  A plan
+    // stages several lists into one buffer.
     void finish(hipStream_t s);
     // The host part of finish: tiles (and flat tiles) in launch order.
     void build_tiles();
+    void stage(ListStage &st);
     void launch(GemmPrec prec, bool c_is_f64, const Slots &sl, hipStream_t s) const;
     // Same with the records at caller-provided device addresses.
     void launch(GemmPrec prec, bool c_is_f64, const Slots &sl, const GemmDev &dv, hipStream_t s) const;
@@ -101,12 +103,14 @@ struct LcList {
     std::vector<LcTile> tiles;
     double flops = 0.0;
     int64_t elems_out = 0, elems_in = 0;
-    DevBuf d_tasks, d_srcs, d_tiles;
+    LcDev dev{};
+    DevBuf d_lists;
 
     int add_task(int dst_slot, int64_t dst_off, int rows, int cols, int ld);
     void add_src(int slot, int64_t off, int ld, double coef);
     void finish(hipStream_t s);
     void build_tiles();   // the host part of finish
+    void stage(ListStage &st);
     void launch(bool f64, const Slots &sl, hipStream_t s) const;
     void launch(bool f64, const Slots &sl, const LcDev &dv, hipStream_t s) const;
     void launch_f32_to_f64(const Slots &sl, hipStream_t s) const;
@@ -154,14 +158,22 @@ struct EnvPlan {
     int64_t nU1 = 0, nU2 = 0;
     GemmList g1, g3;
     LcList w;
-    // upload = false: host work lists only (counts, no device buffers).
-    void build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W, hipStream_t s,
-               bool upload = true);
+    std::vector<int64_t> u1base, u2base;   // per block of U1 (Z1) and U2 (Z2), -1: absent
+    ListBuf d_lists1, d_lists;
+    // The layouts and the list of the first product, then the rest.
+    void begin(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W);
+    void finish(const MpoSite &W);
+    // Both, for host work lists only (counts, no device buffers).
+    void build(int dir_, const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W) {
+        begin(dir_, bl_, br_, p_, W);
+        finish(W);
+    }
+    // After begin(): uploads and launches the first product and, while it runs,
+    // builds the rest.  ws holds U1 and U2; W as given to begin().
+    void run(const MpoSite &W, const void *env_in, const void *site, void *env_out, DevBuf &ws, hipStream_t s);
+    // After build() and the lists' build_tiles(), with the work-list records at
+    // caller-provided device addresses.
     // slots: 0 env_in, 1 site, 2 env_out, 3 U1, 4 U2
-    void run(GemmPrec prec, const void *env_in, const void *site, void *env_out, void *U1, void *U2,
-             hipStream_t s) const;
-    // Same with the work-list records at caller-provided device addresses
-    // (plan built with upload = false and the lists' build_tiles() called).
     void run(GemmPrec prec, const void *env_in, const void *site, void *env_out, void *U1, void *U2,
              const GemmDev &d1, const LcDev &dw, const GemmDev &d3, hipStream_t s) const;
 };
@@ -174,7 +186,9 @@ struct MergePlan {
     GemmList g;
     std::vector<int64_t> rs_base, rs_vbase;
     std::vector<int32_t> rs_rows, rs_cols;
-    DevBuf d_rs_base, d_rs_vbase, d_rs_rows, d_rs_cols;
+    ListBuf d_lists;
+    const int64_t *d_rs_base = nullptr, *d_rs_vbase = nullptr;
+    const int32_t *d_rs_rows = nullptr, *d_rs_cols = nullptr;
     int rs_max = 0;
     void build(const Bond &bl_, const Bond &bm_, const Bond &br_, const Phys &p_, hipStream_t s);
     void run(const double *psiL, const double *V, const double *psiR, double *out, double *scaled,
@@ -200,13 +214,17 @@ struct GradPlan {
     std::vector<DotTask> dots;
     std::vector<DotTile> dtiles;
     std::vector<int32_t> t0, g_of;   // tiles of output entry g_of[k]: t0[k] .. t0[k+1]
-    DevBuf d_dots, d_dtiles, d_t0, d_gof;
+    ListBuf d_lists1, d_lists;
+    const DotTask *d_dots = nullptr;
+    const DotTile *d_dtiles = nullptr;
+    const int32_t *d_t0 = nullptr, *d_gof = nullptr;
     double flops = 0.0;
-    void build(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W, hipStream_t s);
-    // slots: 0 L, 1 psi, 2 R, 3 U1, 4 Z; partial holds dtiles.size() doubles;
-    // G (Dl d d Dr) is overwritten.
-    void run(const double *L, const double *psi, const double *R, double *U1, double *Z, double *partial,
-             double *G, hipStream_t s) const;
+    // Uploads and launches stage 1 and, while it runs, builds the rest; ws is
+    // workspace for U1, ws2 for Z and the partial sums; G (Dl d d Dr) is overwritten.
+    // slots: 0 L, 1 psi, 2 R, 3 U1, 4 Z
+    void run(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSite &W, const double *L, const double *psi,
+             const double *R, DevBuf &ws, DevBuf &ws2, double *G, hipStream_t s);
+    void rest(const MpoSite &W, const std::vector<int64_t> &u1base);
 };
 
 std::vector<double> two_site_mpo(const MpoSite &W1, const MpoSite &W2);

@@ -68,12 +68,11 @@ size_t round32(size_t n) { return (n + 31) & ~size_t(31); }
 
 void run_copies(const std::vector<CopyTask> &tasks, hipStream_t s) {
     if (tasks.empty()) return;
-    DevBuf d;
-    upload(d, tasks, s);
+    ListBuf d;
+    upload_list(d, tasks, s);
     int64_t mx = 0;
     for (auto &t : tasks) mx = std::max<int64_t>(mx, (int64_t)t.rows * t.cols);
     launch_copies(d.as<CopyTask>(), (int)tasks.size(), mx, s);
-    HIP_OK(hipStreamSynchronize(s));   // d is freed on return
 }
 
 // One matrix of the Jacobi iteration: W (nv rows of length len, packed) and
@@ -96,7 +95,7 @@ struct JacMat {
 struct QrState {
     std::vector<int> len, inv_off;   // per matrix: row length of W; offset of P^-1 in d_idx
     std::vector<int32_t> idx;        // P then P^-1 per preconditioned matrix
-    DevBuf d_idx, d_items, d_panels, d_trail, d_back;
+    ListBuf d_idx, d_items, d_panels, d_trail, d_back;
     std::vector<QrItem> qitems;
     std::vector<int> who;            // matrix of each QrItem
     std::vector<QrPanel> panels;
@@ -121,13 +120,13 @@ void qr_factor(const std::vector<Mat> &mats, const std::vector<JacMat> &items, c
         if (!pre[i]) continue;
         for (int r = 0; r < items[i].nv; ++r) refs.push_back(RowRef{qm[i] + (size_t)r * qs.len[i], qs.len[i], 0});
     }
-    DevBuf d_refs, d_norm;
-    upload(d_refs, refs, s);
+    ListBuf d_refs;
+    DevBuf d_norm;
+    upload_list(d_refs, refs, s);
     d_norm.ensure(std::max<size_t>(refs.size(), 1) * sizeof(double));
     launch_row_norms(d_refs.as<RowRef>(), (int)refs.size(), d_norm.as<double>(), s);
     std::vector<double> norms(refs.size());
-    HIP_OK(hipMemcpyAsync(norms.data(), d_norm.ptr, refs.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
+    read_back({{norms.data(), d_norm.ptr, refs.size() * sizeof(double)}}, s);
     std::vector<int> perm_off(nm, -1);
     for (int i = 0; i < nm; ++i) {
         if (!pre[i]) continue;
@@ -142,7 +141,7 @@ void qr_factor(const std::vector<Mat> &mats, const std::vector<JacMat> &items, c
         qs.idx.resize(qs.idx.size() + nv);
         for (int r = 0; r < nv; ++r) qs.idx[qs.inv_off[i] + perm[r]] = r;
     }
-    upload(qs.d_idx, qs.idx, s);
+    upload_list(qs.d_idx, qs.idx, s);
     // A = P W
     std::vector<CopyTask> cp;
     int64_t mx = 0;
@@ -157,8 +156,8 @@ void qr_factor(const std::vector<Mat> &mats, const std::vector<JacMat> &items, c
         cp.push_back(t);
         mx = std::max<int64_t>(mx, (int64_t)items[i].nv * qs.len[i]);
     }
-    DevBuf d_cp;
-    upload(d_cp, cp, s);
+    ListBuf d_cp;
+    upload_list(d_cp, cp, s);
     launch_copies(d_cp.as<CopyTask>(), (int)cp.size(), mx, s);
     // panel task lists: factor, trailing update (Q^T), and later Y (from the right)
     int npan = 0;
@@ -196,10 +195,10 @@ void qr_factor(const std::vector<Mat> &mats, const std::vector<JacMat> &items, c
     qs.panel_off.push_back((int)qs.panels.size());
     qs.trail_off.push_back((int)qs.trail.size());
     qs.back_off.push_back((int)qs.back.size());
-    upload(qs.d_items, qs.qitems, s);
-    upload(qs.d_panels, qs.panels, s);
-    upload(qs.d_trail, qs.trail, s);
-    upload(qs.d_back, qs.back, s);
+    upload_list(qs.d_items, qs.qitems, s);
+    upload_list(qs.d_panels, qs.panels, s);
+    upload_list(qs.d_trail, qs.trail, s);
+    upload_list(qs.d_back, qs.back, s);
     for (int pn = 0; pn < npan; ++pn) {
         launch_qr_panels(qs.d_panels.as<QrPanel>() + qs.panel_off[pn], qs.panel_off[pn + 1] - qs.panel_off[pn],
                          qs.panel_span[pn], s);
@@ -207,12 +206,11 @@ void qr_factor(const std::vector<Mat> &mats, const std::vector<JacMat> &items, c
     }
     // the Jacobi iteration's rows: R
     launch_qr_extract_r(qs.d_items.as<QrItem>(), (int)qs.qitems.size(), qs.max_nv, s);
-    HIP_OK(hipStreamSynchronize(s));   // d_refs, d_norm, d_cp are freed on return
 }
 
 void qr_right_factor(QrState &qs, const std::vector<JacMat> &items, hipStream_t s) {
     for (size_t k = 0; k < qs.qitems.size(); ++k) qs.qitems[k].Z = items[qs.who[k]].Z;   // where the iteration left it
-    upload(qs.d_items, qs.qitems, s);
+    upload_list(qs.d_items, qs.qitems, s);
     launch_qr_embed_z(qs.d_items.as<QrItem>(), (int)qs.qitems.size(), qs.max_elems, s);
     for (int pn = (int)qs.panel_span.size() - 1; pn >= 0; --pn)
         launch_qr_apply(qs.d_back.as<QrApply>() + qs.back_off[pn], qs.back_off[pn + 1] - qs.back_off[pn], s);
@@ -300,9 +298,10 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
     std::vector<JacTask> tasks = eig;
     tasks.insert(tasks.end(), upd.begin(), upd.end());
     tasks.insert(tasks.end(), begt.begin(), begt.end());
-    DevBuf d_items, d_tasks, d_active, d_off;
-    upload(d_items, items, s);
-    upload(d_tasks, tasks, s);
+    ListBuf d_items, d_tasks, d_active;
+    DevBuf d_off;
+    upload_list(d_items, items, s);
+    upload_list(d_tasks, tasks, s);
     const JacTask *t_eig = d_tasks.as<JacTask>(), *t_upd = t_eig + eig.size(), *t_beg = t_upd + upd.size();
     d_off.ensure(n * sizeof(double));
     std::vector<int32_t> active(n, 1);
@@ -317,13 +316,12 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
         sl.p[4] = Qt;
         sl.p[5] = G;
         gG.launch(GemmPrec::F64, true, sl, s);
-        upload(d_active, active, s);
+        upload_list(d_active, active, s);
         launch_fill(d_off.as<double>(), 0.0, n, s);
         launch_jac_begin(d_items.as<JacItem>(), t_beg, (int)begt.size(), d_active.as<int32_t>(),
                          d_off.as<unsigned long long>(), s);
         if (sweep == 0) HIP_OK(hipMemcpyAsync(Z[0], Qt, nz * sizeof(double), hipMemcpyDeviceToDevice, s));   // I
-        HIP_OK(hipMemcpyAsync(off.data(), d_off.ptr, n * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_OK(hipStreamSynchronize(s));
+        read_back({{off.data(), d_off.ptr, n * sizeof(double)}}, s);
         int ract = 0;   // rounds of the largest matrix that is not done
         for (int k = 0; k < n; ++k) {
             if (active[k] && off[k] <= items[k].tol) active[k] = 0;
@@ -332,7 +330,7 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
         if (ract == 0 || sweep == kMaxSweeps) break;
         sweeps = sweep + 1;
         rounds += ract;
-        upload(d_active, active, s);
+        upload_list(d_active, active, s);
         for (int r = 0; r <= ract; ++r)
             launch_jac_round(d_items.as<JacItem>(), t_eig, r < ract ? (int)eig.size() : 0, t_upd, (int)upd.size(), r,
                              d_active.as<int32_t>(), s);
@@ -430,19 +428,19 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
     QrState qs;
     if (any_pre) qr_factor(mats, items, pre, qa, qm, qt, qs, s);
     int sweeps_done = 0, nrounds = 0;
-    DevBuf d_small, d_done;
+    ListBuf d_small;
+    DevBuf d_done;
     std::vector<int32_t> done(small.size(), 0);
     if (!small.empty()) {
         // by size, one launch per size class of the kernel
         std::stable_sort(small.begin(), small.end(), [](const JacSmall &a, const JacSmall &b) { return a.nv < b.nv; });
-        upload(d_small, small, s);
+        upload_list(d_small, small, s);
         d_done.ensure(small.size() * sizeof(int32_t));
         for (size_t a = 0, b = 0; a < small.size(); a = b) {
             const int top = small[a].nv <= 16 ? 16 : small[a].nv <= 32 ? 32 : kJacSmall;
             while (b < small.size() && small[b].nv <= top) ++b;
             launch_jac_small(d_small.as<JacSmall>() + a, (int)(b - a), top, kMaxSweeps, d_done.as<int32_t>() + a, s);
         }
-        HIP_OK(hipMemcpyAsync(done.data(), d_done.ptr, small.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     }
     // blocks whose rows were not orthogonal to tol after kMaxSweeps sweeps:
     // still an exact rotation of the block (absolute accuracy), reported
@@ -467,14 +465,14 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
         for (int r = 0; r < items[i].nv; ++r) refs.push_back(RowRef{items[i].W + (size_t)r * items[i].len, items[i].len, 0});
     }
     first[nm] = (int)refs.size();
-    DevBuf d_refs, d_norm;
-    upload(d_refs, refs, s);
+    ListBuf d_refs;
+    DevBuf d_norm;
+    upload_list(d_refs, refs, s);
     d_norm.ensure(std::max<size_t>(refs.size(), 1) * sizeof(double));
     launch_row_norms(d_refs.as<RowRef>(), (int)refs.size(), d_norm.as<double>(), s);
     std::vector<double> norms(refs.size());
-    if (!refs.empty())
-        HIP_OK(hipMemcpyAsync(norms.data(), d_norm.ptr, refs.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
+    read_back({{norms.data(), d_norm.ptr, refs.size() * sizeof(double)},
+               {done.data(), d_done.ptr, done.size() * sizeof(int32_t)}}, s);
     for (int32_t d : done) n_unconv += d < 0 ? 1 : 0;
 
     // sorted factors: wide Ut = Z rows, Vt = W rows / lambda; tall the reverse
@@ -525,8 +523,8 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
             }
         }
     }
-    DevBuf d_scales;
-    upload(d_scales, scales, s);
+    ListBuf d_scales;
+    upload_list(d_scales, scales, s);
     for (size_t r = 0; r < rowjobs.size(); ++r) {
         auto &[src, dst, len, si] = rowjobs[r];
         CopyTask t{};
@@ -881,6 +879,7 @@ void svd_truncate_multi(pdmrg_ctx *ctx, const std::vector<SvdProblem> &probs, do
         finish_problem(ctx, probs[t], secs[t], res.data() + first[t], outs[t]);
         outs[t].n_unconverged = t == 0 ? n_unconv : 0;   // the batch's count, reported once
     }
+    HIP_OK(hipStreamSynchronize(s));
 }
 
 void svd_truncate_run(pdmrg_ctx *ctx, const Bond &bl, const Bond &br, const Phys &p, const double *psi, int max_m,
