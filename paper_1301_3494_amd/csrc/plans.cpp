@@ -83,17 +83,23 @@ double GemmList::operand_bytes() const {
     return b;
 }
 
-// Estimated time of an FP64 list under a register-direct shape, in flops of one
-// CU at full rate: the work (dimensions rounded up to the 32 that a wave's edge
-// tile keeps) spread over the chip at the shape's rate, plus the longest tile,
-// which the last CU to finish may have started last.
-double GemmList::cost_r64(TileShape ts, int parts) const {
-    // Relative rates, 64 x 64, 128 x 64, 64 x 128, 128 x 128: H_eff at m = 4000
-    // with 98 channels, stage 1 6.9, 5.9, 5.5, 5.1 ms, stage 3 9.6, 8.2, 6.6, 5.9.
-    static const double kRate[4] = {0.66, 0.77, 0.91, 1.0};
-    constexpr double kTileK = 48.0;      // start and end of a tile, in K units
-    constexpr double kPartial = 240.0;   // flops in the time of writing and reading a partial sum
-    const int bm = tile_bm(ts), bn = tile_bn(ts);
+// Estimated time of a list under a register-direct (FP64) or LDS-DMA (FP32,
+// BF16x3) shape, in flops of one CU at full rate: the work (dimensions rounded
+// up to the tile, register-direct ones to the 32 that a wave's edge tile keeps)
+// spread over the chip at the shape's rate, plus the longest tile, which the
+// last CU to finish may have started last.
+double GemmList::cost(TileShape ts, int parts) const {
+    // Relative rates.  Register-direct, 64 x 64, 128 x 64, 64 x 128, 128 x 128: H_eff
+    // at m = 4000 with 98 channels, stage 1 6.9, 5.9, 5.5, 5.1 ms, stage 3 9.6, 8.2,
+    // 6.6, 5.9.  LDS-DMA, 128 x 32, 64 x 64, 32 x 128: stage 1 of the tri 12 x 6
+    // lattice, m = 3000, BF16x3 0.465, 0.385, 0.371 ms, FP32 0.520, 0.489, 0.525.
+    static const double kReg[4] = {0.66, 0.77, 0.91, 1.0}, kSplit[3] = {0.80, 0.97, 1.0}, kF32[3] = {0.94, 1.0, 0.93};
+    constexpr double kTileK = 48.0;   // start and end of a tile, in K units
+    const bool reg = (kR64Shapes >> (int)ts) & 1u, split = !(shapes_allowed & kStagedShapes);
+    const double rate = reg ? kReg[(int)ts - (int)TileShape::T64x64_R]
+                            : (split ? kSplit : kF32)[(int)ts - (int)TileShape::T128x32_D];
+    const double partial = reg ? 240.0 : split ? 230.0 : 150.0;   // flops in the time of writing and reading a partial sum
+    const int bm = tile_bm(ts), bn = tile_bn(ts), rm = reg ? 32 : bm, rn = reg ? 32 : bn;
     int64_t kmax = 0;
     for (const GemmItem &it : items) kmax = std::max(kmax, item_k(*this, it));
     const double krange = std::max(1.0, (double)kmax / std::max(parts, 1));
@@ -101,12 +107,12 @@ double GemmList::cost_r64(TileShape ts, int parts) const {
     for (const GemmItem &it : items) {
         const int64_t k = item_k(*this, it);
         const double ip = split_parts(k, krange);
-        work += 2.0 * ((it.M + 31) / 32 * 32) * (double)((it.N + 31) / 32 * 32) * (k + ip * kTileK);
-        if (ip > 1.0) work += kPartial * it.M * (double)it.N * ip;
+        work += 2.0 * ((it.M + rm - 1) / rm * rm) * (double)((it.N + rn - 1) / rn * rn) * (k + ip * kTileK);
+        if (ip > 1.0) work += partial * it.M * (double)it.N * ip;
         // four times a wave's tile: its SIMD has a quarter of the CU's rate
         longest = std::max(longest, 8.0 * std::min(bm / 2, it.M) * (double)std::min(bn / 2, it.N) * (k / ip + kTileK));
     }
-    return (work / 256.0 + longest) / kRate[(int)ts - (int)TileShape::T64x64_R];
+    return (work / 256.0 + longest) / rate;
 }
 
 // Past 2 GB of operands (each item's counted once) FP64 lists stream from memory
@@ -115,34 +121,35 @@ double GemmList::cost_r64(TileShape ts, int parts) const {
 // or faster (24 x 8 cylinder, m = 2000, 0.4 GB, stage 1 0.148 ms against 0.160;
 // tri 12 x 6, m = 3000, 1 GB, 1.05 against 1.06), and its sums run over
 // ascending k.
+//
+// FP32 and BF16x3 take the LDS-DMA shape of least cost().
 void GemmList::pick_tile(double bytes) {
-    // Relative throughput per padded flop of each shape, from timings of the
-    // H_eff GEMMs of the 8 x 4 cylinder (m = 1024) on MI355X: shorter K steps
-    // (more resident workgroups) win on these short, ragged K loops, and the
-    // LDS-DMA shapes (FP32) ran 1.4-1.9x faster than their full-depth base
-    // shapes (stage 1: 64x64 51.6 -> 36.4 us, 128x32 56.8 -> 38.5 us,
-    // 32x128 70.6 -> 37.6 us).
-    static const double kRate[] = {1.0, 1.0, 0.8, 0.75, 1.1, 1.15, 1.05, 1.2, 1.45, 1.45, 1.2};
     double best = 0.0;
     bool have = false;
     streams = (shapes_allowed & kR64Shapes) && bytes > 2e9;
-    if (streams) {
-        for (int t = (int)TileShape::T64x64_R; t <= (int)TileShape::T128x128_R; ++t) {
-            const double cost = cost_r64((TileShape)t, 1);
-            if (!have || cost < best * 0.999) {
-                best = cost;
+    const unsigned modelled = streams ? kR64Shapes : elem_bytes == 4 ? shapes_allowed & kDmaShapes : 0u;
+    if (modelled) {
+        for (int t = 0; t < kNumShapes; ++t) {
+            if (!((modelled >> t) & 1u)) continue;
+            const double c = cost((TileShape)t, 1);
+            if (!have || c < best * 0.999) {
+                best = c;
                 shape = (TileShape)t;
                 have = true;
             }
         }
         return;
     }
-    // in FP64 the staged kernel measured faster than the LDS-DMA one (the
-    // autotuner still times both)
-    const unsigned shapes = elem_bytes == 8 ? shapes_allowed & kStagedShapes : shapes_allowed;
+    // The staged kernel (in FP64 it measured faster than the LDS-DMA one; the
+    // autotuner still times both): relative throughput per padded flop of each
+    // shape, from timings of the H_eff GEMMs of the 8 x 4 cylinder (m = 1024) on
+    // MI355X: shorter K steps (more resident workgroups) win on these short,
+    // ragged K loops.
+    static const double kRate[] = {1.0, 1.0, 0.8, 0.75, 1.1, 1.15, 1.05, 1.2};
+    const unsigned shapes = shapes_allowed & kStagedShapes;
     std::vector<int64_t> kof(items.size());
     for (size_t i = 0; i < items.size(); ++i) kof[i] = item_k(*this, items[i]);
-    for (int t = 0; t < (int)TileShape::T64x64_R; ++t) {
+    for (int t = 0; t < (int)TileShape::T128x32_D; ++t) {
         if (!(shapes & (1u << t))) continue;
         const TileShape ts = (TileShape)t;
         double cap = 0.0, padded = 0.0;   // tiles after the split-K the long items allow; MFMA work
@@ -731,11 +738,17 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
     lowp = prec != PDMRG_F64;
     TileShape shape = g3.shape;
     int parts = default_parts(shape);
-    if (g3.streams) {   // the split and the shape together
+    if (lowp || g3.streams) {
+        // The split and the shape together.  FP32 and BF16x3 split as far as K
+        // allows: stage 3 with its reduction at 2, 4, 8 parts takes 0.409, 0.415,
+        // 0.388 ms (BF16x3, tri 12 x 6, m = 3000), 0.126, 0.102, 0.096 (FP32, 24 x 8
+        // cylinder, m = 2000), 0.048, 0.036, 0.034 (BF16x3, 8 x 4, m = 1024).
+        const unsigned shapes = lowp ? kDmaShapes : kR64Shapes;
         double best = 0.0;
-        for (int p = 1; p <= kMaxParts64; ++p)
-            for (int t = (int)TileShape::T64x64_R; t <= (int)TileShape::T128x128_R; ++t) {
-                const double c = g3_base.cost_r64((TileShape)t, p);
+        for (int p = lowp ? 8 : 1; p <= (lowp ? 8 : kMaxParts64); ++p)
+            for (int t = 0; t < kNumShapes; ++t) {
+                if (!((shapes >> t) & 1u)) continue;
+                const double c = g3_base.cost((TileShape)t, p);
                 if (best == 0.0 || c < best * 0.999) best = c, parts = p, shape = (TileShape)t;
             }
     }

@@ -64,7 +64,7 @@ struct GemmList {
     double operand_bytes() const;
     bool streams = false;   // set by pick_tile(): the register-direct kernel
     // The time compared for its shapes, with the K split of split_k(parts).
-    double cost_r64(TileShape t, int parts) const;
+    double cost(TileShape t, int parts) const;
     int ntiles_for(TileShape t) const;
     // Build the tiles and place them for the launch (see place_tiles), upload:
     // build_tiles(), then stage() into a buffer of this list's own.  A plan
