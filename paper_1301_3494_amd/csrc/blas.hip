@@ -183,6 +183,111 @@ void launch_dot_reduce(const double *partial, const int32_t *t0, const int32_t *
                        out);
 }
 
+// Gradient: every Z block meets all the channels of R of its charge, so a
+// workgroup holds its chunk of Z in registers and streams the channels past it,
+// four at a time to cover the latency of their loads and of the reduction (24 x
+// 8 cylinder, m = 777: 2504 blocks of some 40 x 40 numbers, 22088 products; a
+// launch over the products read Z nine times and took 47 us, its host lists 170).
+constexpr int kGradBatch = 64;   // channels between barriers
+__global__ __launch_bounds__(256) void grad_dot_kernel(const double *__restrict__ a, const double *__restrict__ r,
+                                                       const GradDot *__restrict__ dots,
+                                                       const DotTile *__restrict__ tiles, int ntiles,
+                                                       const int64_t *__restrict__ r_off, double *__restrict__ partial) {
+    constexpr int U = kDotChunk / 256, J = 4;
+    __shared__ double red[4][kGradBatch];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const DotTile tl = tiles[t];
+        const GradDot d = dots[tl.task];
+        const int e0 = tl.chunk * kDotChunk + (int)threadIdx.x;
+        double va[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) va[u] = e0 + 256 * u < d.n ? a[d.a_off + e0 + 256 * u] : 0.0;
+        double *out = partial + d.part0 + (int64_t)tl.chunk * d.nch;
+        for (int c0 = 0; c0 < d.nch; c0 += kGradBatch) {
+            const int nc = min(kGradBatch, d.nch - c0);
+            for (int c = 0; c < nc; c += J) {
+                double acc[J];
+#pragma unroll
+                for (int j = 0; j < J; ++j) {   // past the last channel: the last one again
+                    const double *b = r + r_off[d.list0 + c0 + min(c + j, nc - 1)];
+                    double vb[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) vb[u] = e0 + 256 * u < d.n ? b[e0 + 256 * u] : 0.0;
+                    acc[j] = 0.0;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) acc[j] += va[u] * vb[u];
+                }
+#pragma unroll
+                for (int w = 32; w > 0; w >>= 1)
+#pragma unroll
+                    for (int j = 0; j < J; ++j) acc[j] += __shfl_down(acc[j], w);
+                if (lane == 0)
+#pragma unroll
+                    for (int j = 0; j < J; ++j)
+                        if (c + j < nc) red[wave][c + j] = acc[j];
+            }
+            __syncthreads();
+            if ((int)threadIdx.x < nc)
+                out[c0 + threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+            __syncthreads();   // red is rewritten by the next batch or tile
+        }
+    }
+}
+
+// A wave per group of output entries, lane = entry: the records of 16 dots at a
+// time through LDS, so that the loads of a lane's sums do not wait for them.
+__global__ __launch_bounds__(64) void grad_sum_kernel(const double *__restrict__ partial, const GradDot *__restrict__ dots,
+                                                      const int32_t *__restrict__ order,
+                                                      const GradSum *__restrict__ sums, int nsums,
+                                                      const int32_t *__restrict__ pos, int width, double *__restrict__ out) {
+    constexpr int kStage = 16;
+    __shared__ GradDot sd[kStage];
+    for (int k = blockIdx.x; k < nsums; k += gridDim.x) {
+        const GradSum s = sums[k];
+        for (int w0 = 0; w0 < width; w0 += 64) {
+            const int w = w0 + (int)threadIdx.x;
+            double acc = 0.0;
+            bool any = false;
+            for (int t0 = s.t0; t0 < s.t1; t0 += kStage) {
+                const int nt = min(kStage, s.t1 - t0);
+                __syncthreads();
+                if ((int)threadIdx.x < nt) sd[threadIdx.x] = dots[order[t0 + threadIdx.x]];
+                __syncthreads();
+                int c[kStage];
+                double v[kStage];
+#pragma unroll
+                for (int t = 0; t < kStage; ++t) c[t] = t < nt && w < width ? pos[sd[t].pos + w] : -1;
+#pragma unroll
+                for (int t = 0; t < kStage; ++t) v[t] = c[t] >= 0 ? partial[sd[t].part0 + c[t]] : 0.0;
+#pragma unroll
+                for (int t = 0; t < kStage; ++t)
+                    if (c[t] >= 0) {
+                        any = true;
+                        acc += v[t];
+                        const int nx = (sd[t].n + kDotChunk - 1) / kDotChunk;
+                        for (int x = 1; x < nx; ++x) acc += partial[sd[t].part0 + (int64_t)x * sd[t].nch + c[t]];
+                    }
+            }
+            if (any) out[s.g0 + w] = acc;
+        }
+    }
+}
+
+void launch_grad_dots(const double *a, const double *r, const GradDot *dots, const DotTile *tiles, int ntiles,
+                      const int64_t *r_off, double *partial, hipStream_t s) {
+    if (ntiles <= 0) return;
+    const unsigned g = (unsigned)std::min<int64_t>(ntiles, kMaxGrid);
+    hipLaunchKernelGGL(grad_dot_kernel, dim3(g), dim3(256), 0, s, a, r, dots, tiles, ntiles, r_off, partial);
+}
+
+void launch_grad_sums(const double *partial, const GradDot *dots, const int32_t *order, const GradSum *sums, int nsums,
+                      const int32_t *pos, int width, double *out, hipStream_t s) {
+    if (nsums <= 0) return;
+    hipLaunchKernelGGL(grad_sum_kernel, dim3((unsigned)std::min<int64_t>(nsums, kMaxGrid)), dim3(64), 0, s, partial, dots,
+                       order, sums, nsums, pos, width, out);
+}
+
 // ------------------------------------------------------------ diag(H_eff)
 __global__ __launch_bounds__(256) void diag_kernel(Slots slots, const DiagTerm *__restrict__ terms,
                                                    const int32_t *__restrict__ groups) {

@@ -100,6 +100,19 @@ struct DotTile {
     int32_t task, chunk;
 };
 
+// Frobenius products of one packed block (n elements at a_off) with several
+// others: channels c = 0 .. nch - 1 at r_off[list0 + c].  The sum over chunk x
+// (kDotChunk elements) with channel c is partial[part0 + x * nch + c]; pos is
+// the row of the position table for this list of channels.
+struct GradDot {
+    int64_t a_off, part0;
+    int32_t n, list0, nch, pos;
+};
+// Output entries g0 .. g0 + width - 1: sums over the dots order[t0 .. t1 - 1].
+struct GradSum {
+    int32_t t0, t1, g0, pad_;
+};
+
 enum class GemmPrec { F64, F32, BF16X3 };
 
 // Output tile shapes of the FP64 / FP32 kernels (4 waves).  0-7: the register-
@@ -175,6 +188,12 @@ void launch_dot_partials(const Slots &slots, int a_slot, int b_slot, const DotTa
                          int ntiles, double *partial, hipStream_t s);
 // out[g_of[k]] = sum over tiles t0[k]..t0[k+1] of partial (in order), for the
 // k = 0..ngroups-1 output entries that have tiles.
+void launch_grad_dots(const double *a, const double *r, const GradDot *dots, const DotTile *tiles, int ntiles,
+                      const int64_t *r_off, double *partial, hipStream_t s);
+// out[g0 + w] = sum over the dots whose list has channel w (at pos[dot.pos + w] >= 0),
+// in order, left alone if there is none.
+void launch_grad_sums(const double *partial, const GradDot *dots, const int32_t *order, const GradSum *sums, int nsums,
+                      const int32_t *pos, int width, double *out, hipStream_t s);
 void launch_dot_reduce(const double *partial, const int32_t *t0, const int32_t *g_of, int ngroups, double *out,
                        hipStream_t s);
 void launch_convert_f64_f32(const double *x, float *y, int64_t n, hipStream_t s);

@@ -149,16 +149,22 @@ void GemmList::pick_tile(double bytes) {
     const unsigned shapes = shapes_allowed & kStagedShapes;
     std::vector<int64_t> kof(items.size());
     for (size_t i = 0; i < items.size(); ++i) kof[i] = item_k(*this, items[i]);
+    double caps[4] = {-1.0, -1.0, -1.0, -1.0}, pads[4] = {};
     for (int t = 0; t < (int)TileShape::T128x32_D; ++t) {
         if (!(shapes & (1u << t))) continue;
         const TileShape ts = (TileShape)t;
-        double cap = 0.0, padded = 0.0;   // tiles after the split-K the long items allow; MFMA work
         const int bm = tile_bm(ts), bn = tile_bn(ts);
-        for (size_t i = 0; i < items.size(); ++i) {
-            const GemmItem &it = items[i];
-            const int tm = (it.M + bm - 1) / bm, tn = (it.N + bn - 1) / bn;
-            cap += tm * (double)tn * std::max<int64_t>(1, std::min<int64_t>(8, kof[i] / 256));
-            padded += 2.0 * (tm * bm) * (double)(tn * bn) * (double)kof[i];
+        // tiles after the split-K the long items allow, and MFMA work: the same for
+        // the depth variants (4, 6 and 5, 7) of 64 x 64 and 128 x 32
+        double &cap = caps[t < 4 ? t : t & 1], &padded = pads[t < 4 ? t : t & 1];
+        if (cap < 0.0) {
+            const int lm = __builtin_ctz(bm), ln = __builtin_ctz(bn);
+            cap = padded = 0.0;
+            for (size_t i = 0; i < items.size(); ++i) {
+                const int tm = (items[i].M + bm - 1) >> lm, tn = (items[i].N + bn - 1) >> ln;
+                cap += tm * (double)tn * std::max<int64_t>(1, std::min<int64_t>(8, kof[i] / 256));
+                padded += 2.0 * (tm * bm) * (double)(tn * bn) * (double)kof[i];
+            }
         }
         const double fill = std::min(1.0, cap / 1024.0);
         const double cost = padded / (kRate[t] * std::max(fill, 1e-3));
@@ -1046,10 +1052,12 @@ void GradPlan::run(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSi
         gz.stage(st);
         st.add(d_dots, dots);
         st.add(d_dtiles, dtiles);
-        st.add(d_t0, t0);
-        st.add(d_gof, g_of);
+        st.add(d_roff, r_off);
+        st.add(d_pos, pos);
+        st.add(d_order, order);
+        st.add(d_sums, sums);
         st.flush(d_lists, s);
-        ws2.ensure((std::max<size_t>(nZ, 1) + std::max<size_t>(dtiles.size(), 1)) * sizeof(double));
+        ws2.ensure((std::max<size_t>(nZ, 1) + std::max<size_t>(npartial, 1)) * sizeof(double));
     } catch (...) {
         (void)hipStreamSynchronize(s);   // nothing left running on the caller's buffers
         throw;
@@ -1057,8 +1065,8 @@ void GradPlan::run(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSi
     double *partial = ws2.as<double>() + std::max<int64_t>(nZ, 1);
     sl.p[4] = ws2.ptr;
     gz.launch(GemmPrec::F64, true, sl, s);
-    launch_dot_partials(sl, 4, 2, d_dots, d_dtiles, (int)dtiles.size(), partial, s);
-    launch_dot_reduce(partial, d_t0, d_gof, (int)g_of.size(), G, s);
+    launch_grad_dots(ws2.as<double>(), R, d_dots, d_dtiles, (int)dtiles.size(), d_roff, partial, s);
+    launch_grad_sums(partial, d_dots, d_order, d_sums, (int)sums.size(), d_pos, Dr, G, s);
 }
 
 // stage 2: Z blocks [b'][b] = U1^T psi, then stage-3 dot tasks
@@ -1067,10 +1075,28 @@ void GradPlan::rest(const MpoSite &W, const std::vector<int64_t> &u1base) {
     gz = GemmList();
     gz.ta = true;
     dots.clear();
-    nZ = 0;
-    std::map<int, std::vector<int>> channels;   // of R, by charge
-    for (int w2 = 0; w2 < Dr; ++w2) channels[W.dr[w2]].push_back(w2);
-    std::vector<int> wr;
+    dtiles.clear();
+    r_off.clear();
+    pos.clear();
+    sums.clear();
+    nZ = npartial = 0;
+    std::vector<int> charge;                  // of the channels of R, each once
+    std::vector<std::vector<int>> channels;   // with that charge, ascending
+    for (int w2 = 0; w2 < Dr; ++w2) {
+        const size_t c = std::find(charge.begin(), charge.end(), W.dr[w2]) - charge.begin();
+        if (c == charge.size()) {
+            charge.push_back(W.dr[w2]);
+            channels.emplace_back();
+        }
+        channels[c].push_back(w2);
+    }
+    struct List {
+        int list0 = -1, nch = 0, pos = 0;
+    };
+    std::vector<List> lists((size_t)br.nsec() * charge.size());   // by sector of R and charge
+    std::vector<int> group;                                       // (w, s, t) of each dot
+    dots.reserve((size_t)nl * Dl * d * d);
+    group.reserve(dots.capacity());
     for (int i = 0; i < nl; ++i)
         for (int w = 0; w < Dl; ++w) {
             const int j = bl.find(bl.q[i] - W.dl[w]);
@@ -1087,49 +1113,48 @@ void GradPlan::rest(const MpoSite &W, const std::vector<int64_t> &u1base) {
                     if (ct < 0) continue;
                     const int qbk = bl.q[j] + p.q[t];
                     // channels w' of R with delta = qb - qbk
-                    const auto ch = channels.find(qb - qbk);
-                    if (ch == channels.end()) continue;
-                    wr.clear();
-                    for (int w2 : ch->second)
-                        if (Rt.rowo[(size_t)kb * Dr + w2] >= 0) wr.push_back(w2);
-                    if (wr.empty()) continue;
+                    const size_t ch = std::find(charge.begin(), charge.end(), qb - qbk) - charge.begin();
+                    if (ch == charge.size()) continue;
                     const int M = br.dim_of(qbk), N = br.dim[kb], K = bl.dim[i];
+                    List &ls = lists[kb * charge.size() + ch];
+                    if (ls.list0 < 0) {
+                        ls.list0 = (int)r_off.size();
+                        ls.pos = (int)pos.size();
+                        pos.resize(pos.size() + Dr, -1);
+                        for (int w2 : channels[ch]) {
+                            const int ro = Rt.rowo[(size_t)kb * Dr + w2];
+                            if (ro < 0) continue;
+                            pos[ls.pos + w2] = (int)r_off.size() - ls.list0;
+                            r_off.push_back(Rt.base[kb] + (int64_t)ro * N);
+                            PD_REQUIRE(r_off.back() >= 0 && r_off.back() + (int64_t)M * N <= Rt.size, PDMRG_ESHAPE,
+                                       "grad: channel outside its buffer");
+                        }
+                        ls.nch = (int)r_off.size() - ls.list0;
+                    }
+                    if (ls.nch == 0) continue;
                     gz.add_item(4, nZ, M, N, N);
                     gz.add_seg(3, u1base[j] + (int64_t)lro * S.cols[j] + ct, S.cols[j], 1, S.base[i] + cs, S.cols[i],
                                K);
-                    for (int w2 : wr) {
-                        const int64_t roff = Rt.base[kb] + (int64_t)Rt.rowo[(size_t)kb * Dr + w2] * br.dim[kb];
-                        const int g = ((w * d + sp) * d + t) * Dr + w2;
-                        dots.push_back(DotTask{nZ, roff, M * N, g});
-                    }
+                    PD_REQUIRE(M > 0 && N > 0, PDMRG_ESHAPE, "grad: empty block");
+                    const int nx = (M * N + kDotChunk - 1) / kDotChunk;
+                    for (int x = 0; x < nx; ++x) dtiles.push_back(DotTile{(int)dots.size(), x});
+                    dots.push_back(GradDot{nZ, npartial, M * N, ls.list0, ls.nch, ls.pos});
+                    group.push_back((w * d + sp) * d + t);
+                    flops += 2.0 * M * N * ls.nch;
+                    npartial += (int64_t)nx * ls.nch;
                     nZ += (int64_t)M * N;
                 }
             }
         }
-    // dot tiles grouped by output entry, tasks of one entry in build order (a
-    // counting sort: the entries are indices of the gradient)
-    std::vector<int> order(dots.size()), first((size_t)Dl * d * d * Dr + 1, 0);
-    for (const DotTask &dt : dots) ++first[(size_t)dt.g + 1];
-    for (size_t k = 1; k < first.size(); ++k) first[k] += first[k - 1];
-    for (size_t k = 0; k < dots.size(); ++k) order[first[dots[k].g]++] = (int)k;
-    dtiles.clear();
-    t0.clear();
-    g_of.clear();
-    for (size_t k = 0; k < order.size(); ++k) {
-        const DotTask &dt = dots[order[k]];
-        PD_REQUIRE(dt.n > 0, PDMRG_ESHAPE, "grad: empty block");
-        if (g_of.empty() || g_of.back() != dt.g) {
-            t0.push_back((int32_t)dtiles.size());
-            g_of.push_back(dt.g);
-        }
-        for (int c = 0; c * kDotChunk < dt.n; ++c) dtiles.push_back(DotTile{order[k], c});
+    // dots by output entry, those of one entry in build order (a counting sort)
+    order.resize(dots.size());
+    std::vector<int> first((size_t)Dl * d * d + 1, 0);
+    for (int g : group) ++first[(size_t)g + 1];
+    for (size_t g = 0; g + 1 < first.size(); ++g) {
+        if (first[g + 1] > 0) sums.push_back(GradSum{first[g], first[g] + first[g + 1], (int)g * Dr, 0});
+        first[g + 1] += first[g];
     }
-    t0.push_back((int32_t)dtiles.size());
-    for (const DotTask &dt : dots) {
-        PD_REQUIRE(dt.a_off >= 0 && dt.a_off + dt.n <= nZ && dt.b_off >= 0 && dt.b_off + dt.n <= Rt.size,
-                   PDMRG_ESHAPE, "grad: dot task outside its buffer");
-        flops += 2.0 * dt.n;
-    }
+    for (size_t k = 0; k < dots.size(); ++k) order[first[group[k]]++] = (int)k;
     flops += g1.flops + gz.flops;
     gz.validate({Lt.size, S.size, Rt.size, nU1, nZ});
     gz.pick_tile();

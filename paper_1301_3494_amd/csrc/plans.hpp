@@ -211,13 +211,19 @@ struct GradPlan {
     EnvLayout Lt, Rt;
     int64_t nU1 = 0, nZ = 0;
     GemmList g1, gz;
-    std::vector<DotTask> dots;
+    std::vector<GradDot> dots;       // one per Z block
     std::vector<DotTile> dtiles;
-    std::vector<int32_t> t0, g_of;   // tiles of output entry g_of[k]: t0[k] .. t0[k+1]
+    std::vector<int64_t> r_off;      // the channels of R that meet a block, by list
+    std::vector<int32_t> pos;        // per list: place of channel w' in it, or -1
+    std::vector<int32_t> order;      // dots by (w, s, t)
+    std::vector<GradSum> sums;
+    int64_t npartial = 0;
     ListBuf d_lists1, d_lists;
-    const DotTask *d_dots = nullptr;
+    const GradDot *d_dots = nullptr;
     const DotTile *d_dtiles = nullptr;
-    const int32_t *d_t0 = nullptr, *d_gof = nullptr;
+    const int64_t *d_roff = nullptr;
+    const int32_t *d_pos = nullptr, *d_order = nullptr;
+    const GradSum *d_sums = nullptr;
     double flops = 0.0;
     // Uploads and launches stage 1 and, while it runs, builds the rest; ws is
     // workspace for U1, ws2 for Z and the partial sums; G (Dl d d Dr) is overwritten.
