@@ -23,6 +23,9 @@
 // that every XCD (b % 8) receives an even share of the work and the tiles
 // that share an A panel share one XCD's L2.
 #include "kernels.hpp"
+#include "split.hpp"
+
+#include <type_traits>
 
 namespace pdmrg {
 
@@ -68,6 +71,62 @@ __device__ __forceinline__ int64_t c_row(const GemmItem &it, const int64_t *__re
     return it.rmap >= 0 ? rowoff[it.rmap + r] : (int64_t)r * it.ldc;
 }
 
+// Output of a tile of H_eff's stage 1 (EpiDev): its blocks that the W stage
+// would only scale and copy go to T2 from here, and to T1 only if another sum
+// reads them.  The W stage, at the rate of a copy, loses most of its traffic for
+// a look-up a channel here.  W stage and stage 1: 8 x 4 cylinder, m = 1024, 30 ->
+// 19 us and 77 -> 81; 24 x 8 FP32, m = 2000, 44 -> 19 and 101 -> 106; tri 12 x 6
+// BF16x3, m = 3000, 126 -> 58 and 387 -> 409; 98 channels, m = 4000, 1.61 -> 0.54 ms
+// and 5.30 -> 5.51.
+// NC columns of a lane (those below N), its rows in ascending order.
+template <int NC, typename TD>
+struct EpiWriter {
+    const int32_t *row;   // of the channel at hand: its first row, the next one's
+    const EpiDst *dst;
+    TD *out;
+    int seg[NC], b[NC], start, end, nseg;
+    EpiDst e[NC];
+    // row0, dst0: those of the channel that holds the tile's first row
+    __device__ __forceinline__ EpiWriter(void *out_, const int32_t *row0, const int32_t *col, const EpiDst *dst0, int nseg_,
+                                         const int (&gn)[NC], int N)
+        : row(row0), dst(dst0), out(static_cast<TD *>(out_)), nseg(nseg_) {
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            int s = 0;
+            if (gn[j] < N)
+                while (gn[j] >= col[s + 1]) ++s;
+            seg[j] = s;
+            b[j] = gn[j] - col[s];
+        }
+        fetch();
+    }
+    __device__ __forceinline__ void fetch() {
+        start = row[0];
+        end = row[1];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) e[j] = dst[seg[j]];
+    }
+    __device__ __forceinline__ void seek(int gm) {
+        if (gm < end) return;
+        do {
+            ++row;
+            dst += nseg;
+        } while (gm >= row[1]);
+        fetch();
+    }
+    // v at row gm (after seek), column j
+    template <typename T, typename TC>
+    __device__ __forceinline__ void store(int gm, int j, T v, TC *c) const {
+        if (e[j].keep) *c = (TC)v;
+        if (e[j].off >= 0) {
+            const T w = T(0) + (T)e[j].coef * v;   // as a sum of one term
+            TD *o = out + e[j].off + (int64_t)(gm - start) * e[j].ld + b[j];
+            if constexpr (std::is_same<TD, uint32_t>::value) *o = pack_split(w);
+            else *o = (TD)w;
+        }
+    }
+};
+
 // ---------------------------------------------------------------- FP64 / FP32
 // LDS tiles are M-major (A) / N-major (B) with the K index contiguous and an
 // odd row stride (BK + 1 elements), so the global->LDS stores of either
@@ -78,12 +137,15 @@ template <typename T> struct KStep;
 template <> struct KStep<double> { static constexpr int BK = 16; };
 template <> struct KStep<float> { static constexpr int BK = 32; };
 
-// KDIV = 2 / 4: a half / quarter of the K step (and LDS) of KStep.
-template <typename T, typename TC, bool TA, bool TB, int BM, int BN, int WGM, int KDIV>
-__global__ __launch_bounds__(NT) void gemm_kmajor(Slots slots, const GemmItem *__restrict__ items,
+// KDIV = 2 / 4: a half / quarter of the K step (and LDS) of KStep.  EPI: output
+// through EpiWriter, in a kernel of its own so that plain lists keep their
+// registers, and held to those of 6 waves a SIMD (4 without the bound: stage 1 of
+// the 8 x 4 cylinder 95 us instead of 81).
+template <typename T, typename TC, bool TA, bool TB, int BM, int BN, int WGM, int KDIV, bool EPI>
+__global__ __launch_bounds__(NT, EPI && KDIV > 1 ? 6 : 1) void gemm_kmajor(Slots slots, const GemmItem *__restrict__ items,
                                                   const GemmSeg *__restrict__ segs,
                                                   const GemmTile *__restrict__ tiles,
-                                                  const int64_t *__restrict__ rowoff, int ntiles) {
+                                                  const int64_t *__restrict__ rowoff, int ntiles, EpiDev epi) {
     constexpr int WGN = 4 / WGM;
     constexpr int BK = KStep<T>::BK / KDIV, LDK = BK + 1;
     constexpr int NLA = BM * BK / NT, NLB = BN * BK / NT;   // elements per thread and step
@@ -206,6 +268,26 @@ __global__ __launch_bounds__(NT) void gemm_kmajor(Slots slots, const GemmItem *_
     // 4 r + lane/16, v_mfma_f32_16x16x4 row 4 (lane/16) + r; column lane % 16.
     constexpr bool kF64 = sizeof(T) == 8;
     TC *C = static_cast<TC *>(const_cast<void *>(slots.p[it.c_slot])) + it.c_off;
+    if constexpr (EPI) {
+        const EpiItem ei = epi.items[tile.item];
+        int gn[WBN];
+#pragma unroll
+        for (int j = 0; j < WBN; ++j) gn[j] = n0 + wn + j * 16 + (lane & 15);
+        EpiWriter<WBN, T> ew(const_cast<void *>(slots.p[epi.slot]), epi.row + ei.row0 + tile.chan, epi.col + ei.col0,
+                             epi.dst + ei.dst0 + tile.chan * ei.nseg, ei.nseg, gn, it.N);
+#pragma unroll
+        for (int i = 0; i < WBM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = m0 + wm + i * 16 + (kF64 ? r * 4 + (lane >> 4) : (lane >> 4) * 4 + r);
+                if (gm >= it.M) continue;
+                ew.seek(gm);
+#pragma unroll
+                for (int j = 0; j < WBN; ++j)
+                    if (gn[j] < it.N) ew.store(gm, j, acc[i][j][r], C + (int64_t)gm * it.ldc + gn[j]);
+            }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < WBM; ++i)
 #pragma unroll
@@ -296,7 +378,7 @@ __device__ __forceinline__ s4v split_lo(float w0, float w1, float w2, float w3) 
 
 template <typename T, typename TC, int BM, int BN, int WGM, int NS, bool SPLIT = false>
 __global__ __launch_bounds__(NT) void gemm_dma(Slots slots, const FlatTile *__restrict__ tiles,
-                                               const int64_t *__restrict__ rowoff, int ntiles) {
+                                               const int64_t *__restrict__ rowoff, int ntiles, EpiDev epi) {
     constexpr int BK = 16;
     constexpr int EW = sizeof(T) / 4;                            // dwords per element
     constexpr int RG = 4 / EW;                                   // rows per A load group (64 dwords)
@@ -453,6 +535,26 @@ __global__ __launch_bounds__(NT) void gemm_dma(Slots slots, const FlatTile *__re
     // 4 r + lane/16, v_mfma_f32_16x16x4 and v_mfma_f32_16x16x16_bf16 row
     // 4 (lane/16) + r; column lane % 16
     TC *C = static_cast<TC *>(const_cast<void *>(slots.p[ft.c_slot])) + ft.c_off;
+    if (epi.items) {
+        using TD = typename std::conditional<SPLIT, uint32_t, T>::type;
+        int gn[WBN];
+#pragma unroll
+        for (int j = 0; j < WBN; ++j) gn[j] = n0 + wn + j * 16 + c;
+        EpiWriter<WBN, TD> ew(const_cast<void *>(slots.p[epi.slot]), epi.row + ft.erow, epi.col + ft.ecol,
+                              epi.dst + ft.edst, ft.eseg, gn, N);
+#pragma unroll
+        for (int i = 0; i < WBM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = m0 + wm + i * 16 + (EW == 2 ? r * 4 + (lane >> 4) : (lane >> 4) * 4 + r);
+                if (gm >= M) continue;
+                ew.seek(gm);
+#pragma unroll
+                for (int j = 0; j < WBN; ++j)
+                    if (gn[j] < N) ew.store(gm, j, acc[i][j][r], C + (int64_t)gm * ft.ldc + gn[j]);
+            }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < WBM; ++i)
 #pragma unroll
@@ -562,7 +664,7 @@ struct Frag64 {
 // One wave's tile of WM x WN blocks at (m0, n0).
 template <int WM, int WN, int NS>
 __device__ __forceinline__ void r64_tile(const Slots &slots, const FlatTile &ft, const int64_t *__restrict__ rowoff,
-                                         int m0, int n0, int r16, int g) {
+                                         const EpiDev &epi, int m0, int n0, int r16, int g) {
     d4 acc[WM][WN];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -634,6 +736,25 @@ __device__ __forceinline__ void r64_tile(const Slots &slots, const FlatTile &ft,
     }
     // v_mfma_f64_16x16x4 result: register r of lane l is row 4 r + l / 16, column l % 16
     double *C = static_cast<double *>(const_cast<void *>(slots.p[ft.c_slot])) + ft.c_off;
+    if (epi.items) {
+        int gn[WN];
+#pragma unroll
+        for (int q = 0; q < WN; ++q) gn[q] = n0 + FB::row(q, r16);
+        EpiWriter<WN, double> ew(const_cast<void *>(slots.p[epi.slot]), epi.row + ft.erow, epi.col + ft.ecol,
+                                 epi.dst + ft.edst, ft.eseg, gn, ft.N);
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = m0 + FA::row(i, 4 * r + g);
+                if (gm >= ft.M) continue;
+                ew.seek(gm);
+#pragma unroll
+                for (int q = 0; q < WN; ++q)
+                    if (gn[q] < ft.N) ew.store(gm, q, acc[i][q][r], C + (int64_t)gm * ft.ldc + gn[q]);
+            }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -653,7 +774,7 @@ __device__ __forceinline__ void r64_tile(const Slots &slots, const FlatTile &ft,
 // tile) that lie wholly outside.
 template <int WM, int WN, int NS, int WPE>
 __global__ __launch_bounds__(NT, WPE) void gemm_r64(Slots slots, const FlatTile *__restrict__ tiles,
-                                                    const int64_t *__restrict__ rowoff, int ntiles) {
+                                                    const int64_t *__restrict__ rowoff, int ntiles, EpiDev epi) {
     if ((int)blockIdx.x >= ntiles) return;
     const FlatTile ft = tiles[blockIdx.x];
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
@@ -662,31 +783,31 @@ __global__ __launch_bounds__(NT, WPE) void gemm_r64(Slots slots, const FlatTile 
     if (m0 >= ft.M || n0 >= ft.N) return;   // also an idle tile (M = 0)
     if constexpr (WN == 4)
         if (n0 + 32 >= ft.N) {
-            r64_tile<WM, 2, NS>(slots, ft, rowoff, m0, n0, r16, g);
+            r64_tile<WM, 2, NS>(slots, ft, rowoff, epi, m0, n0, r16, g);
             return;
         }
     if constexpr (WM == 4)
         if (m0 + 32 >= ft.M) {
-            r64_tile<2, WN, NS>(slots, ft, rowoff, m0, n0, r16, g);
+            r64_tile<2, WN, NS>(slots, ft, rowoff, epi, m0, n0, r16, g);
             return;
         }
-    r64_tile<WM, WN, NS>(slots, ft, rowoff, m0, n0, r16, g);
+    r64_tile<WM, WN, NS>(slots, ft, rowoff, epi, m0, n0, r16, g);
 }
 
 template <int WM, int WN, int NS, int WPE>
-static void dispatch_r64(dim3 g, hipStream_t s, const Slots &sl, const FlatTile *t, const int64_t *ro, int n) {
-    hipLaunchKernelGGL((gemm_r64<WM, WN, NS, WPE>), g, dim3(NT), 0, s, sl, t, ro, n);
+static void dispatch_r64(dim3 g, hipStream_t s, const Slots &sl, const FlatTile *t, const int64_t *ro, const EpiDev &ep, int n) {
+    hipLaunchKernelGGL((gemm_r64<WM, WN, NS, WPE>), g, dim3(NT), 0, s, sl, t, ro, n, ep);
 }
 
-void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff, int ntiles,
-                     hipStream_t s) {
+void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff,
+                     const EpiDev &epi, int ntiles, hipStream_t s) {
     if (ntiles <= 0) return;
     const dim3 g(ntiles);
     switch (shape) {
-        case TileShape::T64x64_R: dispatch_r64<2, 2, 3, 4>(g, s, slots, tiles, rowoff, ntiles); break;
-        case TileShape::T128x64_R: dispatch_r64<4, 2, 2, 3>(g, s, slots, tiles, rowoff, ntiles); break;
-        case TileShape::T64x128_R: dispatch_r64<2, 4, 2, 3>(g, s, slots, tiles, rowoff, ntiles); break;
-        case TileShape::T128x128_R: dispatch_r64<4, 4, 2, 2>(g, s, slots, tiles, rowoff, ntiles); break;
+        case TileShape::T64x64_R: dispatch_r64<2, 2, 3, 4>(g, s, slots, tiles, rowoff, epi, ntiles); break;
+        case TileShape::T128x64_R: dispatch_r64<4, 2, 2, 3>(g, s, slots, tiles, rowoff, epi, ntiles); break;
+        case TileShape::T64x128_R: dispatch_r64<2, 4, 2, 3>(g, s, slots, tiles, rowoff, epi, ntiles); break;
+        case TileShape::T128x128_R: dispatch_r64<4, 4, 2, 2>(g, s, slots, tiles, rowoff, epi, ntiles); break;
         default: break;
     }
 }
@@ -697,19 +818,22 @@ struct GemmArgs {
     const GemmSeg *sg;
     const GemmTile *tl;
     const int64_t *ro;
+    EpiDev ep;
     int n;
 };
 
 template <typename T, typename TC, int BM, int BN, int WGM, int KDIV>
 static void dispatch_shape(bool ta, bool tb, dim3 g, hipStream_t s, const GemmArgs &a) {
-    if (!ta && !tb)
-        hipLaunchKernelGGL((gemm_kmajor<T, TC, false, false, BM, BN, WGM, KDIV>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n);
+    if (a.ep.items)   // H_eff: not transposed
+        hipLaunchKernelGGL((gemm_kmajor<T, TC, false, false, BM, BN, WGM, KDIV, true>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n, a.ep);
+    else if (!ta && !tb)
+        hipLaunchKernelGGL((gemm_kmajor<T, TC, false, false, BM, BN, WGM, KDIV, false>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n, a.ep);
     else if (ta && !tb)
-        hipLaunchKernelGGL((gemm_kmajor<T, TC, true, false, BM, BN, WGM, KDIV>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n);
+        hipLaunchKernelGGL((gemm_kmajor<T, TC, true, false, BM, BN, WGM, KDIV, false>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n, a.ep);
     else if (!ta && tb)
-        hipLaunchKernelGGL((gemm_kmajor<T, TC, false, true, BM, BN, WGM, KDIV>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n);
+        hipLaunchKernelGGL((gemm_kmajor<T, TC, false, true, BM, BN, WGM, KDIV, false>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n, a.ep);
     else
-        hipLaunchKernelGGL((gemm_kmajor<T, TC, true, true, BM, BN, WGM, KDIV>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n);
+        hipLaunchKernelGGL((gemm_kmajor<T, TC, true, true, BM, BN, WGM, KDIV, false>), g, dim3(NT), 0, s, a.sl, a.it, a.sg, a.tl, a.ro, a.n, a.ep);
 }
 
 // Pipeline depth of the LDS-DMA kernel: two stages (loads one K step ahead)
@@ -717,16 +841,17 @@ static void dispatch_shape(bool ta, bool tb, dim3 g, hipStream_t s, const GemmAr
 // the H_eff GEMMs than three or four stages at lower occupancy.
 constexpr int kDmaStages = 2;
 template <typename T, typename TC, int BM, int BN, int WGM, bool SPLIT>
-static void dispatch_dma(dim3 g, hipStream_t s, const Slots &sl, const FlatTile *t, const int64_t *ro, int n) {
-    hipLaunchKernelGGL((gemm_dma<T, TC, BM, BN, WGM, kDmaStages, SPLIT>), g, dim3(NT), 0, s, sl, t, ro, n);
+static void dispatch_dma(dim3 g, hipStream_t s, const Slots &sl, const FlatTile *t, const int64_t *ro, const EpiDev &ep,
+                         int n) {
+    hipLaunchKernelGGL((gemm_dma<T, TC, BM, BN, WGM, kDmaStages, SPLIT>), g, dim3(NT), 0, s, sl, t, ro, n, ep);
 }
 template <typename T, typename TC, bool SPLIT = false>
 static void dispatch_dma_shape(TileShape shape, dim3 g, hipStream_t s, const Slots &sl, const FlatTile *t,
-                               const int64_t *ro, int n) {
+                               const int64_t *ro, const EpiDev &ep, int n) {
     switch (shape) {
-        case TileShape::T128x32_D: dispatch_dma<T, TC, 128, 32, 4, SPLIT>(g, s, sl, t, ro, n); break;
-        case TileShape::T64x64_D: dispatch_dma<T, TC, 64, 64, 2, SPLIT>(g, s, sl, t, ro, n); break;
-        case TileShape::T32x128_D: dispatch_dma<T, TC, 32, 128, 1, SPLIT>(g, s, sl, t, ro, n); break;
+        case TileShape::T128x32_D: dispatch_dma<T, TC, 128, 32, 4, SPLIT>(g, s, sl, t, ro, ep, n); break;
+        case TileShape::T64x64_D: dispatch_dma<T, TC, 64, 64, 2, SPLIT>(g, s, sl, t, ro, ep, n); break;
+        case TileShape::T32x128_D: dispatch_dma<T, TC, 32, 128, 1, SPLIT>(g, s, sl, t, ro, ep, n); break;
         default: break;
     }
 }
@@ -757,23 +882,23 @@ static void dispatch_kmajor(TileShape shape, bool ta, bool tb, dim3 g, hipStream
 }
 
 void launch_gemm_flat(GemmPrec prec, TileShape shape, bool c_is_f64, const Slots &slots, const FlatTile *tiles,
-                      const int64_t *rowoff, int ntiles, hipStream_t s) {
+                      const int64_t *rowoff, const EpiDev &epi, int ntiles, hipStream_t s) {
     if (ntiles <= 0) return;
     const dim3 g(ntiles);
-    if (prec == GemmPrec::F64) dispatch_dma_shape<double, double>(shape, g, s, slots, tiles, rowoff, ntiles);
+    if (prec == GemmPrec::F64) dispatch_dma_shape<double, double>(shape, g, s, slots, tiles, rowoff, epi, ntiles);
     else if (prec == GemmPrec::BF16X3 && c_is_f64)
-        dispatch_dma_shape<float, double, true>(shape, g, s, slots, tiles, rowoff, ntiles);
-    else if (prec == GemmPrec::BF16X3) dispatch_dma_shape<float, float, true>(shape, g, s, slots, tiles, rowoff, ntiles);
-    else if (c_is_f64) dispatch_dma_shape<float, double>(shape, g, s, slots, tiles, rowoff, ntiles);
-    else dispatch_dma_shape<float, float>(shape, g, s, slots, tiles, rowoff, ntiles);
+        dispatch_dma_shape<float, double, true>(shape, g, s, slots, tiles, rowoff, epi, ntiles);
+    else if (prec == GemmPrec::BF16X3) dispatch_dma_shape<float, float, true>(shape, g, s, slots, tiles, rowoff, epi, ntiles);
+    else if (c_is_f64) dispatch_dma_shape<float, double>(shape, g, s, slots, tiles, rowoff, epi, ntiles);
+    else dispatch_dma_shape<float, float>(shape, g, s, slots, tiles, rowoff, epi, ntiles);
 }
 
 void launch_gemm(GemmPrec prec, TileShape shape, bool ta, bool tb, bool c_is_f64, const Slots &slots,
                  const GemmItem *items, const GemmSeg *segs, const GemmTile *tiles, const int64_t *rowoff,
-                 int ntiles, hipStream_t s) {
+                 const EpiDev &epi, int ntiles, hipStream_t s) {
     if (ntiles <= 0) return;
     dim3 grid(ntiles);
-    const GemmArgs a{slots, items, segs, tiles, rowoff, ntiles};
+    const GemmArgs a{slots, items, segs, tiles, rowoff, epi, ntiles};
     switch (prec) {
         case GemmPrec::F64:
             dispatch_kmajor<double, double>(shape, ta, tb, grid, s, a);

@@ -36,7 +36,8 @@ struct GemmItem {
 };
 
 struct GemmTile {
-    int32_t item, m0, n0, pad_;
+    int32_t item, m0, n0;
+    int32_t chan;   // EpiItem: channel of row m0
 };
 
 // A tile of a single-segment item with everything the tile needs in one
@@ -46,6 +47,27 @@ struct FlatTile {
     int64_t a_off, b_off, c_off;
     int32_t a_slot, b_slot, c_slot, rmap;
     int32_t M, N, K, lda, ldb, ldc, m0, n0;
+    int32_t erow, ecol, edst, eseg;   // EpiDev (item's columns, first channel of the tile's rows)
+};
+
+// Where stage 1 of H_eff puts its output blocks.  An item's rows are channels
+// (epi_row: first row of each, then M), its columns segments (epi_col: first
+// column of each, then N).  The block of channel c and segment s (dst[c * eseg +
+// s]) is stored in C if `keep`, and, times coef, at off of slot EpiDev::slot
+// (row stride ld) if off >= 0: the W stage's sums of one term each.
+struct EpiDst {
+    int64_t off;
+    double coef;
+    int32_t ld, keep;
+};
+struct EpiItem {
+    int32_t row0, col0, dst0, nseg;
+};
+struct EpiDev {
+    const EpiItem *items;   // null: plain output
+    const int32_t *row, *col;
+    const EpiDst *dst;
+    int slot;
 };
 
 // Scaled sum of same-shaped strided blocks: dst = sum_j coef_j * src_j.
@@ -160,15 +182,15 @@ inline int tile_bn(TileShape t) {
 // with item < 0 are idle).
 void launch_gemm(GemmPrec prec, TileShape shape, bool ta, bool tb, bool c_is_f64, const Slots &slots,
                  const GemmItem *items, const GemmSeg *segs, const GemmTile *tiles, const int64_t *rowoff,
-                 int ntiles, hipStream_t s);
+                 const EpiDev &epi, int ntiles, hipStream_t s);
 // FP32 or FP64 operands (prec F32 / F64), non-transposed, one segment per
 // item, LDS-DMA tile shape (T128x32_D, T64x64_D, T32x128_D); one workgroup per
 // entry of `tiles`.
 void launch_gemm_flat(GemmPrec prec, TileShape shape, bool c_is_f64, const Slots &slots, const FlatTile *tiles,
-                      const int64_t *rowoff, int ntiles, hipStream_t s);
+                      const int64_t *rowoff, const EpiDev &epi, int ntiles, hipStream_t s);
 // The same for FP64 and a register-direct tile shape (_R).
-void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff, int ntiles,
-                     hipStream_t s);
+void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff,
+                     const EpiDev &epi, int ntiles, hipStream_t s);
 // chunk: kLcChunk or kLcChunkSmall elements per tile (as the tiles were built).
 void launch_lincomb(bool f64, int chunk, const Slots &slots, const LcTask *tasks, const LcSrc *srcs,
                     const LcTile *tiles, int ntiles, hipStream_t s);

@@ -260,6 +260,11 @@ void GemmList::stage(ListStage &st) {
         st.add(dev.ftiles, ftiles);
     }
     st.add(dev.rowoff, rowoff);
+    if (epi_items.empty()) return;
+    st.add(dev.epi.items, epi_items);
+    st.add(dev.epi.row, epi_row);
+    st.add(dev.epi.col, epi_col);
+    st.add(dev.epi.dst, epi_dst);
 }
 
 void GemmList::build_tiles() {
@@ -277,6 +282,12 @@ void GemmList::build_tiles() {
     check_grid((int64_t)tiles.size(), 256, "gemm");
     PD_REQUIRE(std::count_if(tiles.begin(), tiles.end(), [](const GemmTile &t) { return t.item >= 0; }) ==
                    ntiles_real, PDMRG_ESHAPE, "gemm: tile placement lost tiles");
+    if (!epi_items.empty())
+        for (GemmTile &t : tiles) {
+            if (t.item < 0) continue;
+            const int32_t *r = epi_row.data() + epi_items[t.item].row0;
+            while (r[t.chan + 1] <= t.m0) ++t.chan;
+        }
     ftiles.clear();
     bool single = !ta && !tb;
     for (const GemmItem &it : items) single = single && it.nseg <= 1;
@@ -303,6 +314,13 @@ void GemmList::build_tiles() {
                 f.K = std::max(sg.K, 0);
                 f.lda = sg.lda;
                 f.ldb = sg.ldb;
+            }
+            if (!epi_items.empty()) {
+                const EpiItem &ei = epi_items[t.item];
+                f.erow = ei.row0 + t.chan;
+                f.ecol = ei.col0;
+                f.edst = ei.dst0 + t.chan * ei.nseg;
+                f.eseg = ei.nseg;
             }
         }
         ftiles.push_back(f);
@@ -461,14 +479,15 @@ void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, const GemmD
     if ((1u << (int)shape) & kR64Shapes) {
         PD_REQUIRE(prec == GemmPrec::F64 && (!ftiles.empty() || tiles.empty()), PDMRG_EINVAL,
                    "gemm: the register-direct kernel is for FP64 and one segment per item");
-        launch_gemm_r64(shape, sl, dv.ftiles, dv.rowoff, (int)ftiles.size(), s);
+        launch_gemm_r64(shape, sl, dv.ftiles, dv.rowoff, dv.epi, (int)ftiles.size(), s);
         return;
     }
     if (!ftiles.empty()) {
-        launch_gemm_flat(prec, shape, c_is_f64, sl, dv.ftiles, dv.rowoff, (int)ftiles.size(), s);
+        launch_gemm_flat(prec, shape, c_is_f64, sl, dv.ftiles, dv.rowoff, dv.epi, (int)ftiles.size(), s);
         return;
     }
-    launch_gemm(prec, shape, ta, tb, c_is_f64, sl, dv.items, dv.segs, dv.tiles, dv.rowoff, (int)tiles.size(), s);
+    launch_gemm(prec, shape, ta, tb, c_is_f64, sl, dv.items, dv.segs, dv.tiles, dv.rowoff, dv.epi,
+                (int)tiles.size(), s);
 }
 
 int LcList::add_task(int dst_slot, int64_t dst_off, int rows, int cols, int ld) {
@@ -585,6 +604,7 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
 
     // stage 1: T1[j] = Lket[j] (rows (w, a)) x X[j] (rows a', cols (t1 t2 b'))
     std::vector<int64_t> t1base(nl, -1);
+    std::vector<int> chan((size_t)nl * Dl, -1), seg((size_t)nl * d2, -1), item_of(nl, -1);   // EpiItem indices
     nT1 = 0;
     g1 = GemmList();
     g1.elem_bytes = prec == PDMRG_F64 ? 8 : 4;
@@ -595,7 +615,30 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
         g1.add_item(4, nT1, M, N, N);
         g1.add_seg(2, Lt.base[j], K, 0, X.base[j], N, K);
         nT1 += (int64_t)M * N;
+        EpiItem ei{(int32_t)g1.epi_row.size(), (int32_t)g1.epi_col.size(), (int32_t)g1.epi_dst.size(), 0};
+        int nc = 0;
+        for (int ww = 0; ww < Dl; ++ww) {
+            const int r0 = Lt.rowo[(size_t)j * Dl + ww];
+            if (r0 < 0) continue;
+            chan[(size_t)j * Dl + ww] = nc++;
+            g1.epi_row.push_back(r0);
+        }
+        g1.epi_row.push_back(M);
+        for (int tg = 0; tg < d2; ++tg) {
+            const int c0 = X.colo[(size_t)j * d2 + tg];
+            if (c0 < 0) continue;
+            seg[(size_t)j * d2 + tg] = ei.nseg++;
+            g1.epi_col.push_back(c0);
+        }
+        g1.epi_col.push_back(N);
+        g1.epi_dst.resize(g1.epi_dst.size() + (size_t)nc * ei.nseg, EpiDst{-1, 0.0, 0, 0});
+        item_of[j] = (int)g1.epi_items.size();
+        g1.epi_items.push_back(ei);
     }
+    auto epi_at = [&](int j, int ww, int tg) -> EpiDst & {
+        const EpiItem &ei = g1.epi_items[item_of[j]];
+        return g1.epi_dst[ei.dst0 + (size_t)chan[(size_t)j * Dl + ww] * ei.nseg + seg[(size_t)j * d2 + tg]];
+    };
 
     // T2 blocks: one per output block (i, s1 s2) -> [dim(q_i) x Rt.rows[k]],
     // grouped by the bra sector k they multiply, so that the blocks sharing
@@ -616,6 +659,17 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
 
     // stage 2: W stage
     w = LcList();
+    const std::vector<int64_t> sz = {X.size, X.size, Lt.size, Rt.size, nT1, nT2, 0};
+    struct Term {
+        int j, ww, tg;
+        int64_t off;
+        double c;
+    };
+    std::vector<Term> terms;
+    // below this the W stage is latency, and looking blocks up costs stage 1 more
+    // than it saves (16-site chain, m = 64, 0.1 MB: 19.0 -> 21.6 us; 8 x 4 cylinder,
+    // m = 1024, 63 MB: 187 -> 181)
+    const bool direct = nT1 * g1.elem_bytes >= (int64_t(32) << 20);
     std::vector<std::vector<Entry>> nz((size_t)d2 * Dr);   // of (s1 s2, w2): (w, t1 t2) in order
     for (int ww = 0; ww < Dl; ++ww)
         for (int sg = 0; sg < d2; ++sg)
@@ -635,7 +689,7 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
                 const int ro = Rt.rowo[(size_t)k * Dr + w2];
                 if (ro < 0) continue;
                 const int cols = br.dim_of(qb - W2.dr[w2]);
-                w.add_task(5, tb + ro, bl.dim[i], cols, Rt.rows[k]);
+                terms.clear();
                 for (const Entry &e : nz[(size_t)sg * Dr + w2]) {
                     const int ww = e.x, tg = e.y;
                     const int j = bl.find(bl.q[i] - W1.dl[ww]);
@@ -646,7 +700,22 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
                     if (co < 0) continue;
                     PD_REQUIRE(X.width[(size_t)j * d2 + tg] == cols, PDMRG_ESHAPE,
                                "heff: MPO entry violates charge conservation");
-                    w.add_src(4, t1base[j] + (int64_t)lro * X.cols[j] + co, X.cols[j], e.c);
+                    terms.push_back(Term{j, ww, tg, t1base[j] + (int64_t)lro * X.cols[j] + co, e.c});
+                }
+                // a sum of one term is left to stage 1 (a block goes to one place besides T1)
+                EpiDst *one = direct && terms.size() == 1 ? &epi_at(terms[0].j, terms[0].ww, terms[0].tg) : nullptr;
+                if (one && one->off < 0) {
+                    one->off = tb + ro;
+                    one->coef = terms[0].c;
+                    one->ld = Rt.rows[k];
+                    check_span(sz, 5, one->off, bl.dim[i], cols, one->ld, "W stage dst");
+                    w.flops += 2.0 * bl.dim[i] * (double)cols;
+                    continue;
+                }
+                w.add_task(5, tb + ro, bl.dim[i], cols, Rt.rows[k]);
+                for (const Term &t : terms) {
+                    w.add_src(4, t.off, X.cols[t.j], t.c);
+                    epi_at(t.j, t.ww, t.tg).keep = 1;
                 }
             }
         }
@@ -735,7 +804,8 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
     const double bytes = g1.operand_bytes() + g3.operand_bytes();
     g1.pick_tile(bytes);
     g3.pick_tile(bytes);
-    const std::vector<int64_t> sz = {X.size, X.size, Lt.size, Rt.size, nT1, nT2, 0};
+    g1.dev.epi.slot = 5;
+    if (!direct) g1.epi_items.clear();
     g1.validate(sz);
     w.validate(sz);
     g1.finish(s);

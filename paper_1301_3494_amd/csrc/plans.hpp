@@ -21,6 +21,7 @@ struct GemmDev {
     const GemmTile *tiles;
     const FlatTile *ftiles;
     const int64_t *rowoff;
+    EpiDev epi;
 };
 struct LcDev {
     const LcTask *tasks;
@@ -49,6 +50,10 @@ struct GemmList {
     // LDS-DMA and register-direct shapes on lists of single-segment items: the
     // tiles as FlatTile records in the same launch order
     std::vector<FlatTile> ftiles;
+    // Stage 1 of H_eff: where the blocks of an item go (per item; empty: to C).
+    std::vector<EpiItem> epi_items;
+    std::vector<int32_t> epi_row, epi_col;
+    std::vector<EpiDst> epi_dst;
     GemmDev dev{};                         // set by stage() / finish()
     DevBuf d_lists;                        // what finish() uploads
 
