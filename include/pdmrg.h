@@ -252,10 +252,11 @@ int heff_info(const pdmrg_heff *op, double *flops_Lpsi, double *flops_W, double 
  * half-depth, 6: 64x64 and 7: 128x32 with quarter-depth K steps; 8: 128x32,
  * 9: 64x64, 10: 32x128 with K steps of 16 staged by direct-to-LDS loads, FP32
  * and FP64 only; 11: 64x64, 12: 128x64, 13: 64x128, 14: 128x128 with operands
- * loaded straight into registers, FP64 only), their tile counts (without the
- * idle padding of the launch order), and the number of K parts of the longest
- * stage-3 item (the other items are cut into ranges of about the same length).
- * Outputs optional. */
+ * loaded straight into registers, FP64 only; 15: 64x64 and 16: 128x64, 17 and 18
+ * the same with K steps of 32, all accesses of 16 bytes, FP32 and BF16x3 only),
+ * their tile counts (without the idle padding of the launch order), and the
+ * number of K parts of the longest stage-3 item (the other items are cut into
+ * ranges of about the same length).  Outputs optional. */
 int heff_plan_info(const pdmrg_heff *op, int32_t *shape_Lpsi, int32_t *shape_R, int32_t *tiles_Lpsi,
                    int32_t *tiles_R, int32_t *splitk_parts);
 /* diag(H_eff) into diag_dev (TWO_SITE layout, FP64). */

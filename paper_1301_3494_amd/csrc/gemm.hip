@@ -13,8 +13,8 @@
 // of 16 x 16 MFMA blocks (v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4).  FP64
 // operands that stream from memory go straight into registers (gemm_r64).  BF16x3
 // takes operands split once in memory (each 4-byte word a bf16 pair x = hi +
-// lo, both rounded to nearest even) through the FP32 LDS-DMA pipeline and
-// accumulates lo*hi' + hi*lo' + hi*hi' with v_mfma_f32_16x16x16_bf16 in FP32.
+// lo, both rounded to nearest even) through the FP32 kernels (gemm_quad,
+// gemm_dma) and accumulates lo*hi' + hi*lo' + hi*hi' with bf16 MFMAs in FP32.
 //
 // Operands are read with buffer loads: the descriptor of each segment spans
 // its operand and an offset outside it returns zero, so ragged tile edges need
@@ -78,6 +78,9 @@ __device__ __forceinline__ int64_t c_row(const GemmItem &it, const int64_t *__re
 // 19 us and 77 -> 81; 24 x 8 FP32, m = 2000, 44 -> 19 and 101 -> 106; tri 12 x 6
 // BF16x3, m = 3000, 126 -> 58 and 387 -> 409; 98 channels, m = 4000, 1.61 -> 0.54 ms
 // and 5.30 -> 5.51.
+// 16-byte accesses to rows of any 4-byte alignment
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned w4u __attribute__((ext_vector_type(4), aligned(4)));
 // NC columns of a lane (those below N), its rows in ascending order.
 template <int NC, typename TD>
 struct EpiWriter {
@@ -123,6 +126,20 @@ struct EpiWriter {
             TD *o = out + e[j].off + (int64_t)(gm - start) * e[j].ld + b[j];
             if constexpr (std::is_same<TD, uint32_t>::value) *o = pack_split(w);
             else *o = (TD)w;
+        }
+    }
+    // four neighbouring columns of one segment
+    __device__ __forceinline__ void store4(int gm, const float (&v)[4], float *c) const {
+        if (e[0].keep) *reinterpret_cast<f4u *>(c) = f4u{v[0], v[1], v[2], v[3]};
+        if (e[0].off >= 0) {
+            TD *o = out + e[0].off + (int64_t)(gm - start) * e[0].ld + b[0];
+            float w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = 0.0f + (float)e[0].coef * v[j];
+            if constexpr (std::is_same<TD, uint32_t>::value)
+                *reinterpret_cast<w4u *>(o) = w4u{pack_split(w[0]), pack_split(w[1]), pack_split(w[2]), pack_split(w[3])};
+            else
+                *reinterpret_cast<f4u *>(o) = f4u{w[0], w[1], w[2], w[3]};
         }
     }
 };
@@ -569,6 +586,218 @@ __global__ __launch_bounds__(NT) void gemm_dma(Slots slots, const FlatTile *__re
                 if (gn < N) Cr[gn] = (TC)acc[i][j][r];
             }
         }
+}
+
+// ---------------------------------------------------------------- FP32 / BF16x3, quads
+// Operands of 4-byte words moved 16 bytes a lane all the way: the LDS-DMA kernel
+// above spends its vector slots on one-dword loads and reads B a word at a time
+// (BF16x3, tri 12 x 6, m = 3000: matrix cores a third busy).  Four waves stacked
+// along M, each 16 WBM rows by the tile's 64 columns:
+//   A stage: rows of 16 k (64 bytes), chunk c (4 words) at c ^ (row / 4 % 4), so
+//     that the 16 rows of an operand read spread over the banks;
+//   B stage: rows of 64 columns; a lane reads 4 neighbouring columns of k = 4 g +
+//     q, so MFMA column block j holds columns 4 x + j and one read serves four
+//     blocks.
+// k = 4 g + q in both operands, as in the LDS-DMA kernel.  KS = 2 stages two such
+// steps for v_mfma_f32_16x16x32_bf16 (half the issue of the 16-deep one).
+//
+// A chunk of A that crosses the end of K is cut word by word; loads past the
+// last column or row of an operand end within the kQuadPad bytes that the
+// caller leaves behind it (those values are cut, or of columns not stored).
+typedef unsigned w4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ w4 buf_quad(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(w4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+// the low (HI: the values' high parts) or high halves of four words
+template <bool HI>
+__device__ __forceinline__ u2v halves(unsigned a, unsigned b, unsigned c, unsigned d) {
+    constexpr unsigned sel = HI ? 0x05040100u : 0x07060302u;
+    return u2v{__builtin_amdgcn_perm(b, a, sel), __builtin_amdgcn_perm(d, c, sel)};
+}
+
+template <bool SPLIT, int WBM, int KS>
+__global__ __launch_bounds__(NT) void gemm_quad(Slots slots, const FlatTile *__restrict__ tiles,
+                                                const int64_t *__restrict__ rowoff, int ntiles, EpiDev epi) {
+    constexpr int BM = 64 * WBM, BK = 16 * KS, WBN = 4;
+    __shared__ w4 As[2][KS][BM * 4];
+    __shared__ w4 Bs[2][KS][16 * 16];
+    if ((int)blockIdx.x >= ntiles) return;
+    const FlatTile ft = tiles[blockIdx.x];
+    if (ft.M <= 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = ft.M, N = ft.N, K = ft.K, m0 = ft.m0, n0 = ft.n0;
+    const __amdgpu_buffer_rsrc_t rA = operand_rsrc(static_cast<const float *>(slots.p[ft.a_slot]) + ft.a_off);
+    const __amdgpu_buffer_rsrc_t rB = operand_rsrc(static_cast<const float *>(slots.p[ft.b_slot]) + ft.b_off);
+    const int nsteps = K > 0 ? (K + BK - 1) / BK : 0;
+    // this thread's chunks: A rows tid / 4 + 64 u, words 4 (tid % 4); B row tid / 16, columns 4 (tid % 16)
+    const int ac = tid & 3, ar = tid >> 2, bc = tid & 15, bk = tid >> 4;
+    unsigned aoff[WBM];
+#pragma unroll
+    for (int u = 0; u < WBM; ++u) {
+        const int m = m0 + ar + 64 * u;
+        aoff[u] = m < M ? ((unsigned)m * (unsigned)ft.lda + 4u * ac) * 4u : kOutOfRange;
+    }
+    const unsigned ldbb = (unsigned)ft.ldb * 4u;
+    const unsigned boff = n0 + 4 * bc < N ? (unsigned)(n0 + 4 * bc) * 4u + (unsigned)bk * ldbb : kOutOfRange;
+    w4 ra[KS][WBM], rb[KS];
+    auto load = [&](int s) {
+#pragma unroll
+        for (int h = 0; h < KS; ++h) {
+            const int k0 = s * BK + 16 * h, ka = k0 + 4 * ac;
+#pragma unroll
+            for (int u = 0; u < WBM; ++u) {
+                ra[h][u] = buf_quad(rA, aoff[u] != kOutOfRange && ka < K ? aoff[u] + (unsigned)k0 * 4u : kOutOfRange);
+                if (k0 + 16 > K)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (ka + q >= K) ra[h][u][q] = 0;
+            }
+            rb[h] = buf_quad(rB, boff != kOutOfRange && k0 + bk < K ? boff + (unsigned)k0 * ldbb : kOutOfRange);
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int h = 0; h < KS; ++h) {
+#pragma unroll
+            for (int u = 0; u < WBM; ++u) {
+                const int r = ar + 64 * u;
+                As[buf][h][4 * r + (ac ^ ((r >> 2) & 3))] = ra[h][u];
+            }
+            Bs[buf][h][tid] = rb[h];
+        }
+    };
+    f4 acc[WBM][WBN];
+#pragma unroll
+    for (int i = 0; i < WBM; ++i)
+#pragma unroll
+        for (int j = 0; j < WBN; ++j) acc[i][j] = f4{0, 0, 0, 0};
+    if (nsteps > 0) {
+        load(0);
+        store(0);
+    }
+    __syncthreads();
+    for (int s = 0; s < nsteps; ++s) {
+        const int buf = s & 1;
+        if (s + 1 < nsteps) load(s + 1);
+        w4 a[KS][WBM], b[KS][4];
+#pragma unroll
+        for (int h = 0; h < KS; ++h) {
+#pragma unroll
+            for (int i = 0; i < WBM; ++i) {
+                const int r = wave * 16 * WBM + 16 * i + r16;
+                a[h][i] = As[buf][h][4 * r + (g ^ ((r >> 2) & 3))];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) b[h][q] = Bs[buf][h][(4 * g + q) * 16 + r16];
+        }
+        if constexpr (SPLIT) {
+            using V = typename std::conditional<KS == 2, bf8, s4v>::type;
+            auto pack = [](u2v x, u2v y) {
+                if constexpr (KS == 2) return __builtin_bit_cast(bf8, w4{x.x, x.y, y.x, y.y});
+                else return __builtin_bit_cast(s4v, x);
+            };
+            auto mfma = [](V x, V y, f4 c) {
+                if constexpr (KS == 2) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+                else return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, y, c, 0, 0, 0);
+            };
+            V ah[WBM], al[WBM];
+#pragma unroll
+            for (int i = 0; i < WBM; ++i) {
+                const w4 x = a[0][i], y = a[KS - 1][i];
+                ah[i] = pack(halves<true>(x.x, x.y, x.z, x.w), halves<true>(y.x, y.y, y.z, y.w));
+                al[i] = pack(halves<false>(x.x, x.y, x.z, x.w), halves<false>(y.x, y.y, y.z, y.w));
+            }
+#pragma unroll
+            for (int j = 0; j < WBN; ++j) {
+                const V bh = pack(halves<true>(b[0][0][j], b[0][1][j], b[0][2][j], b[0][3][j]),
+                                  halves<true>(b[KS - 1][0][j], b[KS - 1][1][j], b[KS - 1][2][j], b[KS - 1][3][j]));
+                const V bl = pack(halves<false>(b[0][0][j], b[0][1][j], b[0][2][j], b[0][3][j]),
+                                  halves<false>(b[KS - 1][0][j], b[KS - 1][1][j], b[KS - 1][2][j], b[KS - 1][3][j]));
+#pragma unroll
+                for (int i = 0; i < WBM; ++i) acc[i][j] = mfma(al[i], bh, acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < WBM; ++i) acc[i][j] = mfma(ah[i], bl, acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < WBM; ++i) acc[i][j] = mfma(ah[i], bh, acc[i][j]);
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < KS; ++h)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < WBM; ++i)
+#pragma unroll
+                        for (int j = 0; j < WBN; ++j)
+                            acc[i][j] = mfma16(__builtin_bit_cast(float, (unsigned)a[h][i][q]),
+                                               __builtin_bit_cast(float, (unsigned)b[h][q][j]), acc[i][j]);
+        }
+        if (s + 1 < nsteps) store(buf ^ 1);
+        __syncthreads();
+    }
+    // register r of lane l: row 4 (l / 16) + r of the block, column 4 (l % 16) + j of the tile
+    float *C = static_cast<float *>(const_cast<void *>(slots.p[ft.c_slot])) + ft.c_off;
+    const int mw = m0 + wave * 16 * WBM + 4 * g, nw = n0 + 4 * r16;
+    if (epi.items) {
+        using TD = typename std::conditional<SPLIT, uint32_t, float>::type;
+        int gn[WBN];
+#pragma unroll
+        for (int j = 0; j < WBN; ++j) gn[j] = nw + j;
+        EpiWriter<WBN, TD> ew(const_cast<void *>(slots.p[epi.slot]), epi.row + ft.erow, epi.col + ft.ecol,
+                              epi.dst + ft.edst, ft.eseg, gn, N);
+        const bool quad = nw + 3 < N && ew.seg[0] == ew.seg[3];
+#pragma unroll
+        for (int i = 0; i < WBM; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gm = mw + 16 * i + r;
+                if (gm >= M) continue;
+                ew.seek(gm);
+                float *c = C + (int64_t)gm * ft.ldc + nw;
+                const float v[4] = {acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
+                if (quad) {
+                    ew.store4(gm, v, c);
+                    continue;
+                }
+#pragma unroll
+                for (int j = 0; j < WBN; ++j)
+                    if (gn[j] < N) ew.store(gm, j, v[j], c + j);
+            }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < WBM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int gm = mw + 16 * i + r;
+            if (gm >= M) continue;
+            float *c = C + (ft.rmap >= 0 ? rowoff[ft.rmap + gm] : (int64_t)gm * ft.ldc) + nw;
+            if (nw + 3 < N) {
+                *reinterpret_cast<f4u *>(c) = f4u{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < WBN; ++j)
+                if (nw + j < N) c[j] = acc[i][j][r];
+        }
+}
+
+void launch_gemm_quad(bool split, TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff,
+                      const EpiDev &epi, int ntiles, hipStream_t s) {
+    if (ntiles <= 0) return;
+    const dim3 g(ntiles);
+#define PD_QUAD(SP, WBM, KS) \
+    hipLaunchKernelGGL((gemm_quad<SP, WBM, KS>), g, dim3(NT), 0, s, slots, tiles, rowoff, ntiles, epi)
+    switch (shape) {
+        case TileShape::T64x64_Q: if (split) PD_QUAD(true, 1, 1); else PD_QUAD(false, 1, 1); break;
+        case TileShape::T128x64_Q: if (split) PD_QUAD(true, 2, 1); else PD_QUAD(false, 2, 1); break;
+        case TileShape::T64x64_Q32: if (split) PD_QUAD(true, 1, 2); else PD_QUAD(false, 1, 2); break;
+        case TileShape::T128x64_Q32: if (split) PD_QUAD(true, 2, 2); else PD_QUAD(false, 2, 2); break;
+        default: break;
+    }
+#undef PD_QUAD
 }
 
 // ---------------------------------------------------------------- FP64, register-direct

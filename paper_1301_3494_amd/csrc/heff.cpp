@@ -54,7 +54,8 @@ const char *shape_name(int t) {
     static const char *n[kNumShapes] = {"64x64", "128x32", "32x128", "128x128",
                                         "64x64k16", "128x32k16", "64x64k8", "128x32k8",
                                         "128x32dma", "64x64dma", "32x128dma",
-                                        "64x64reg", "128x64reg", "64x128reg", "128x128reg"};
+                                        "64x64reg", "128x64reg", "64x128reg", "128x128reg",
+                                        "64x64quad", "128x64quad", "64x64quad32", "128x64quad32"};
     return n[t];
 }
 
@@ -66,7 +67,7 @@ void tune_heff(pdmrg_ctx *ctx, pdmrg_heff *op, const std::string &key) {
     const GemmPrec gp = gemm_prec(op->prec);
     const bool f64 = op->prec == PDMRG_F64;
     const size_t es = f64 ? sizeof(double) : sizeof(float);
-    DevBuf xin(std::max<int64_t>(op->nX, 1) * es), yout(std::max<int64_t>(op->nX, 1) * sizeof(double));
+    DevBuf xin(std::max<int64_t>(op->nX, 1) * es + kQuadPad), yout(std::max<int64_t>(op->nX, 1) * sizeof(double));
     // timed on nonzero operands (the clock of the FP64 matrix cores depends on
     // them): the left environment stands in for x
     HIP_OK(hipMemsetAsync(xin.ptr, 0, xin.bytes, s));
@@ -169,8 +170,8 @@ void heff_build(pdmrg_ctx *ctx, pdmrg_heff *op, const Bond &bl, const Bond &br, 
         op->lp = L;
         op->rp = R;
     } else {
-        op->L.ensure(std::max<int64_t>(op->nL, 1) * es);
-        op->R.ensure(std::max<int64_t>(op->nR, 1) * es);
+        op->L.ensure(std::max<int64_t>(op->nL, 1) * es + kQuadPad);
+        op->R.ensure(std::max<int64_t>(op->nR, 1) * es + kQuadPad);
         if (prec == PDMRG_F64) {
             if (op->nL) HIP_OK(hipMemcpyAsync(op->L.ptr, L, op->nL * es, hipMemcpyDeviceToDevice, s));
             if (op->nR) HIP_OK(hipMemcpyAsync(op->R.ptr, R, op->nR * es, hipMemcpyDeviceToDevice, s));
@@ -184,14 +185,14 @@ void heff_build(pdmrg_ctx *ctx, pdmrg_heff *op, const Bond &bl, const Bond &br, 
         op->lp = op->L.ptr;
         op->rp = op->R.ptr;
     }
-    if (prec != PDMRG_F64) op->xs.ensure(std::max<int64_t>(op->nX, 1) * sizeof(float));
+    if (prec != PDMRG_F64) op->xs.ensure(std::max<int64_t>(op->nX, 1) * sizeof(float) + kQuadPad);
     // intermediates: another operator's where they are large enough
     auto pick = [&](DevBuf &own, void *other, size_t other_bytes, size_t need) -> void * {
         if (other && other_bytes >= need) return other;
         own.ensure(need);
         return own.ptr;
     };
-    const size_t n1 = std::max<int64_t>(pl.nT1, 1) * es, n2 = std::max<int64_t>(pl.nT2, 1) * es;
+    const size_t n1 = std::max<int64_t>(pl.nT1, 1) * es, n2 = std::max<int64_t>(pl.nT2, 1) * es + kQuadPad;
     op->t1 = pick(op->T1, ws_from ? ws_from->t1 : nullptr, ws_from ? ws_bytes(ws_from, 1) : 0, n1);
     op->t2 = pick(op->T2, ws_from ? ws_from->t2 : nullptr, ws_from ? ws_bytes(ws_from, 2) : 0, n2);
     if (ctx->autotune > 0) {

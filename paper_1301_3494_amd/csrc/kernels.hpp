@@ -149,17 +149,20 @@ enum class TileShape {
     // FP32 / FP64, non-transposed operands: K steps of 16 staged by
     // direct-to-LDS loads (other operands: the half-depth kernel)
     T128x32_D = 8, T64x64_D = 9, T32x128_D = 10,
-    T64x64_R = 11, T128x64_R = 12, T64x128_R = 13, T128x128_R = 14
+    T64x64_R = 11, T128x64_R = 12, T64x128_R = 13, T128x128_R = 14,
+    // FP32 / BF16X3, non-transposed operands: 16-byte accesses, K steps of 16 or 32
+    T64x64_Q = 15, T128x64_Q = 16, T64x64_Q32 = 17, T128x64_Q32 = 18
 };
-constexpr int kNumShapes = 15;
+constexpr int kNumShapes = 19;
 constexpr unsigned kStagedShapes = (1u << 8) - 1;
 constexpr unsigned kDmaShapes = (1u << 8) | (1u << 9) | (1u << 10);
 constexpr unsigned kR64Shapes = (1u << 11) | (1u << 12) | (1u << 13) | (1u << 14);
+constexpr unsigned kQuadShapes = (1u << 15) | (1u << 16) | (1u << 17) | (1u << 18);
 inline int tile_bm(TileShape t) {
     switch (t) {
         case TileShape::T32x128: case TileShape::T32x128_D: return 32;
         case TileShape::T64x64: case TileShape::T64x64_K16: case TileShape::T64x64_K8: case TileShape::T64x64_D:
-        case TileShape::T64x64_R: case TileShape::T64x128_R:
+        case TileShape::T64x64_R: case TileShape::T64x128_R: case TileShape::T64x64_Q: case TileShape::T64x64_Q32:
             return 64;
         default: return 128;
     }
@@ -170,6 +173,7 @@ inline int tile_bn(TileShape t) {
             return 32;
         case TileShape::T64x64: case TileShape::T64x64_K16: case TileShape::T64x64_K8: case TileShape::T64x64_D:
         case TileShape::T64x64_R: case TileShape::T128x64_R:
+        case TileShape::T64x64_Q: case TileShape::T128x64_Q: case TileShape::T64x64_Q32: case TileShape::T128x64_Q32:
             return 64;
         default: return 128;
     }
@@ -188,6 +192,11 @@ void launch_gemm(GemmPrec prec, TileShape shape, bool ta, bool tb, bool c_is_f64
 // entry of `tiles`.
 void launch_gemm_flat(GemmPrec prec, TileShape shape, bool c_is_f64, const Slots &slots, const FlatTile *tiles,
                       const int64_t *rowoff, const EpiDev &epi, int ntiles, hipStream_t s);
+// FP32 operands (split: BF16x3 words) and a quad shape (_Q), C in FP32.  Every
+// operand has kQuadPad bytes of memory behind it.
+constexpr int kQuadPad = 16;
+void launch_gemm_quad(bool split, TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff,
+                      const EpiDev &epi, int ntiles, hipStream_t s);
 // The same for FP64 and a register-direct tile shape (_R).
 void launch_gemm_r64(TileShape shape, const Slots &slots, const FlatTile *tiles, const int64_t *rowoff,
                      const EpiDev &epi, int ntiles, hipStream_t s);

@@ -83,21 +83,26 @@ double GemmList::operand_bytes() const {
     return b;
 }
 
-// Estimated time of a list under a register-direct (FP64) or LDS-DMA (FP32,
-// BF16x3) shape, in flops of one CU at full rate: the work (dimensions rounded
-// up to the tile, register-direct ones to the 32 that a wave's edge tile keeps)
-// spread over the chip at the shape's rate, plus the longest tile, which the
-// last CU to finish may have started last.
+// Estimated time of a list under a register-direct (FP64) or quad (FP32, BF16x3)
+// shape, in flops of one CU at full rate: the work (dimensions rounded up to the
+// tile, register-direct ones to the 32 that a wave's edge tile keeps) spread
+// over the chip at the shape's rate, plus the longest tile, which the last CU to
+// finish may have started last.
 double GemmList::cost(TileShape ts, int parts) const {
     // Relative rates.  Register-direct, 64 x 64, 128 x 64, 64 x 128, 128 x 128: H_eff
     // at m = 4000 with 98 channels, stage 1 6.9, 5.9, 5.5, 5.1 ms, stage 3 9.6, 8.2,
-    // 6.6, 5.9.  LDS-DMA, 128 x 32, 64 x 64, 32 x 128: stage 1 of the tri 12 x 6
-    // lattice, m = 3000, BF16x3 0.465, 0.385, 0.371 ms, FP32 0.520, 0.489, 0.525.
-    static const double kReg[4] = {0.66, 0.77, 0.91, 1.0}, kSplit[3] = {0.80, 0.97, 1.0}, kF32[3] = {0.94, 1.0, 0.93};
-    constexpr double kTileK = 48.0;   // start and end of a tile, in K units
+    // 6.6, 5.9.  Quads, 64 x 64, 128 x 64 and the same with K steps of 32: tri 12 x
+    // 6, m = 3000, BF16x3 stage 1 (K = 330) 0.415, 0.349, 0.366, 0.359 ms, stage 3 (K =
+    // 1100 a part) 0.382, 0.344, 0.335, 0.331, FP32 0.500, 0.488, 0.510, 0.512 and
+    // 0.510, 0.514, 0.505, 0.519; the LDS-DMA kernel's best are 0.409, 0.388, 0.527,
+    // 0.540.
+    static const double kReg[4] = {0.66, 0.77, 0.91, 1.0}, kSplit[4] = {0.86, 0.98, 0.99, 1.02},
+                        kF32[4] = {0.97, 1.0, 1.0, 0.98};
     const bool reg = (kR64Shapes >> (int)ts) & 1u, split = !(shapes_allowed & kStagedShapes);
     const double rate = reg ? kReg[(int)ts - (int)TileShape::T64x64_R]
-                            : (split ? kSplit : kF32)[(int)ts - (int)TileShape::T128x32_D];
+                            : (split ? kSplit : kF32)[(int)ts - (int)TileShape::T64x64_Q];
+    // start and end of a tile, in K units (deep steps: half a step of K wasted more)
+    const double kTileK = ts == TileShape::T64x64_Q32 || ts == TileShape::T128x64_Q32 ? 80.0 : 48.0;
     const double partial = reg ? 240.0 : split ? 230.0 : 150.0;   // flops in the time of writing and reading a partial sum
     const int bm = tile_bm(ts), bn = tile_bn(ts), rm = reg ? 32 : bm, rn = reg ? 32 : bn;
     int64_t kmax = 0;
@@ -122,12 +127,12 @@ double GemmList::cost(TileShape ts, int parts) const {
 // tri 12 x 6, m = 3000, 1 GB, 1.05 against 1.06), and its sums run over
 // ascending k.
 //
-// FP32 and BF16x3 take the LDS-DMA shape of least cost().
+// FP32 and BF16x3 take the quad shape of least cost().
 void GemmList::pick_tile(double bytes) {
     double best = 0.0;
     bool have = false;
     streams = (shapes_allowed & kR64Shapes) && bytes > 2e9;
-    const unsigned modelled = streams ? kR64Shapes : elem_bytes == 4 ? shapes_allowed & kDmaShapes : 0u;
+    const unsigned modelled = streams ? kR64Shapes : elem_bytes == 4 ? shapes_allowed & kQuadShapes : 0u;
     if (modelled) {
         for (int t = 0; t < kNumShapes; ++t) {
             if (!((modelled >> t) & 1u)) continue;
@@ -291,7 +296,7 @@ void GemmList::build_tiles() {
     ftiles.clear();
     bool single = !ta && !tb;
     for (const GemmItem &it : items) single = single && it.nseg <= 1;
-    if (!single || !(((kDmaShapes | kR64Shapes) >> (int)shape) & 1u)) return;
+    if (!single || !(((kDmaShapes | kR64Shapes | kQuadShapes) >> (int)shape) & 1u)) return;
     ftiles.reserve(tiles.size());
     for (const GemmTile &t : tiles) {
         FlatTile f{};
@@ -475,7 +480,13 @@ void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, hipStream_t
 
 void GemmList::launch(GemmPrec prec, bool c_is_f64, const Slots &sl, const GemmDev &dv, hipStream_t s) const {
     PD_REQUIRE(prec != GemmPrec::BF16X3 || !ftiles.empty() || tiles.empty(), PDMRG_EINVAL,
-               "gemm: BF16x3 needs an LDS-DMA plan (split operands)");
+               "gemm: BF16x3 needs an LDS-DMA or quad plan (split operands)");
+    if ((1u << (int)shape) & kQuadShapes) {
+        PD_REQUIRE(prec != GemmPrec::F64 && !c_is_f64 && (!ftiles.empty() || tiles.empty()), PDMRG_EINVAL,
+                   "gemm: the quad kernel is for FP32 and BF16x3 and one segment per item");
+        launch_gemm_quad(prec == GemmPrec::BF16X3, shape, sl, dv.ftiles, dv.rowoff, dv.epi, (int)ftiles.size(), s);
+        return;
+    }
     if ((1u << (int)shape) & kR64Shapes) {
         PD_REQUIRE(prec == GemmPrec::F64 && (!ftiles.empty() || tiles.empty()), PDMRG_EINVAL,
                    "gemm: the register-direct kernel is for FP64 and one segment per item");
@@ -797,9 +808,10 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
         }
 
     // tile shapes: both lists are non-transposed with one segment per item,
-    // so the LDS-DMA shapes apply; BF16x3 (split operands) runs only those
-    g1.shapes_allowed = g3.shapes_allowed = prec == PDMRG_BF16X3 ? kDmaShapes
-                                            : prec == PDMRG_F32  ? kStagedShapes | kDmaShapes
+    // so the LDS-DMA, register-direct and quad shapes apply; BF16x3 (split
+    // operands) runs only the first and the last
+    g1.shapes_allowed = g3.shapes_allowed = prec == PDMRG_BF16X3 ? kDmaShapes | kQuadShapes
+                                            : prec == PDMRG_F32  ? kStagedShapes | kDmaShapes | kQuadShapes
                                                                  : kStagedShapes | kDmaShapes | kR64Shapes;
     const double bytes = g1.operand_bytes() + g3.operand_bytes();
     g1.pick_tile(bytes);
@@ -816,10 +828,10 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
     int parts = default_parts(shape);
     if (lowp || g3.streams) {
         // The split and the shape together.  FP32 and BF16x3 split as far as K
-        // allows: stage 3 with its reduction at 2, 4, 8 parts takes 0.409, 0.415,
-        // 0.388 ms (BF16x3, tri 12 x 6, m = 3000), 0.126, 0.102, 0.096 (FP32, 24 x 8
-        // cylinder, m = 2000), 0.048, 0.036, 0.034 (BF16x3, 8 x 4, m = 1024).
-        const unsigned shapes = lowp ? kDmaShapes : kR64Shapes;
+        // allows: stage 3 with its reduction at 2, 4, 8 parts takes 0.365, 0.356,
+        // 0.335 ms (BF16x3, tri 12 x 6, m = 3000), 0.108, 0.093, 0.090 (FP32, 24 x 8
+        // cylinder, m = 2000), 0.037, 0.030, 0.032 (BF16x3, 8 x 4, m = 1024).
+        const unsigned shapes = lowp ? kQuadShapes : kR64Shapes;
         double best = 0.0;
         for (int p = lowp ? 8 : 1; p <= (lowp ? 8 : kMaxParts64); ++p)
             for (int t = 0; t < kNumShapes; ++t) {

@@ -37,10 +37,10 @@ def problem():
     return args, dev(blocks_to_flat(psi, tx, nx, pl.TWO_SITE)), blocks_to_flat(ref, tx, nx, pl.TWO_SITE)
 
 
-# staged 128 x 32 and 64 x 64 (half depth), 128 x 128 and full depth; LDS-DMA; register-direct
+# staged, LDS-DMA, register-direct and quad kernels
 @pytest.mark.parametrize("prec,shape", [("f64", s) for s in (None, 0, 1, 2, 3, 4, 5, 8, 9, 10, 11, 12, 13, 14)] +
-                         [("f32", s) for s in (None, 3, 4, 5, 6, 7, 8, 9, 10)] +
-                         [("bf16x3", s) for s in (None, 8, 9, 10)])
+                         [("f32", s) for s in (None, 3, 4, 5, 6, 7, 8, 9, 10, 15, 16, 17, 18)] +
+                         [("bf16x3", s) for s in (None, 8, 9, 10, 15, 16, 17, 18)])
 def test_one_term_blocks_from_stage_1(problem, prec, shape, tmp_path):
     """Sums of some 1e4 products of unit normals: 1e-13 in FP64, 1e-5 with FP32
     and BF16x3 operands, relative to the norm."""

@@ -1,8 +1,8 @@
-"""FP64 H_eff with the register-direct GEMM shapes at the edges of their tiles:
-bonds whose sectors are one row wide, odd, just under, at and over the 32 / 64 /
-128 boundaries of the wave and workgroup tiles and of the 8-deep K steps, forced
-through imported tuning entries, against the same contraction on dense NumPy
-blocks."""
+"""H_eff with the register-direct (FP64) and quad (FP32, BF16x3) GEMM shapes at the
+edges of their tiles: bonds whose sectors are one row wide, odd, just under, at
+and over the 16 / 32 / 64 / 128 boundaries of the wave and workgroup tiles and
+of the K steps, forced through imported tuning entries, against the same
+contraction on dense NumPy blocks."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,10 @@ from oracle.blocks import Bond
 
 pytestmark = pytest.mark.gpu
 PQ = (-1, 1)
-NAMES = {11: "64x64reg", 12: "128x64reg", 13: "64x128reg", 14: "128x128reg"}
+NAMES = {11: "64x64reg", 12: "128x64reg", 13: "64x128reg", 14: "128x128reg",
+         15: "64x64quad", 16: "128x64quad", 17: "64x64quad32", 18: "128x64quad32"}
+PLANS = [("f64", s, p) for s in (11, 12, 13, 14) for p in (1, 16)] + \
+    [(t, s, p) for t in ("f32", "bf16x3") for s in (15, 16, 17, 18) for p in (1, 8)]
 SITE = 5
 
 # (left bond, right bond) of a two-site problem
@@ -30,12 +33,11 @@ def mpo():
     return M.build_mpo(models.heisenberg_terms(models.square_cylinder_bonds(3, 4)), 12, models.OPS, PQ)
 
 
-@pytest.mark.parametrize("parts", [1, 16])
-@pytest.mark.parametrize("shape", sorted(NAMES))
+@pytest.mark.parametrize("prec,shape,parts", PLANS)
 @pytest.mark.parametrize("case", range(len(BONDS)))
-def test_heff_f64_register_direct_shapes(mpo, case, shape, parts, tmp_path):
-    """FP64 sums of at most a few thousand terms: 1e-13 relative.  x, the
-    environments and y lie inside buffers of NaN: a value read past an operand
+def test_heff_tile_edges(mpo, case, prec, shape, parts, tmp_path):
+    """Sums of at most a few thousand terms: 1e-13 relative in FP64, 1e-5 with
+    FP32 and BF16x3 operands.  x, the environments and y lie inside buffers of NaN: a value read past an operand
     that reached a product would make the result NaN."""
     import torch
     bl, br = BONDS[case]
@@ -58,12 +60,12 @@ def test_heff_f64_register_direct_shapes(mpo, case, shape, parts, tmp_path):
 
     ctx = pl.Context(0)
     pl.set_autotune(ctx, 1)
-    args = (ctx, B1, B2, P, mpo_site(mpo, SITE), mpo_site(mpo, SITE + 1), Ld, Rd, pl.F64)
+    args = (ctx, B1, B2, P, mpo_site(mpo, SITE), mpo_site(mpo, SITE + 1), Ld, Rd, pl.PREC_NAMES[prec])
     pl.Heff(*args).free()                                   # creates this operator's entry
     f = tmp_path / "plans.tsv"
     pl.autotune_export(str(f))
     keys = [r.split("\t")[0] for r in f.read_text().splitlines() if r]
-    f.write_text("".join("%s\t%d\t%d\t%d\n" % (k, shape, shape, parts) for k in keys if k.split("|")[1] == str(pl.F64)))
+    f.write_text("".join("%s\t%d\t%d\t%d\n" % (k, shape, shape, parts) for k in keys if k.split("|")[1] == str(pl.PREC_NAMES[prec])))
     pl.autotune_import(str(f))
     op = pl.Heff(*args)
     info = op.info()
@@ -75,6 +77,6 @@ def test_heff_f64_register_direct_shapes(mpo, case, shape, parts, tmp_path):
     ref = dmrg.heff_apply(L, R, mpo.W[SITE], mpo.W[SITE + 1], psi, Bond(bl), Bond(br), PQ, dl, dr)
     ref = blocks_to_flat(ref, tx, nx, pl.TWO_SITE)
     assert np.all(np.isfinite(got))
-    assert np.linalg.norm(got - ref) <= 1e-13 * np.linalg.norm(ref)
+    assert np.linalg.norm(got - ref) <= (1e-13 if prec == "f64" else 1e-5) * np.linalg.norm(ref)
     gap = pool[32 + nx - 16:32 + nx]                        # around y, still untouched
     assert bool(torch.isnan(gap).all()) and bool(torch.isnan(pool[32 + 2 * nx:48 + 2 * nx]).all())
