@@ -951,10 +951,8 @@ def main():
     achieved = stage_flops / (r["ms"][st] * 1e-3) / 1e12
     peak = PEAK_TFLOPS[args.prec]
     shape = info["shape_Lpsi"] if st == 0 else info["shape_R"]
-    if args.prec == "bf16x3":
-        kname = "gemm_bf16x3"
-    else:
-        kname = "gemm_dma" if shape.endswith("dma") else "gemm_kmajor"
+    kname = "gemm_quad" if "quad" in shape else "gemm_dma" if shape.endswith("dma") else \
+        "gemm_r64" if shape.endswith("reg") else "gemm_kmajor"
     traffic = stored_traffic(args.prec, st, {k: info[k] for k in ("shape_Lpsi", "shape_R", "splitk_parts")})
     out = {
         "metric": "H_eff matvec TFLOP/s (% MFMA peak); sweep s, mixed vs FP64 at 1e-9 rel E",
