@@ -661,20 +661,38 @@ void launch_dav_g_scatter(double *G, int ld, int k, const double *dots, bool exa
 // (J^T A).  One wave64; k <= 64.
 constexpr int SE_MAX = 64;
 
-__global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, int ld, double *theta_out,
-                                                       double *c_out) {
-    __shared__ double A[SE_MAX][SE_MAX + 1];
-    __shared__ double V[SE_MAX][SE_MAX + 1];
-    __shared__ double rc[SE_MAX / 2], rs[SE_MAX / 2];
-    __shared__ int rp[SE_MAX / 2], rq[SE_MAX / 2];
-    __shared__ double red[64];
-    const int l = threadIdx.x;
+template <int M>
+struct SmallEig {
+    double A[M][M + 1], V[M][M + 1];
+    double rc[M / 2], rs[M / 2];
+    int rp[M / 2], rq[M / 2];
+    double red[64];
+};
+
+// LDS written by one lane of a wave, read by another of the same wave.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// k <= M; called by one whole wave, l = its lane.
+template <int M>
+__device__ __forceinline__ void small_eig(SmallEig<M> &L, const double *G, int k, int ld, int l, double *theta_out,
+                                          double *c_out) {
+    auto &A = L.A;
+    auto &V = L.V;
+    auto &rc = L.rc;
+    auto &rs = L.rs;
+    auto &rp = L.rp;
+    auto &rq = L.rq;
+    auto &red = L.red;
     for (int i = 0; i < k; ++i)
         for (int j = l; j < k; j += 64) {
             A[i][j] = 0.5 * (G[i * ld + j] + G[j * ld + i]);
             V[i][j] = (i == j) ? 1.0 : 0.0;
         }
-    __syncthreads();
+    wave_sync();
     const int n = (k % 2) ? k + 1 : k;   // players, one dummy if k is odd
     for (int sweep = 0; sweep < 60; ++sweep) {
         double off = 0.0, dia = 0.0;
@@ -684,25 +702,25 @@ __global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, i
                 else dia += A[i][j] * A[i][j];
             }
         red[l] = off;
-        __syncthreads();
+        wave_sync();
         if (l == 0) {
             double so = 0.0;
-            for (int i = 0; i < 64; ++i) so += red[i];
+            for (int i = 0; i < k; ++i) so += red[i];   // the other lanes hold zeros
             red[0] = so;
         }
-        __syncthreads();
+        wave_sync();
         const double soff = red[0];
-        __syncthreads();
+        wave_sync();
         red[l] = dia;
-        __syncthreads();
+        wave_sync();
         if (l == 0) {
             double sd = 0.0;
-            for (int i = 0; i < 64; ++i) sd += red[i];
+            for (int i = 0; i < k; ++i) sd += red[i];
             red[0] = sd;
         }
-        __syncthreads();
+        wave_sync();
         const double sdia = red[0];
-        __syncthreads();
+        wave_sync();
         if (soff <= 1e-30 * sdia || soff == 0.0) break;
         for (int r = 0; r < n - 1; ++r) {
             if (l < n / 2) {
@@ -718,7 +736,7 @@ __global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, i
                 }
                 rp[l] = p; rq[l] = q; rc[l] = c; rs[l] = s;
             }
-            __syncthreads();
+            wave_sync();
             // columns: A J and V J
             for (int e = l; e < (n / 2) * k; e += 64) {
                 const int pr = e / k, i = e % k;
@@ -732,7 +750,7 @@ __global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, i
                 V[i][p] = c * vp - s * vq;
                 V[i][q] = s * vp + c * vq;
             }
-            __syncthreads();
+            wave_sync();
             // rows: J^T A
             for (int e = l; e < (n / 2) * k; e += 64) {
                 const int pr = e / k, j = e % k;
@@ -743,7 +761,7 @@ __global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, i
                 A[p][j] = c * ap - s * aq;
                 A[q][j] = s * ap + c * aq;
             }
-            __syncthreads();
+            wave_sync();
         }
     }
     if (l == 0) {
@@ -754,15 +772,170 @@ __global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, i
         red[1] = (V[0][best] < 0.0) ? -1.0 : 1.0;
         rp[0] = best;
     }
-    __syncthreads();
+    wave_sync();
     const int best = rp[0];
     const double sg = red[1];
     for (int i = l; i < k; i += 64) c_out[i] = sg * V[i][best];
     if (l == 0) theta_out[0] = red[0];
 }
 
+__global__ __launch_bounds__(64) void small_eig_kernel(const double *G, int k, int ld, double *theta_out,
+                                                       double *c_out) {
+    __shared__ SmallEig<SE_MAX> L;
+    small_eig<SE_MAX>(L, G, k, ld, threadIdx.x, theta_out, c_out);
+}
+
 void launch_small_eig(const double *G, int k, int ld, double *theta_out, double *c_out, hipStream_t s) {
     hipLaunchKernelGGL(small_eig_kernel, dim3(1), dim3(64), 0, s, G, k, ld, theta_out, c_out);
+}
+
+// ------------------------------------------------------------ whole Davidson step, short vectors
+// One workgroup does what ext_gram, g_scatter, small_eig, ritz, sub_dot (twice)
+// and their four reductions do in ten launches of 1024 blocks, which on short
+// vectors cost 60 us a step of launches, almost empty blocks and their trees
+// whatever n is.  What bounds it: small_eig's chain (some 8 us) and the passes
+// over the vectors, 8 k n words through one CU's path to L2 (about 60 bytes a
+// ns).  A Davidson run of 3 / 12 products, whole call: n = 14 246 -> 147 / 1146
+// -> 679 us, n = 1818 272 -> 176 / 1263 -> 895, n = 3224 278 -> 197 / 1280 ->
+// 1035.  The basis held in registers spills at four elements a thread (246 /
+// 1176 us); four vectors' loads at a time were slower (219 / 1105), as were
+// lane exchanges through LDS (210 / 1096).
+// The same bits: the elements stay in 1024 chunks of c = ceil(n / 1024), GL = 2^j
+// >= c lanes a chunk; a chunk's sum is the tree over its lanes that a wave of
+// block_store_sums forms (there the lanes past c add zeros), and the chunks' sums
+// are added as in reduce_partials_kernel.
+// v of the lane O further on in this row of 16 lanes (past its end: 0).
+template <int O>
+__device__ __forceinline__ double row_down(double v) {
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    const i2 b = __builtin_bit_cast(i2, v);
+    return __builtin_bit_cast(double, i2{__builtin_amdgcn_update_dpp(0, b.x, 0x100 + O, 0xf, 0xf, true),
+                                         __builtin_amdgcn_update_dpp(0, b.y, 0x100 + O, 0xf, 0xf, true)});
+}
+constexpr int kStepOut = 8;   // sums whose chunk values are in LDS at a time
+template <int GL>
+__global__ __launch_bounds__(1024) void dav_step_kernel(const double *__restrict__ V, const double *__restrict__ HV,
+                                                        int n, int k, double *G, int ldg, int exact_row,
+                                                        const double *__restrict__ diag, double *__restrict__ X,
+                                                        double *__restrict__ HX, double *__restrict__ T,
+                                                        double *scal) {
+    __shared__ double P[kStepOut][kDavChunks];
+    __shared__ double S[2 * kDavFused + 2];
+    __shared__ double cc[kDavFused], theta[1];
+    __shared__ SmallEig<kDavFused> E;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, e = tid & (GL - 1);
+    const int c = (n + kDavChunks - 1) / kDavChunks;
+    // element of this thread in pass u (chunk (u 1024 + tid) / GL), -1: none
+    auto at = [&](int u) {
+        const int i = (u * 1024 + tid) / GL * c + e;
+        return e < c && i < n ? i : -1;
+    };
+    auto chunk_sum = [&](double x, int v, int u) {
+#pragma clang fp contract(off)   // a product given as x is rounded before it is added to
+        if (GL > 2) x += row_down<2>(x);
+        if (GL > 1) x += row_down<1>(x);
+        if (e == 0) P[v][(u * 1024 + tid) / GL] = x;
+    };
+    // S[v] = sum of the chunk values of val(v, u, i), v < nout; output 0 is in P already if pre
+    auto sums = [&](int nout, bool pre, auto val) {
+        for (int v0 = 0; v0 < nout; v0 += kStepOut) {
+            const int v1 = min(nout, v0 + kStepOut);
+            for (int v = v0 + (pre && v0 == 0 ? 1 : 0); v < v1; ++v)
+#pragma unroll
+                for (int u = 0; u < GL; ++u) {
+                    const int i = at(u);
+                    chunk_sum(i >= 0 ? val(v, u, i) : 0.0, v - v0, u);
+                }
+            __syncthreads();
+            if (wave < v1 - v0) {
+                double q[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double *p = &P[wave][64 * j + lane];
+                    q[j] = (((0.0 + p[0]) + p[256]) + p[512]) + p[768];
+                }
+                double x = (q[0] + q[2]) + (q[1] + q[3]);
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+                if (lane == 0) S[v0 + wave] = x;
+            }
+            __syncthreads();
+        }
+    };
+    // row and column of vector k - 1 of the projected matrix
+    const int k0 = k - 1;
+    const double *vk = V + (int64_t)k0 * n, *hk = HV + (int64_t)k0 * n;
+    sums(2 * k0 + 1, false, [&](int v, int, int i) {
+        return v <= k0 ? V[(int64_t)v * n + i] * hk[i] : HV[(int64_t)(v - k0 - 1) * n + i] * vk[i];
+    });
+    if (tid <= k0) G[tid * ldg + k0] = exact_row && k0 > 0 && tid == 0 ? S[k0 + 1] : S[tid];
+    if (tid < k0) G[k0 * ldg + tid] = S[k0 + 1 + tid];
+    __syncthreads();
+    if (wave == 0) small_eig<kDavFused>(E, G, k, ldg, lane, theta, cc);
+    __syncthreads();
+    // Ritz vector, residual, preconditioned correction t
+    const double th = theta[0];
+    double t[GL];
+#pragma unroll
+    for (int u = 0; u < GL; ++u) {
+        const int i = at(u);
+        double rr = 0.0;
+        t[u] = 0.0;
+        if (i >= 0) {
+            double x = 0.0, hx = 0.0;
+            for (int v = 0; v < k; ++v) {
+                x += cc[v] * V[(int64_t)v * n + i];
+                hx += cc[v] * HV[(int64_t)v * n + i];
+            }
+            const double r = hx - th * x;
+            double den = diag[i] - th;
+            if (fabs(den) < 1e-8) den = copysign(1e-8, den);
+            t[u] = r / den;
+            X[i] = x;
+            HX[i] = hx;
+            rr = r * r;
+        }
+        chunk_sum(rr, 0, u);
+    }
+    // t orthogonalised twice against the basis
+    auto project = [&](int first) {   // t -= sum_v S[first + v] V_v
+#pragma unroll
+        for (int u = 0; u < GL; ++u) {
+            const int i = at(u);
+            if (i < 0) continue;
+            double a = 0.0;
+            for (int v = 0; v < k; ++v) a += S[first + v] * V[(int64_t)v * n + i];
+            t[u] = t[u] - a;
+        }
+    };
+    sums(k + 1, true, [&](int v, int u, int i) { return V[(int64_t)(v - 1) * n + i] * t[u]; });
+    if (tid == 0) {
+        scal[0] = th;
+        scal[1] = S[0];
+    }
+    project(1);
+    sums(k, false, [&](int v, int u, int i) { return V[(int64_t)v * n + i] * t[u]; });
+    project(0);
+    sums(1, false, [&](int, int u, int) { return t[u] * t[u]; });
+    if (tid == 0) scal[2] = S[0];
+#pragma unroll
+    for (int u = 0; u < GL; ++u) {
+        const int i = at(u);
+        if (i >= 0) T[i] = t[u];
+    }
+}
+
+void launch_dav_step(const double *V, const double *HV, int64_t n, int k, double *G, int ldg, bool exact_row,
+                     const double *diag, double *x, double *hx, double *t, double *scal, hipStream_t s) {
+    if (k < 1 || k > kDavFused || n < 1 || n > kDavShort) throw std::invalid_argument("dav_step: k or n out of range");
+    const int64_t c = (n + kDavChunks - 1) / kDavChunks;
+#define DAV_STEP(GL) \
+    hipLaunchKernelGGL(dav_step_kernel<GL>, dim3(1), dim3(1024), 0, s, V, HV, (int)n, k, G, ldg, (int)exact_row, diag, \
+                       x, hx, t, scal)
+    if (c <= 1) DAV_STEP(1);
+    else if (c <= 2) DAV_STEP(2);
+    else DAV_STEP(4);
+#undef DAV_STEP
 }
 
 // ------------------------------------------------------------ local measurements

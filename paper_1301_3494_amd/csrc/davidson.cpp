@@ -31,7 +31,7 @@ struct DavWs {
                       // passes reduce [rr, V_0.t, ..] into 1 .. k + 1
     double *partial;  // [nblk][ks]
 };
-constexpr int kBlk = 1024;   // blocks of the reduction passes (4 per CU: memory parallelism)
+constexpr int kBlk = kDavChunks;   // blocks of the reduction passes (4 per CU: memory parallelism)
 constexpr int kScal = 8 + kDavFused + 2;
 }  // namespace
 
@@ -67,6 +67,10 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
     // subspaces of up to kDavFused vectors take the fused passes (one read of
     // each vector per pass, fewer launches); larger ones the separate kernels
     const bool fused = ks <= kDavFused;
+    // Short vectors: all of a step's passes in one workgroup.  One CU's rate ends
+    // it: at n = 6220 a run of 12 products takes 1336 us against 1287 with the
+    // passes apart (3 products: 244 against 286), at n = 3224 1035 against 1280.
+    const bool whole = fused && n <= kDavShort;
 
     auto dot_into = [&](const double *U, int nv, const double *x, double *out, int stride = 1) {
         launch_multidot(U, n, nv, x, n, w.partial, kBlk, s);
@@ -103,8 +107,13 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
 
     // Ritz pair of the k-vector basis, residual r (|r|^2 -> scal[1]),
     // preconditioned correction t orthogonalised twice against V
-    // (|t|^2 -> scal[2]); theta -> scal[0], x, hx
+    // (|t|^2 -> scal[2]); theta -> scal[0], x, hx.  With `whole` also row and
+    // column k - 1 of G, which extend_G has written otherwise.
     auto ritz_step = [&](int k) {
+        if (whole) {
+            launch_dav_step(w.V, w.HV, n, k, w.G, ks, refine, diag, w.X, w.HX, w.t, w.scal, s);
+            return;
+        }
         launch_small_eig(w.G, k, ks, w.scal + 0, w.c, s);
         if (fused) {
             launch_dav_ritz(w.V, w.HV, n, k, w.c, w.scal + 0, diag, w.X, w.HX, w.r, w.t, n, w.partial, kBlk, s);
@@ -129,7 +138,7 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
     launch_scale_by_inv_sqrt(psi, w.scal + 3, w.V, n, s);
     matvec(refine ? op64 : op, w.V, w.HV);
     int k = 1;
-    extend_G(0);
+    if (!whole) extend_G(0);
 
     double host[3] = {0, 0, 0};
     double theta = 0, rn = 0;
@@ -161,7 +170,7 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
                 launch_scale_by_inv_sqrt(w.X, w.scal + 3, w.V, n, s);
                 matvec(op64, w.V, w.HV);
                 k = 1;
-                extend_G(0);
+                if (!whole) extend_G(0);
                 ritz_step(1);   // x = V0 (c = 1), hx = HV0
                 read_back({{host, w.scal, 3 * sizeof(double)}}, s);
                 theta = host[0];
@@ -175,7 +184,7 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
         // append t / |t|
         launch_scale_by_inv_sqrt(w.t, w.scal + 2, w.V + (size_t)k * n, n, s);
         matvec(op, w.V + (size_t)k * n, w.HV + (size_t)k * n);
-        extend_G(k);
+        if (!whole) extend_G(k);
         ++k;
     }
     // psi <- x / |x|

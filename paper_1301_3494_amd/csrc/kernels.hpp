@@ -284,6 +284,13 @@ int dav_ext_gram_width(int k);
 void launch_dav_ext_gram(const double *V, const double *HV, int64_t ldv, int k, int64_t n, double *partial,
                          int nblk, hipStream_t s);
 void launch_dav_g_scatter(double *G, int ld, int k, const double *dots, bool exact_row, hipStream_t s);
+// All of a step's passes in one workgroup, for n <= kDavShort: row and column k -
+// 1 of G (as ext_gram and g_scatter), the lowest eigenpair of its k rows, ritz,
+// both projections and |t|^2; scal = [theta, r.r, t.t].  The same bits as the
+// passes with kDavChunks blocks.
+constexpr int kDavChunks = 1024, kDavShort = 4 * kDavChunks;
+void launch_dav_step(const double *V, const double *HV, int64_t n, int k, double *G, int ldg, bool exact_row,
+                     const double *diag, double *x, double *hx, double *t, double *scal, hipStream_t s);
 // Lowest eigenpair of the k x k symmetric matrix G (row-major, ld) by cyclic
 // Jacobi in one workgroup: theta_out[0] = eigenvalue, c_out[0..k) eigenvector
 // with c[0] >= 0.
