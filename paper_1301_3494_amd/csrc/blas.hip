@@ -483,19 +483,41 @@ void launch_scale_by_inv_sqrt(const double *x, const double *nrm2, double *y, in
 }
 
 // ------------------------------------------------------------ fused Davidson passes
-// Block b owns the contiguous element range [b chunk, (b + 1) chunk); every
-// thread keeps one running sum per output, then the sums of a block are
-// reduced in a fixed order (lanes by xor-shuffle, the 4 waves in LDS).
-template <int NO>
-__device__ __forceinline__ void block_store_sums(double (&acc)[NO], int nout, double *row) {
+// v of the lane O further on in this row of 16 lanes (past its end: 0).
+template <int O>
+__device__ __forceinline__ double row_down(double v) {
+    typedef int i2 __attribute__((ext_vector_type(2)));
+    const i2 b = __builtin_bit_cast(i2, v);
+    return __builtin_bit_cast(double, i2{__builtin_amdgcn_update_dpp(0, b.x, 0x100 + O, 0xf, 0xf, true),
+                                         __builtin_amdgcn_update_dpp(0, b.y, 0x100 + O, 0xf, 0xf, true)});
+}
+
+// Block b owns the contiguous element range [b chunk, (b + 1) chunk) of nel
+// elements; every thread keeps one running sum per output, then the sums of a
+// block are reduced in a fixed order (a tree over the lanes, of which only lane
+// 0's branch is needed, and the 4 waves in LDS).  Waves without elements and
+// outputs that are zero by construction (used(v) false) skip the tree.  On short
+// ranges the trees are most of a block's time, and lane exchanges through LDS
+// most of a tree's; with the last four steps in the VALU four products of a run
+// took 1029 us instead of 1070 (n = 586150), twelve 1184 instead of 1273 (n =
+// 6220) and 1692 instead of 1813 (n = 147122).
+template <int NO, class Used>
+__device__ __forceinline__ void block_store_sums(double (&acc)[NO], int nout, int nel, double *row, Used used) {
     __shared__ double sh[4][NO];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int v = 0; v < NO; ++v) {
         if (v < nout) {   // uniform over the block
-            double x = acc[v];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+            double x = 0.0;
+            if (64 * wave < nel && used(v)) {
+                x = acc[v];
+                x += __shfl_xor(x, 32);
+                x += __shfl_xor(x, 16);
+                x += row_down<8>(x);
+                x += row_down<4>(x);
+                x += row_down<2>(x);
+                x += row_down<1>(x);
+            }
             if (lane == 0) sh[wave][v] = x;
         }
     }
@@ -551,7 +573,8 @@ __global__ __launch_bounds__(256) void dav_ritz_kernel(const double *__restrict_
         for (int v = 0; v < KM; ++v)
             if (v < k) acc[v + 1] += vv[v] * t;
     }
-    block_store_sums<KM + 1>(acc, k + 1, partial + (int64_t)blockIdx.x * (k + 1));
+    block_store_sums<KM + 1>(acc, k + 1, (int)min(i1 - i0, (int64_t)256), partial + (int64_t)blockIdx.x * (k + 1),
+                             [](int) { return true; });
 }
 
 template <int KM>
@@ -585,7 +608,8 @@ __global__ __launch_bounds__(256) void dav_sub_dot_kernel(const double *__restri
         }
     }
     const int nout = with_dots ? k : 1;
-    block_store_sums<KM>(acc, nout, partial + (int64_t)blockIdx.x * nout);
+    block_store_sums<KM>(acc, nout, (int)min(i1 - i0, (int64_t)256), partial + (int64_t)blockIdx.x * nout,
+                         [](int) { return true; });
 }
 
 template <int KM>
@@ -608,7 +632,9 @@ __global__ __launch_bounds__(256) void dav_ext_gram_kernel(const double *__restr
         acc[KM] += vk * hk;
     }
     // row of 2 KM + 1 sums: [V_v.HV_k (v < k) ..., V_k.HV_k at KM, HV_v.V_k at KM + 1 + v]
-    block_store_sums<2 * KM + 1>(acc, 2 * KM + 1, partial + (int64_t)blockIdx.x * (2 * KM + 1));
+    block_store_sums<2 * KM + 1>(acc, 2 * KM + 1, (int)min(i1 - i0, (int64_t)256),
+                                 partial + (int64_t)blockIdx.x * (2 * KM + 1),
+                                 [&](int v) { return v < k || v == KM || (v > KM && v - KM - 1 < k); });
 }
 
 __global__ void dav_g_scatter_kernel(double *G, int ld, int k, int km, const double *dots, int exact_row) {
@@ -792,26 +818,18 @@ void launch_small_eig(const double *G, int k, int ld, double *theta_out, double 
 // ------------------------------------------------------------ whole Davidson step, short vectors
 // One workgroup does what ext_gram, g_scatter, small_eig, ritz, sub_dot (twice)
 // and their four reductions do in ten launches of 1024 blocks, which on short
-// vectors cost 60 us a step of launches, almost empty blocks and their trees
-// whatever n is.  What bounds it: small_eig's chain (some 8 us) and the passes
+// vectors cost some 50 us a step of launches and almost empty blocks whatever n
+// is.  What bounds it: small_eig's chain (some 8 us) and the passes
 // over the vectors, 8 k n words through one CU's path to L2 (about 60 bytes a
-// ns).  A Davidson run of 3 / 12 products, whole call: n = 14 246 -> 147 / 1146
-// -> 679 us, n = 1818 272 -> 176 / 1263 -> 895, n = 3224 278 -> 197 / 1280 ->
-// 1035.  The basis held in registers spills at four elements a thread (246 /
+// ns).  A Davidson run of 3 / 12 products, whole call, against the launches:
+// n = 196 161 us against 257 / 717 against 1071, n = 1818 180 against 258 / 903
+// against 1157, n = 3224 202 against 260 / 1048 against 1172.  The basis held in registers spills at four elements a thread (246 /
 // 1176 us); four vectors' loads at a time were slower (219 / 1105), as were
 // lane exchanges through LDS (210 / 1096).
 // The same bits: the elements stay in 1024 chunks of c = ceil(n / 1024), GL = 2^j
 // >= c lanes a chunk; a chunk's sum is the tree over its lanes that a wave of
 // block_store_sums forms (there the lanes past c add zeros), and the chunks' sums
 // are added as in reduce_partials_kernel.
-// v of the lane O further on in this row of 16 lanes (past its end: 0).
-template <int O>
-__device__ __forceinline__ double row_down(double v) {
-    typedef int i2 __attribute__((ext_vector_type(2)));
-    const i2 b = __builtin_bit_cast(i2, v);
-    return __builtin_bit_cast(double, i2{__builtin_amdgcn_update_dpp(0, b.x, 0x100 + O, 0xf, 0xf, true),
-                                         __builtin_amdgcn_update_dpp(0, b.y, 0x100 + O, 0xf, 0xf, true)});
-}
 constexpr int kStepOut = 8;   // sums whose chunk values are in LDS at a time
 template <int GL>
 __global__ __launch_bounds__(1024) void dav_step_kernel(const double *__restrict__ V, const double *__restrict__ HV,
