@@ -173,13 +173,15 @@ private:
 };
 // Device memory of lists that live within one call and are read on one stream:
 // on release it is free at once for the next list on that stream (which is
-// written behind the kernels that read this one).
+// written behind the kernels that read this one).  Lists larger than the pool's
+// blocks, and those on hipStreamPerThread (one handle, a stream per thread), are
+// DevBufs.
 struct ListBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
     int dev = 0;
     hipStream_t s = nullptr;
-    DevBuf large;   // lists past the pool's largest block
+    DevBuf large;   // what is not from the pool
     ListBuf() = default;
     ~ListBuf() { release(); }
     ListBuf(const ListBuf &) = delete;

@@ -397,7 +397,9 @@ void ListBuf::ensure(size_t n, hipStream_t stream) {
     HIP_OK(hipGetDevice(&d));
     size_t cls = size_t(4) << 10;
     while (cls < n) cls <<= 1;
-    if (cls > kListBlock) {
+    // hipStreamPerThread is one handle for as many streams as there are threads:
+    // a block freed on one is not ordered before the list copies of another
+    if (cls > kListBlock || stream == hipStreamPerThread) {
         large.ensure(n);
         ptr = large.ptr;
         bytes = large.bytes;

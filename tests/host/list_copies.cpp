@@ -1,0 +1,190 @@
+// Host checks of the list and result copies of csrc/layout.cpp on a stand-in
+// for the HIP runtime: device memory is host memory, and what is launched on a
+// stream waits in that stream's queue until the check runs it, so every order
+// that the real streams allow can be tried.  hipStreamPerThread stands for a
+// queue of each thread, as in the runtime.  One check per run: argv[1].
+#include "../../paper_1301_3494_amd/csrc/common.hpp"
+#include "../../paper_1301_3494_amd/csrc/kernels.hpp"
+
+#include <cstdio>
+#include <cstdlib>
+#include <deque>
+#include <set>
+
+using namespace pdmrg;
+
+// ---------------------------------------------------------------- the stand-in
+namespace {
+using Queue = std::deque<std::function<void()>>;
+std::mutex g_mu;
+std::map<std::pair<hipStream_t, std::thread::id>, Queue> g_queues;
+std::set<void *> g_device, g_pinned;   // live allocations
+
+Queue &queue(hipStream_t s) {
+    return g_queues[{s, s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()}];
+}
+void push(hipStream_t s, std::function<void()> f) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    queue(s).push_back(std::move(f));
+}
+void run_one(Queue &q) {
+    if (q.empty()) return;
+    auto f = std::move(q.front());
+    q.pop_front();
+    f();
+}
+void run_all(Queue &q) {
+    while (!q.empty()) run_one(q);
+}
+struct Event {
+    bool recorded = false, passed = true;
+};
+
+#define CHECK(c)                                                                   \
+    do {                                                                           \
+        if (!(c)) {                                                                \
+            std::printf("%s:%d: %s\n", __FILE__, __LINE__, #c);                    \
+            std::exit(1);                                                          \
+        }                                                                          \
+    } while (0)
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_device.insert(*p = std::malloc(n));
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() {
+    std::lock_guard<std::mutex> lk(g_mu);
+    for (auto &q : g_queues) run_all(q.second);
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    (void)hipDeviceSynchronize();
+    std::lock_guard<std::mutex> lk(g_mu);
+    CHECK(g_device.erase(p) == 1);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_pinned.insert(*p = std::malloc(n));
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    CHECK(g_pinned.erase(p) == 1);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    *e = reinterpret_cast<hipEvent_t>(new Event());
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e) { delete reinterpret_cast<Event *>(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    auto *ev = reinterpret_cast<Event *>(e);
+    ev->passed = false;
+    push(s, [ev] { ev->passed = true; });
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) { return reinterpret_cast<Event *>(e)->passed ? hipSuccess : hipErrorNotReady; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipDeviceSynchronize(); }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    run_all(queue(s));
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
+    push(s, [=] { std::memcpy(dst, src, n); });
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "stand-in error"; }
+}
+
+namespace pdmrg {
+void launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+    push(s, [=] { std::memcpy(dst, src, n); });
+}
+}  // namespace pdmrg
+
+// ---------------------------------------------------------------- the checks
+namespace {
+// A "kernel" on s that reads the list behind `list` into `out`.
+void launch_reader(const int *list, std::vector<int> &out, hipStream_t s) {
+    push(s, [=, &out] { std::copy(list, list + out.size(), out.begin()); });
+}
+
+// Two threads with a context each on hipStreamPerThread: one thread's list is
+// released once its kernel is launched, the other's copy runs between the first
+// one's copy and kernel.
+void per_thread_streams() {
+    StageHold hold;
+    const hipStream_t s = hipStreamPerThread;
+    std::vector<int> list_a(100, 1), list_b(100, 2), seen_a(100), seen_b(100);
+    {
+        ListBuf d;
+        upload_list(d, list_a, s);
+        launch_reader(d.as<int>(), seen_a, s);
+    }
+    run_one(queue(s));   // A's copy
+    std::thread b([&] {
+        ListBuf d;
+        upload_list(d, list_b, s);
+        launch_reader(d.as<int>(), seen_b, s);
+        CHECK(hipStreamSynchronize(s) == hipSuccess);
+    });
+    b.join();
+    CHECK(hipStreamSynchronize(s) == hipSuccess);   // A's kernel
+    CHECK(seen_a == list_a && seen_b == list_b);
+}
+
+// The same on ordinary streams: the block of a released list goes to the next
+// list on its stream and to no other stream's.
+void ordinary_streams() {
+    StageHold hold;
+    int h1, h2;
+    const auto s1 = reinterpret_cast<hipStream_t>(&h1), s2 = reinterpret_cast<hipStream_t>(&h2);
+    std::vector<int> a(100, 1), b(100, 2), c(100, 3), seen_a(100), seen_b(100), seen_c(100);
+    void *pa, *pb, *pc;
+    {
+        ListBuf d;
+        upload_list(d, a, s1);
+        pa = d.ptr;
+        launch_reader(d.as<int>(), seen_a, s1);
+    }
+    {
+        ListBuf d;
+        upload_list(d, b, s2);
+        pb = d.ptr;
+        launch_reader(d.as<int>(), seen_b, s2);
+    }
+    run_all(queue(s2));
+    {
+        ListBuf d;
+        upload_list(d, c, s1);
+        pc = d.ptr;
+        launch_reader(d.as<int>(), seen_c, s1);
+    }
+    run_all(queue(s1));
+    CHECK(pa != pb && pa == pc);
+    CHECK(seen_a == a && seen_b == b && seen_c == c);
+}
+}  // namespace
+
+int main(int argc, char **argv) {
+    const std::map<std::string, void (*)()> checks = {
+        {"per_thread_streams", per_thread_streams},
+        {"ordinary_streams", ordinary_streams},
+    };
+    const auto it = checks.find(argc > 1 ? argv[1] : "");
+    CHECK(it != checks.end());
+    it->second();
+    std::printf("ok\n");
+    return 0;
+}
