@@ -626,7 +626,7 @@ __global__ __launch_bounds__(256) void jac_begin_kernel(const JacItem *__restric
                                                         const JacTask *__restrict__ tasks,
                                                         const int32_t *__restrict__ active,
                                                         unsigned long long *__restrict__ offmax) {
-    __shared__ double dr[64], dc[64], red[4];
+    __shared__ double d[2][64], f[2][64], red[4];   // norms^2 of the block's rows and columns, 1 / norm
     const JacTask tk = tasks[blockIdx.x];
     const JacItem it = items[tk.item];
     if (!active[tk.item]) return;
@@ -636,19 +636,21 @@ __global__ __launch_bounds__(256) void jac_begin_kernel(const JacItem *__restric
     double v[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) v[u] = G[(int64_t)(r0 + 4 * u + (tid >> 6)) * it.np + c0 + (tid & 63)];
-    if (tid < 128) {   // 1 / norm of the block's rows and columns (0: absent or zero)
+    if (tid < 128) {   // 0: absent or zero
         const int r = (tid < 64 ? r0 : c0 - 64) + tid;
-        const double d = r < it.nv ? G[(int64_t)r * it.np + r] : 0.0;
-        const double f = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
-        if (tid < 64) dr[tid] = f;
-        else dc[tid - 64] = f;
+        const double g = r < it.nv ? G[(int64_t)r * it.np + r] : 0.0;
+        d[tid >> 6][tid & 63] = g;
+        f[tid >> 6][tid & 63] = g > 0.0 ? 1.0 / sqrt(g) : 0.0;
     }
     __syncthreads();
     double off = 0.0;
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int i = 4 * u + (tid >> 6), j = tid & 63;
-        if (r0 + i < c0 + j) off = fmax(off, fabs(v[u]) * dr[i] * dc[j]);
+        // what eig_sweep would rotate (none where the product of the norms leaves
+        // the range: rows that small or large count as orthogonal)
+        const double dd = d[0][i] * d[1][j];
+        if (r0 + i < c0 + j && dd > 0.0 && v[u] * v[u] > it.tol * it.tol * dd) off = fmax(off, fabs(v[u]) * f[0][i] * f[1][j]);
         it.Qt[(int64_t)(r0 + i) * it.np + c0 + j] = r0 + i == c0 + j ? 1.0 : 0.0;
         if (r0 != c0) it.Qt[(int64_t)(c0 + i) * it.np + r0 + j] = 0.0;
     }
