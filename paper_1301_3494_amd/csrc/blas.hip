@@ -351,16 +351,15 @@ __global__ __launch_bounds__(256) void list_copy_kernel(T *__restrict__ dst, con
     if (e < n) dst[e] = src[e];
 }
 template <typename T>
-static void list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
-    const unsigned v = (unsigned)(n / sizeof(T));
-    if (v > 0)
-        hipLaunchKernelGGL((list_copy_kernel<T>), dim3((v + 255) / 256), dim3(256), 0, s, static_cast<T *>(dst),
-                           static_cast<const T *>(src), v);
+static hipError_t list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+    unsigned v = (unsigned)(n / sizeof(T));
+    if (v == 0) return hipSuccess;
+    void *args[] = {&dst, &src, &v};
+    return hipLaunchKernel(reinterpret_cast<const void *>(list_copy_kernel<T>), dim3((v + 255) / 256), dim3(256), args, 0, s);
 }
-void launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+hipError_t launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
     const size_t bits = reinterpret_cast<size_t>(dst) | reinterpret_cast<size_t>(src) | n;
-    if (bits % sizeof(uint4) == 0) list_copy<uint4>(dst, src, n, s);
-    else list_copy<uint32_t>(dst, src, n, s);
+    return bits % sizeof(uint4) == 0 ? list_copy<uint4>(dst, src, n, s) : list_copy<uint32_t>(dst, src, n, s);
 }
 
 __global__ void row_scale_kernel(const double *x, double *y, const int64_t *base, const int32_t *rows,

@@ -233,8 +233,9 @@ void launch_convert_f64_split(const double *x, uint32_t *y, int64_t n, hipStream
 void launch_convert_f32_f64(const float *x, double *y, int64_t n, hipStream_t s);
 void launch_fill(double *x, double v, int64_t n, hipStream_t s);
 // n bytes (a multiple of 4) from or to pinned host memory; 16 a lane where both
-// sides are 16-byte aligned and n is a multiple of 16.
-void launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s);
+// sides are 16-byte aligned and n is a multiple of 16.  The launch's own error
+// comes back: what the copy should have brought must not be used then.
+hipError_t launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s);
 // Row scaling of row-major blocks: block k (base[k], rows[k] x cols[k]) gets
 // y[r][c] = x[r][c] * scale[vbase[k] + r].
 void launch_row_scale(const double *x, double *y, const int64_t *base, const int32_t *rows,

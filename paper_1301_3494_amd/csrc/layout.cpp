@@ -466,16 +466,19 @@ void read_back(const std::vector<HostCopy> &parts, hipStream_t s) {
     Pinned b;
     if (total > 0 && total <= kPinnedBlock) b = pin_take(dev, total);
     size_t at = 0;
+    hipError_t e = hipSuccess;
     for (const HostCopy &p : parts) {
-        if (p.bytes == 0) continue;
-        if (b.ptr) launch_list_copy(static_cast<char *>(b.ptr) + at, p.src, p.bytes, s);
-        else HIP_OK(hipMemcpyAsync(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost, s));
+        if (p.bytes == 0 || e != hipSuccess) continue;
+        e = b.ptr ? launch_list_copy(static_cast<char *>(b.ptr) + at, p.src, p.bytes, s)
+                  : hipMemcpyAsync(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost, s);
         at += (p.bytes + 255) & ~size_t(255);
     }
-    const hipError_t e = hipStreamSynchronize(s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
     if (b.ptr) {
         at = 0;
         for (const HostCopy &p : parts) {
+            if (e != hipSuccess) break;
             if (p.bytes) std::memcpy(p.dst, static_cast<char *>(b.ptr) + at, p.bytes);
             at += (p.bytes + 255) & ~size_t(255);
         }
@@ -505,12 +508,14 @@ void ListStage::copy(char *dst, hipStream_t s) {
         if (b.ptr) std::memcpy(static_cast<char *>(b.ptr) + pt.at, pt.src, pt.bytes);
         else HIP_OK(hipMemcpyAsync(dst + pt.at, pt.src, pt.bytes, hipMemcpyHostToDevice, s));
     }
+    hipError_t e = hipSuccess;
     if (b.ptr) {
-        launch_list_copy(dst, b.ptr, total_, s);
+        e = launch_list_copy(dst, b.ptr, total_, s);
         pin_give(b, s);
     }
     parts_.clear();
     total_ = 0;
+    HIP_OK(e);
 }
 
 void check_grid(int64_t blocks, int threads, const char *what) {

@@ -108,8 +108,11 @@ const char *hipGetErrorString(hipError_t) { return "stand-in error"; }
 }
 
 namespace pdmrg {
-void launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+bool g_fail_copies = false;
+hipError_t launch_list_copy(void *dst, const void *src, size_t n, hipStream_t s) {
+    if (g_fail_copies) return hipErrorLaunchFailure;
     push(s, [=] { std::memcpy(dst, src, n); });
+    return hipSuccess;
 }
 }  // namespace pdmrg
 
@@ -175,12 +178,42 @@ void ordinary_streams() {
     CHECK(pa != pb && pa == pc);
     CHECK(seen_a == a && seen_b == b && seen_c == c);
 }
+
+// A copy that could not be launched is an error, not the last copy's contents;
+// its block is there for the next one.
+void failed_copies() {
+    StageHold hold;
+    double src = 7.0, dst = 0.0;
+    read_back({{&dst, &src, sizeof dst}}, nullptr);
+    CHECK(dst == 7.0 && g_pinned.size() == 1);
+    auto throws = [](auto &&f) {
+        try {
+            f();
+        } catch (const Error &e) {
+            return e.code == PDMRG_EHIP;
+        }
+        return false;
+    };
+    src = 8.0;
+    g_fail_copies = true;
+    dst = 1.0;
+    CHECK(throws([&] { read_back({{&dst, &src, sizeof dst}}, nullptr); }) && dst == 1.0);
+    CHECK(throws([&] {
+        ListBuf d;
+        upload_list(d, std::vector<int>(10, 1), nullptr);
+    }));
+    g_fail_copies = false;
+    CHECK(hipDeviceSynchronize() == hipSuccess);
+    read_back({{&dst, &src, sizeof dst}}, nullptr);
+    CHECK(dst == 8.0 && g_pinned.size() == 1);
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::map<std::string, void (*)()> checks = {
         {"per_thread_streams", per_thread_streams},
         {"ordinary_streams", ordinary_streams},
+        {"failed_copies", failed_copies},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     CHECK(it != checks.end());

@@ -27,3 +27,7 @@ def run(program, check):
 @pytest.mark.parametrize("check", ["per_thread_streams", "ordinary_streams"])
 def test_blocks_are_reused_in_stream_order_only(program, check):
     run(program, check)
+
+
+def test_a_copy_that_was_not_launched_is_an_error(program):
+    run(program, "failed_copies")
