@@ -292,7 +292,7 @@ void DevBuf::release() {
 //
 // Pinned blocks are reused once the event behind their last copy has passed.
 // All of them together are bounded; a list that finds no block, or is larger
-// than one, goes through the runtime's pageable copy.  The device side of lists
+// than one, goes through the runtime's pageable copy and waits for it.  The device side of lists
 // that live within one call (ListBuf) is kept by stream, also bounded: a block
 // from the allocator above would be a new one each time (75 us of hipMalloc for
 // 0.5 MB), for it has to wait for the whole device before it is used again.
@@ -502,16 +502,20 @@ void ListStage::copy(char *dst, hipStream_t s) {
     HIP_OK(hipGetDevice(&dev));
     Pinned b;
     if (total_ > 0 && total_ <= kPinnedBlock) b = pin_take(dev, total_);
+    hipError_t e = hipSuccess;
     for (const Part &pt : parts_) {
         *pt.dst = dst + pt.at;
         if (pt.bytes == 0) continue;
         if (b.ptr) std::memcpy(static_cast<char *>(b.ptr) + pt.at, pt.src, pt.bytes);
-        else HIP_OK(hipMemcpyAsync(dst + pt.at, pt.src, pt.bytes, hipMemcpyHostToDevice, s));
+        else if (e == hipSuccess) e = hipMemcpyAsync(dst + pt.at, pt.src, pt.bytes, hipMemcpyHostToDevice, s);
     }
-    hipError_t e = hipSuccess;
     if (b.ptr) {
         e = launch_list_copy(dst, b.ptr, total_, s);
         pin_give(b, s);
+    } else if (total_ > 0) {
+        // the runtime may still be reading the host arrays
+        const hipError_t es = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = es;
     }
     parts_.clear();
     total_ = 0;

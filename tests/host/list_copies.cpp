@@ -207,6 +207,36 @@ void failed_copies() {
     read_back({{&dst, &src, sizeof dst}}, nullptr);
     CHECK(dst == 8.0 && g_pinned.size() == 1);
 }
+
+// The host arrays are free once the lists are on their way, whichever way that
+// is: through a pinned block, or past it for lists that no block holds and once
+// all blocks are in use.
+void host_arrays_are_free() {
+    StageHold hold;
+    auto check = [](size_t n) {
+        std::vector<int> list(n, 5), seen(n);
+        ListBuf d;
+        upload_list(d, list, nullptr);
+        launch_reader(d.as<int>(), seen, nullptr);
+        std::fill(list.begin(), list.end(), -1);
+        CHECK(hipStreamSynchronize(nullptr) == hipSuccess);
+        CHECK(seen == std::vector<int>(n, 5));
+    };
+    check(1000);
+    check(size_t(5) << 20);   // 20 MB
+    // pinned blocks whose copies have not run
+    int h;
+    const auto busy = reinterpret_cast<hipStream_t>(&h);
+    std::vector<std::unique_ptr<ListBuf>> bufs;
+    const std::vector<int> big(size_t(3) << 19, 1);   // 6 MB
+    for (int k = 0; k < 12; ++k) {
+        bufs.emplace_back(new ListBuf());
+        upload_list(*bufs.back(), big, busy);
+        check(1000);
+        check(size_t(1) << 20);
+    }
+    CHECK(hipDeviceSynchronize() == hipSuccess);
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -214,6 +244,7 @@ int main(int argc, char **argv) {
         {"per_thread_streams", per_thread_streams},
         {"ordinary_streams", ordinary_streams},
         {"failed_copies", failed_copies},
+        {"host_arrays_are_free", host_arrays_are_free},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     CHECK(it != checks.end());

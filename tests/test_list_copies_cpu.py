@@ -31,3 +31,7 @@ def test_blocks_are_reused_in_stream_order_only(program, check):
 
 def test_a_copy_that_was_not_launched_is_an_error(program):
     run(program, "failed_copies")
+
+
+def test_host_arrays_are_free_once_a_list_is_on_its_way(program):
+    run(program, "host_arrays_are_free")
