@@ -43,6 +43,7 @@ int pdmrg_ctx_create(int device, void *stream, pdmrg_ctx **out) {
     auto *c = new pdmrg_ctx();
     c->device = device;
     c->stream = static_cast<hipStream_t>(stream);
+    c->stage_hold.bind(device, c->stream);
     *out = c;
     API_END
 }

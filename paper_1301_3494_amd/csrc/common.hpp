@@ -208,11 +208,16 @@ struct HostCopy {
 };
 void read_back(const std::vector<HostCopy> &parts, hipStream_t s);
 
-// Held by every context: the pinned blocks behind ListStage and read_back and
-// the device blocks behind ListBuf are freed with the last one.
+// Held by every context: the pinned blocks behind ListStage and read_back are
+// freed with the last one, the device blocks behind ListBuf with the last one on
+// their stream.
 struct StageHold {
+    int dev = 0;
+    hipStream_t s = nullptr;
+    bool bound = false;
     StageHold();
     ~StageHold();
+    void bind(int device, hipStream_t stream);   // once, the context's stream
     StageHold(const StageHold &) = delete;
     StageHold &operator=(const StageHold &) = delete;
 };

@@ -388,6 +388,7 @@ struct Driver {
             c->device = ctx->device;
             HIP_OK(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
             c->owns_stream = true;
+            c->stage_hold.bind(c->device, c->stream);
             ctx->sub.push_back(c);
         }
         ctx->sub[r]->autotune = ctx->autotune;

@@ -295,7 +295,8 @@ void DevBuf::release() {
 // than one, goes through the runtime's pageable copy and waits for it.  The device side of lists
 // that live within one call (ListBuf) is kept by stream, also bounded: a block
 // from the allocator above would be a new one each time (75 us of hipMalloc for
-// 0.5 MB), for it has to wait for the whole device before it is used again.
+// 0.5 MB), for it has to wait for the whole device before it is used again.  The
+// blocks of a stream go with the last context on it.
 namespace {
 constexpr size_t kPinnedBytes = size_t(64) << 20, kPinnedBlock = size_t(8) << 20;
 constexpr size_t kListBytes = size_t(256) << 20, kListBlock = size_t(8) << 20;
@@ -317,11 +318,18 @@ struct PinPool {
     size_t bytes = 0;               // of all blocks
     std::vector<ListBlock> lists;   // device blocks, free for lists on their stream
     size_t list_bytes = 0;          // of all of them
+    std::map<std::pair<int, hipStream_t>, int> users;   // contexts on a stream
     int holders = 0;
 };
 PinPool &pins() {
     static PinPool *p = new PinPool();
     return *p;
+}
+
+void pin_free(Pinned &b) {
+    (void)hipEventSynchronize(b.done);
+    (void)hipEventDestroy(b.done);
+    (void)hipHostFree(b.ptr);
 }
 
 // A block of at least n bytes whose last copy has ended, or one without ptr.
@@ -363,10 +371,18 @@ Pinned pin_take(int dev, size_t n) {
     return b;
 }
 
-void pin_free(Pinned &b) {
-    (void)hipEventSynchronize(b.done);
-    (void)hipEventDestroy(b.done);
-    (void)hipHostFree(b.ptr);
+// Out of the pool, under g_pin_mu: the idle list blocks that `which` chooses.
+template <class F>
+std::vector<ListBlock> lists_out(F which) {
+    PinPool &p = pins();
+    std::vector<ListBlock> out;
+    for (size_t k = p.lists.size(); k-- > 0;) {
+        if (!which(p.lists[k])) continue;
+        out.push_back(p.lists[k]);
+        p.list_bytes -= p.lists[k].bytes;
+        p.lists.erase(p.lists.begin() + (ptrdiff_t)k);
+    }
+    return out;
 }
 }  // namespace
 
@@ -374,17 +390,28 @@ StageHold::StageHold() {
     std::lock_guard<std::mutex> lk(g_pin_mu);
     ++pins().holders;
 }
+void StageHold::bind(int device, hipStream_t stream) {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    dev = device;
+    s = stream;
+    bound = true;
+    ++pins().users[{dev, s}];
+}
 StageHold::~StageHold() {
     std::vector<Pinned> all;
     std::vector<ListBlock> lists;
     {
         std::lock_guard<std::mutex> lk(g_pin_mu);
         PinPool &p = pins();
-        if (--p.holders > 0) return;
-        all.swap(p.blocks);
-        lists.swap(p.lists);
+        const bool last = --p.holders == 0;
+        bool dead = false;   // no context left on its stream
+        if (bound && --p.users[{dev, s}] == 0) {
+            p.users.erase({dev, s});
+            dead = true;
+        }
+        lists = lists_out([&](const ListBlock &b) { return last || (dead && b.dev == dev && b.s == s); });
+        if (last) all.swap(p.blocks);
         for (const Pinned &b : all) p.bytes -= b.bytes;
-        for (const ListBlock &b : lists) p.list_bytes -= b.bytes;
     }
     for (Pinned &b : all) pin_free(b);
     for (ListBlock &b : lists) (void)hipFree(b.ptr);   // waits for the device

@@ -18,7 +18,10 @@ namespace {
 using Queue = std::deque<std::function<void()>>;
 std::mutex g_mu;
 std::map<std::pair<hipStream_t, std::thread::id>, Queue> g_queues;
-std::set<void *> g_device, g_pinned;   // live allocations
+std::map<void *, size_t> g_device;     // live allocations
+std::set<void *> g_pinned;
+size_t g_device_bytes = 0, g_device_limit = size_t(-1);
+int g_pageable = 0;                    // copies past the pinned blocks
 
 Queue &queue(hipStream_t s) {
     return g_queues[{s, s == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()}];
@@ -54,7 +57,9 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t n) {
     std::lock_guard<std::mutex> lk(g_mu);
-    g_device.insert(*p = std::malloc(n));
+    if (g_device_bytes + n > g_device_limit) return hipErrorOutOfMemory;
+    g_device[*p = std::malloc(n)] = n;
+    g_device_bytes += n;
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() {
@@ -65,7 +70,9 @@ hipError_t hipDeviceSynchronize() {
 hipError_t hipFree(void *p) {
     (void)hipDeviceSynchronize();
     std::lock_guard<std::mutex> lk(g_mu);
-    CHECK(g_device.erase(p) == 1);
+    CHECK(g_device.count(p) == 1);
+    g_device_bytes -= g_device[p];
+    g_device.erase(p);
     std::free(p);
     return hipSuccess;
 }
@@ -100,6 +107,7 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
+    ++g_pageable;
     push(s, [=] { std::memcpy(dst, src, n); });
     return hipSuccess;
 }
@@ -237,6 +245,39 @@ void host_arrays_are_free() {
     }
     CHECK(hipDeviceSynchronize() == hipSuccess);
 }
+
+// Contexts that come and go on streams of their own while one lives on: the
+// blocks of a stream go with the last context on it, and lists do not end up in
+// the allocator.
+void dead_streams() {
+    StageHold keep;
+    keep.bind(0, nullptr);
+    const std::vector<int> list(size_t(1) << 20, 3);   // 4 MB
+    std::vector<int> handles(200);
+    auto use = [&](hipStream_t s) {
+        ListBuf d;
+        upload_list(d, list, s);
+        CHECK(!d.large.ptr);
+    };
+    use(nullptr);
+    const size_t mine = g_device_bytes;
+    for (int &h : handles) {
+        const auto s = reinterpret_cast<hipStream_t>(&h);
+        StageHold one;
+        one.bind(0, s);
+        use(s);
+        {
+            StageHold two;   // another context on that stream
+            two.bind(0, s);
+            use(s);
+        }
+        CHECK(hipStreamSynchronize(s) == hipSuccess);
+        CHECK(g_device_bytes == 2 * mine);
+    }
+    CHECK(g_device_bytes == mine);
+    use(nullptr);
+    CHECK(g_device_bytes == mine);
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -245,6 +286,7 @@ int main(int argc, char **argv) {
         {"ordinary_streams", ordinary_streams},
         {"failed_copies", failed_copies},
         {"host_arrays_are_free", host_arrays_are_free},
+        {"dead_streams", dead_streams},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     CHECK(it != checks.end());

@@ -35,3 +35,8 @@ def test_a_copy_that_was_not_launched_is_an_error(program):
 
 def test_host_arrays_are_free_once_a_list_is_on_its_way(program):
     run(program, "host_arrays_are_free")
+
+
+@pytest.mark.parametrize("check", ["dead_streams"])
+def test_idle_blocks_are_given_back(program, check):
+    run(program, check)
