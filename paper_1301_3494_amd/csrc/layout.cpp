@@ -174,7 +174,17 @@ size_t size_class(size_t n) {
     return (n + step - 1) / step * step;
 }
 
+// The idle blocks behind ListBuf (below): freed, and their bytes.
+void list_pool_trim();
+int64_t list_pool_idle();
+
 namespace {
+void count_in_use(int64_t bytes) {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    DeviceCache &c = cache();
+    c.in_use += bytes;
+    c.peak = std::max(c.peak, c.in_use);
+}
 // under g_cache_mu: a cached block of class `cls` on `dev`, or null
 void *take_free(DeviceCache &c, int dev, size_t cls) {
     auto it = c.free_.find(std::make_pair(dev, cls));
@@ -231,6 +241,7 @@ void DevBuf::alloc(size_t n) {
             HIP_OK(hipDeviceSynchronize());
             for (auto &kv : all)
                 for (void *q : kv.second) (void)hipFree(q);
+            list_pool_trim();
             p = nullptr;
             e = hipMalloc(&p, cls);
         }
@@ -242,18 +253,14 @@ void DevBuf::alloc(size_t n) {
     }
     ptr = p;
     bytes = cls;
-    {
-        std::lock_guard<std::mutex> lk(g_cache_mu);
-        c.in_use += (int64_t)cls;
-        c.peak = std::max(c.peak, c.in_use);
-    }
+    count_in_use((int64_t)cls);
     poison(ptr, cls);
 }
 
 void alloc_stats(int64_t *in_use, int64_t *peak, int64_t *cached) {
+    int64_t held = list_pool_idle();
     std::lock_guard<std::mutex> lk(g_cache_mu);
     DeviceCache &c = cache();
-    int64_t held = 0;
     for (auto *m : {&c.free_, &c.pending_})
         for (auto &kv : *m) held += (int64_t)kv.first.second * (int64_t)kv.second.size();
     if (in_use) *in_use = c.in_use;
@@ -296,7 +303,8 @@ void DevBuf::release() {
 // that live within one call (ListBuf) is kept by stream, also bounded: a block
 // from the allocator above would be a new one each time (75 us of hipMalloc for
 // 0.5 MB), for it has to wait for the whole device before it is used again.  The
-// blocks of a stream go with the last context on it.
+// blocks of a stream go with the last context on it, all of them when memory is
+// short.
 namespace {
 constexpr size_t kPinnedBytes = size_t(64) << 20, kPinnedBlock = size_t(8) << 20;
 constexpr size_t kListBytes = size_t(256) << 20, kListBlock = size_t(8) << 20;
@@ -386,6 +394,21 @@ std::vector<ListBlock> lists_out(F which) {
 }
 }  // namespace
 
+void list_pool_trim() {
+    std::vector<ListBlock> lists;
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        lists = lists_out([](const ListBlock &) { return true; });
+    }
+    for (ListBlock &b : lists) (void)hipFree(b.ptr);   // waits for the device
+}
+int64_t list_pool_idle() {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    int64_t n = 0;
+    for (const ListBlock &b : pins().lists) n += (int64_t)b.bytes;
+    return n;
+}
+
 StageHold::StageHold() {
     std::lock_guard<std::mutex> lk(g_pin_mu);
     ++pins().holders;
@@ -460,10 +483,14 @@ void ListBuf::ensure(size_t n, hipStream_t stream) {
     bytes = cls;
     dev = d;
     s = stream;
+    if (large.ptr) return;
+    count_in_use((int64_t)cls);
+    poison(ptr, cls);
 }
 
 void ListBuf::release() {
     if (ptr && !large.ptr) {
+        count_in_use(-(int64_t)bytes);
         std::lock_guard<std::mutex> lk(g_pin_mu);
         pins().lists.push_back(ListBlock{ptr, bytes, dev, s});
     }

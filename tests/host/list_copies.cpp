@@ -278,6 +278,31 @@ void dead_streams() {
     use(nullptr);
     CHECK(g_device_bytes == mine);
 }
+
+// Idle list blocks are counted as held for reuse, blocks in use as in use, and
+// they are given back when an allocation fails.
+void list_memory() {
+    StageHold hold;
+    int64_t in_use, peak, cached;
+    {
+        ListBuf d;
+        upload_list(d, std::vector<int>(size_t(1) << 20, 3), nullptr);   // 4 MB
+        alloc_stats(&in_use, &peak, &cached);
+        CHECK(in_use == int64_t(4) << 20 && peak == in_use && cached == 0);
+    }
+    alloc_stats(&in_use, &peak, &cached);
+    CHECK(in_use == 0 && cached == int64_t(4) << 20);
+    g_device_limit = size_t(6) << 20;
+    DevBuf b(size_t(5) << 20);
+    CHECK(b.ptr && g_device_bytes == size_t(5) << 20);
+    alloc_stats(&in_use, &peak, &cached);
+    CHECK(in_use == int64_t(5) << 20 && cached == 0);
+    // and a list that finds no memory of its own takes it from the allocator's cache
+    b.release();
+    ListBuf d;
+    upload_list(d, std::vector<int>(size_t(1) << 20, 3), nullptr);
+    CHECK(d.ptr && g_device_bytes <= g_device_limit);
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -287,6 +312,7 @@ int main(int argc, char **argv) {
         {"failed_copies", failed_copies},
         {"host_arrays_are_free", host_arrays_are_free},
         {"dead_streams", dead_streams},
+        {"list_memory", list_memory},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     CHECK(it != checks.end());
