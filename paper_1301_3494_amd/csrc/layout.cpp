@@ -299,7 +299,8 @@ void DevBuf::release() {
 //
 // Pinned blocks are reused once the event behind their last copy has passed.
 // All of them together are bounded; a list that finds no block, or is larger
-// than one, goes through the runtime's pageable copy and waits for it.  The device side of lists
+// than one, goes through the runtime's pageable copy and waits for it; idle
+// blocks of other sizes make room first.  The device side of lists
 // that live within one call (ListBuf) is kept by stream, also bounded: a block
 // from the allocator above would be a new one each time (75 us of hipMalloc for
 // 0.5 MB), for it has to wait for the whole device before it is used again.  The
@@ -345,6 +346,8 @@ Pinned pin_take(int dev, size_t n) {
     size_t cls = size_t(64) << 10;
     while (cls < n) cls <<= 2;
     cls = std::min(cls, kPinnedBlock);
+    std::vector<Pinned> idle;
+    bool room = false;
     {
         std::lock_guard<std::mutex> lk(g_pin_mu);
         PinPool &p = pins();
@@ -359,9 +362,21 @@ Pinned pin_take(int dev, size_t n) {
             (void)hipGetLastError();   // not ready; the later ones hardly are
             ++busy;
         }
-        if (p.bytes + cls > kPinnedBytes) return Pinned{};
-        p.bytes += cls;
+        for (size_t k = 0; k < p.blocks.size() && p.bytes + cls > kPinnedBytes;) {
+            if (hipEventQuery(p.blocks[k].done) != hipSuccess) {
+                (void)hipGetLastError();
+                ++k;
+                continue;
+            }
+            idle.push_back(p.blocks[k]);
+            p.bytes -= p.blocks[k].bytes;
+            p.blocks.erase(p.blocks.begin() + (ptrdiff_t)k);
+        }
+        room = p.bytes + cls <= kPinnedBytes;
+        if (room) p.bytes += cls;
     }
+    for (Pinned &b : idle) pin_free(b);
+    if (!room) return Pinned{};
     Pinned b;
     b.dev = dev;
     b.bytes = cls;

@@ -303,6 +303,26 @@ void list_memory() {
     upload_list(d, std::vector<int>(size_t(1) << 20, 3), nullptr);
     CHECK(d.ptr && g_device_bytes <= g_device_limit);
 }
+
+// Large lists that have used up the pinned memory leave it to small ones.
+void pinned_sizes() {
+    StageHold hold;
+    const std::vector<int> big(size_t(3) << 19, 1), small(100, 2);   // 6 MB
+    {
+        std::vector<std::unique_ptr<ListBuf>> bufs;
+        for (int k = 0; k < 8; ++k) {
+            bufs.emplace_back(new ListBuf());
+            upload_list(*bufs.back(), big, nullptr);
+        }
+    }
+    CHECK(g_pageable == 0 && g_pinned.size() == 8);
+    CHECK(hipDeviceSynchronize() == hipSuccess);
+    for (int k = 0; k < 3; ++k) {
+        ListBuf d;
+        upload_list(d, small, nullptr);
+    }
+    CHECK(g_pageable == 0);
+}
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -313,6 +333,7 @@ int main(int argc, char **argv) {
         {"host_arrays_are_free", host_arrays_are_free},
         {"dead_streams", dead_streams},
         {"list_memory", list_memory},
+        {"pinned_sizes", pinned_sizes},
     };
     const auto it = checks.find(argc > 1 ? argv[1] : "");
     CHECK(it != checks.end());

@@ -37,6 +37,6 @@ def test_host_arrays_are_free_once_a_list_is_on_its_way(program):
     run(program, "host_arrays_are_free")
 
 
-@pytest.mark.parametrize("check", ["dead_streams", "list_memory"])
+@pytest.mark.parametrize("check", ["dead_streams", "list_memory", "pinned_sizes"])
 def test_idle_blocks_are_given_back(program, check):
     run(program, check)
