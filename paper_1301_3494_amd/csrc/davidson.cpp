@@ -70,8 +70,8 @@ DavResult davidson_run(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double 
     // Short vectors: all of a step's passes in one workgroup.  One CU's rate ends
     // it: at n = 6220 a run of 12 products takes 1336 us against 1184 with the
     // passes apart (3 products: 244 against 268), at n = 3224 1048 against 1172
-    // (202 against 260).
-    const bool whole = fused && n <= kDavShort;
+    // (202 against 260).  An empty vector takes the passes apart.
+    const bool whole = fused && n > 0 && n <= kDavShort;
 
     auto dot_into = [&](const double *U, int nv, const double *x, double *out, int stride = 1) {
         launch_multidot(U, n, nv, x, n, w.partial, kBlk, s);
