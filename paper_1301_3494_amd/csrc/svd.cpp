@@ -216,7 +216,19 @@ void qr_right_factor(QrState &qs, const std::vector<JacMat> &items, hipStream_t 
         launch_qr_apply(qs.d_back.as<QrApply>() + qs.back_off[pn], qs.back_off[pn + 1] - qs.back_off[pn], s);
 }
 
-// Block Jacobi sweeps (svd.hip) on the matrices of more than kJacSmall rows,
+// Whether a matrix takes the sweeps of many launches (JacBatch) rather than the
+// kernel that iterates it in one workgroup: with few but long rows that one's
+// passes over W, at a workgroup's rate, outweigh the launches and the wait of a
+// sweep.  One workgroup / launches, whole call in us, at the sizes around the
+// lines: 5 x 8192 1258 / 1274, 5 x 16384 2097 / 1908; 16 x 4096 943 / 1159, 16 x
+// 8192 915 / 885; 17 x 2048 923 / 1070, 17 x 4096 990 / 785; 33 x 1024 927 / 1036, 33
+// x 2048 1380 / 1167; 63 x 1024 1361 / 1245.
+bool jac_batched(int nv, int len) {
+    const int longest = nv > 32 ? 1400 : nv > 16 ? 3000 : nv > 8 ? 8000 : 10000;
+    return nv > kJacSmall || (nv > 1 && len > longest);
+}
+
+// Block Jacobi sweeps (svd.hip) on the matrices that jac_batched() names,
 // all in the same launches.  Every matrix has W at the same offset of two
 // planes, and Z, the next Z, Qt and the two G at the same offset of five (the
 // GEMM that applies a sweep's rotations goes from one W and Z to the other).
@@ -225,7 +237,11 @@ struct JacBatch {
     std::vector<JacItem> items;
     std::vector<size_t> woff, zoff;
     size_t nw = 0, nz = 0, npair = 0;           // plane sizes, pairs of 32-row blocks
-    double *W[2] = {}, *Z[2] = {}, *Qt = nullptr, *G = nullptr, *Qr = nullptr, *Gd = nullptr;
+    size_t ngp = 0;                             // partial Gram matrices of few long rows
+    double *W[2] = {}, *Z[2] = {}, *Qt = nullptr, *G = nullptr, *Qr = nullptr, *Gd = nullptr, *Gp = nullptr;
+    // Ranges of the row length that the Gram matrix of one 64 x 64 block is summed
+    // over: by the matrix alone, so its bits do not depend on the batch.
+    static int gram_parts(int nv, int len) { return nv > kJacSmall ? 1 : std::min(64, (len + 255) / 256); }
 
     void add(int i, const JacMat &m) {
         const int np = (m.nv + 63) / 64 * 64;
@@ -240,8 +256,9 @@ struct JacBatch {
         it.np = np;
         items.push_back(it);
         npair += np / 64;
+        if (gram_parts(m.nv, m.len) > 1) ngp += (size_t)gram_parts(m.nv, m.len) * m.nv * m.nv;
     }
-    size_t doubles() const { return 2 * nw + 5 * nz + 4 * npair * 4096 + 12 * 32; }
+    size_t doubles() const { return 2 * nw + 5 * nz + 4 * npair * 4096 + ngp + 14 * 32; }
     // Takes the planes from the arena and points the matrices into the first ones.
     void place(Arena &ar, std::vector<JacMat> &mats) {
         for (int h = 0; h < 2; ++h) W[h] = ar.take(nw), Z[h] = ar.take(nz);
@@ -249,6 +266,7 @@ struct JacBatch {
         G = ar.take(2 * nz);
         Qr = ar.take(2 * npair * 4096);
         Gd = ar.take(2 * npair * 4096);
+        Gp = ar.take(std::max<size_t>(ngp, 1));
         for (size_t k = 0; k < who.size(); ++k) mats[who[k]].W = W[0] + woff[k], mats[who[k]].Z = Z[0] + zoff[k];
     }
     // Runs the sweeps, points the matrices at their final W and Z; returns the
@@ -260,8 +278,10 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
     const int n = (int)who.size();
     if (n == 0) return 0;
     launch_fill(G, 0.0, (int64_t)(2 * nz), s);   // the padding
-    // slots: 0 W, 1 next W, 2 Z, 3 next Z, 4 Qt, 5 G
+    // slots: 0 W, 1 next W, 2 Z, 3 next Z, 4 Qt, 5 G, 6 partial G
     GemmList gG, gWZ;
+    LcList sum;
+    size_t gp0 = 0;
     gG.tb = true;
     std::vector<JacTask> eig, upd, begt;
     size_t pair0 = 0;
@@ -281,6 +301,19 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
                 begt.push_back(JacTask{k, a, b, 0});
             }
             for (int c = 0; c < 4 * nb; ++c) upd.push_back(JacTask{k, a, -1, c});
+            const int parts = gram_parts(it.nv, len);
+            if (parts > 1) {
+                sum.add_task(5, zoff[k], it.nv, it.nv, it.np);
+                for (int q = 0, k0 = 0; q < parts; ++q) {
+                    const int k1 = (int)((int64_t)len * (q + 1) / parts);
+                    gG.add_item(6, gp0, it.nv, it.nv, it.nv);
+                    gG.add_seg(0, woff[k] + k0, len, 0, woff[k] + k0, len, k1 - k0);
+                    sum.add_src(6, gp0, it.nv, 1.0);
+                    gp0 += (size_t)it.nv * it.nv;
+                    k0 = k1;
+                }
+                continue;
+            }
             // rows 64 a .. of G from their diagonal block on
             const int m = std::min(64, it.nv - 64 * a), cols = it.nv - 64 * a;
             gG.add_item(5, zoff[k] + (size_t)64 * a * it.np + 64 * a, m, cols, it.np);
@@ -295,6 +328,7 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
         g->pick_tile();
         g->finish(s);
     }
+    if (!sum.tasks.empty()) sum.finish(s);
     std::vector<JacTask> tasks = eig;
     tasks.insert(tasks.end(), upd.begin(), upd.end());
     tasks.insert(tasks.end(), begt.begin(), begt.end());
@@ -315,7 +349,9 @@ int JacBatch::run(std::vector<JacMat> &mats, int &sweeps, int &rounds, hipStream
         sl.p[3] = Z[cur ^ 1];
         sl.p[4] = Qt;
         sl.p[5] = G;
+        sl.p[6] = Gp;
         gG.launch(GemmPrec::F64, true, sl, s);
+        if (!sum.tasks.empty()) sum.launch(true, sl, s);
         upload_list(d_active, active, s);
         launch_fill(d_off.as<double>(), 0.0, n, s);
         launch_jac_begin(d_items.as<JacItem>(), t_beg, (int)begt.size(), d_active.as<int32_t>(),
@@ -380,7 +416,7 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
         items[i].tol = std::max(1e-14, 8.0 * 2.220446049250313e-16 * std::sqrt((double)items[i].len));
         need += round32(nv * m.nr) + round32(nv * m.nc) + 64;
         if (pre[i]) need += 2 * round32(nv * len) + round32((nv + kQrPanel - 1) / kQrPanel * 256) + 96;
-        if ((int)nv > kJacSmall) {
+        if (jac_batched((int)nv, items[i].len)) {
             items[i].ldz = (int)((nv + 63) / 64 * 64);
             batch.add(i, items[i]);
         } else {
@@ -398,7 +434,7 @@ void svd_batch(pdmrg_ctx *ctx, const std::vector<Mat> &mats, std::vector<SvdRes>
         const Mat &m = mats[i];
         const bool wide = m.nr <= m.nc;
         const int nv = items[i].nv, len = std::max(m.nr, m.nc);
-        if (nv <= kJacSmall) {
+        if (!jac_batched(nv, items[i].len)) {
             items[i].W = ar.take((size_t)nv * items[i].len);
             items[i].Z = ar.take((size_t)nv * nv);
             small.push_back(JacSmall{items[i].W, items[i].Z, items[i].tol, nv, items[i].len});

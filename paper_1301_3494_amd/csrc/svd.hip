@@ -672,43 +672,108 @@ void launch_jac_begin(const JacItem *items, const JacTask *tasks, int ntasks, co
 // A matrix of at most 2 P rows, whole iteration in one workgroup: Gram matrix
 // (FP64 MFMA), one cyclic sweep of it, W <- J^T W and Z <- J^T Z, until the
 // fresh Gram matrix meets the tolerance.  W and Z stay in global memory (the
-// caches); no launch, no host step between sweeps.
+// caches); no launch, no host step between sweeps.  What bounds it is the sweep
+// of the Gram matrix on short rows and the latency of the passes over W on long
+// ones, so both passes load several steps ahead: 48 x 1024 1290 -> 1050 us a call,
+// 16 x 2048 894 -> 770.  Up to 16 rows the Gram matrix is one tile, a chain of MFMAs
+// of one wave; from 1024 columns on all waves take a range of them, the next loads
+// under way: 16 x 2048 770 -> 610, 8 x 4096 730 -> 510.
 template <int P>
 __global__ __launch_bounds__(eig_threads(P)) void jac_small_kernel(const JacSmall *__restrict__ items, int max_sweeps,
                                                                    int32_t *__restrict__ sweeps) {
     constexpr int kThreads = eig_threads(P), kWaves = kThreads / 64, kT = P / 8;   // kT: 16-row tiles
+    // loads in flight, as registers allow: 16-wide steps of the Gram sums, tiles of columns of the update
+    constexpr int kAhead = P == 8 ? 8 : 2, kCols = P == 8 ? 16 : P == 16 ? 4 : 1;
     __shared__ EigLds<P> L;
     __shared__ double Gs[2 * P][2 * P + 2];   // Gram matrix, then the rotation
+    constexpr int kGw = P == 8 ? kWaves : 1;
+    __shared__ double Gw[kGw][16][17];        // its sums over the waves' ranges
     const JacSmall it = items[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int e = tid; e < it.nv * it.nv; e += kThreads) it.Z[e] = (e / it.nv == e % it.nv) ? 1.0 : 0.0;
+    if (it.nv == 1) {   // nothing to rotate
+        if (tid == 0) sweeps[blockIdx.x] = 0;
+        return;
+    }
     const int nt16 = (it.nv + 15) / 16;
     int done = -1;
     for (int sw = 0; sw < max_sweeps; ++sw) {
         __syncthreads();   // rows of W (and Z) are whole
         for (int e = tid; e < 4 * P * P; e += kThreads) Gs[e / (2 * P)][e % (2 * P)] = 0.0;
         __syncthreads();
-        // tiles (ti <= tj) of the Gram matrix, one at a time per wave
-        for (int t = w; t < nt16 * (nt16 + 1) / 2; t += kWaves) {
-            int ti = 0, rest = t;
+        // tiles (ti <= tj) of the Gram matrix, one at a time per wave; the only tile
+        // of up to 16 rows by all waves, a range of the columns each, if they are many
+        const bool shared = P == 8 && it.len >= 1024;
+        for (int t = w; t < (shared ? kWaves : nt16 * (nt16 + 1) / 2); t += kWaves) {
+            int ti = 0, rest = shared ? 0 : t;
             while (rest >= nt16 - ti) { rest -= nt16 - ti; ++ti; }
             const int tj = ti + rest;
+            const int steps = (it.len + 15) / 16;
+            const int kend = shared ? min(it.len, 16 * (steps * (w + 1) / kWaves)) : it.len;
             const int ra = 16 * ti + r16, rb = 16 * tj + r16;
             const double *pa = it.W + (int64_t)min(ra, it.nv - 1) * it.len;
             const double *pb = it.W + (int64_t)min(rb, it.nv - 1) * it.len;
             d4 acc = {0, 0, 0, 0};
-            for (int k0 = 0; k0 < it.len; k0 += 16) {
+            const bool ia = ra < it.nv, ib = rb < it.nv;
+            int k0 = shared ? 16 * (steps * w / kWaves) : 0;
+            // whole runs of kAhead steps; P < 32: the next run's loads under way during the sums
+            constexpr int kBuf = P == 32 ? 1 : 2;
+            double a[kBuf][kAhead][4], b[kBuf][P == 8 ? 1 : kAhead][4];   // P = 8: one tile, b = a
+            auto load = [&](int h, int k) {
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double x = pa[k + 16 * u + 4 * g + j];
+                        a[h][u][j] = ia ? x : 0.0;
+                        if constexpr (P > 8) {
+                            const double y = pb[k + 16 * u + 4 * g + j];
+                            b[h][u][j] = ib ? y : 0.0;
+                        }
+                    }
+            };
+            auto mul = [&](int h) {
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc = mfma_f64(a[h][u][j], P == 8 ? a[h][u][j] : b[h][P == 8 ? 0 : u][j], acc);
+            };
+            const int runs = max(0, kend - k0) / (16 * kAhead);
+            if constexpr (kBuf == 1)
+                for (int i = 0; i < runs; ++i) {
+                    load(0, k0);
+                    mul(0);
+                    k0 += 16 * kAhead;
+                }
+            if (kBuf == 2 && runs > 0) load(0, k0);
+            for (int i = 0; kBuf == 2 && i < runs; i += 2) {
+                if (i + 1 < runs) load(kBuf - 1, k0 + 16 * kAhead);
+                mul(0);
+                k0 += 16 * kAhead;
+                if (i + 1 < runs) {
+                    if (i + 2 < runs) load(0, k0 + 16 * kAhead);
+                    mul(kBuf - 1);
+                    k0 += 16 * kAhead;
+                }
+            }
+            for (; k0 < kend; k0 += 16) {
                 double a[4], b[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int k = k0 + 4 * g + j;
                     const bool in = k < it.len;
-                    a[j] = in && ra < it.nv ? pa[k] : 0.0;
-                    b[j] = in && rb < it.nv ? pb[k] : 0.0;
+                    a[j] = in && ia ? pa[k] : 0.0;
+                    b[j] = in && ib ? pb[k] : 0.0;
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc = mfma_f64(a[j], b[j], acc);
+            }
+            if (shared) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Gw[w % kGw][4 * r + g][r16] = acc[r];
+                continue;
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -717,6 +782,14 @@ __global__ __launch_bounds__(eig_threads(P)) void jac_small_kernel(const JacSmal
             }
         }
         __syncthreads();
+        if (shared) {
+            for (int e = tid; e < 256; e += kThreads) {
+                double x = Gw[0][e / 16][e % 16];
+                for (int q = 1; q < kWaves; ++q) x += Gw[q % kGw][e / 16][e % 16];
+                Gs[e / 16][e % 16] = x;
+            }
+            __syncthreads();
+        }
         auto at = [&](int r, int c) { return Gs[min(r, c)][max(r, c)]; };
         auto put = [&](int o, int k, double v) { Gs[o][k] = v; };
         if (!eig_sweep<P>(L, it.nv, it.tol, at, put, [](int, int, double) {})) {
@@ -724,30 +797,41 @@ __global__ __launch_bounds__(eig_threads(P)) void jac_small_kernel(const JacSmal
             break;
         }
         __syncthreads();
-        // W <- J^T W, then Z: a wave takes 16 columns at a time
+        // W <- J^T W, then Z: a wave takes kCols times 16 columns at a time
         const int cw = (it.len + 15) / 16, cz = (it.nv + 15) / 16;
-        for (int t = w; t < cw + cz; t += kWaves) {
-            double *X = t < cw ? it.W : it.Z;
-            const int len = t < cw ? it.len : it.nv, col = 16 * (t < cw ? t : t - cw) + r16;
-            double b[kT][4];
+        for (int t0 = w * kCols; t0 < cw + cz; t0 += kWaves * kCols) {
+            double b[kCols][kT][4];
 #pragma unroll
-            for (int ks = 0; ks < kT; ++ks)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = 16 * ks + 4 * g + j;
-                    b[ks][j] = k < it.nv && col < len ? X[(int64_t)k * len + col] : 0.0;
-                }
-            for (int ti = 0; ti < nt16; ++ti) {
-                d4 acc = {0, 0, 0, 0};
+            for (int u = 0; u < kCols; ++u) {
+                const int t = t0 + u;
+                const double *X = t < cw ? it.W : it.Z;
+                const int len = t < cw ? it.len : it.nv, col = 16 * (t < cw ? t : t - cw) + r16;
 #pragma unroll
                 for (int ks = 0; ks < kT; ++ks)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc = mfma_f64(Gs[16 * ti + r16][16 * ks + 4 * g + j], b[ks][j], acc);
+                    for (int j = 0; j < 4; ++j) {
+                        const int k = 16 * ks + 4 * g + j;
+                        b[u][ks][j] = k < it.nv && t < cw + cz && col < len ? X[(int64_t)k * len + col] : 0.0;
+                    }
+            }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int o = 16 * ti + 4 * r + g;
-                    if (o < it.nv && col < len) X[(int64_t)o * len + col] = acc[r];
+            for (int u = 0; u < kCols; ++u) {
+                const int t = t0 + u;
+                if (t >= cw + cz) break;
+                double *X = t < cw ? it.W : it.Z;
+                const int len = t < cw ? it.len : it.nv, col = 16 * (t < cw ? t : t - cw) + r16;
+                for (int ti = 0; ti < nt16; ++ti) {
+                    d4 acc = {0, 0, 0, 0};
+#pragma unroll
+                    for (int ks = 0; ks < kT; ++ks)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            acc = mfma_f64(Gs[16 * ti + r16][16 * ks + 4 * g + j], b[u][ks][j], acc);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int o = 16 * ti + 4 * r + g;
+                        if (o < it.nv && col < len) X[(int64_t)o * len + col] = acc[r];
+                    }
                 }
             }
         }
