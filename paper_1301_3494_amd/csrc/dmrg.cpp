@@ -664,17 +664,21 @@ struct Driver {
             for (int r0 = 0; r0 < tasks[t].rows; r0 += kSegRows) tiles.push_back(SegTile{(int32_t)t, r0});
         }
         t0.push_back((int32_t)tiles.size());
-        DevBuf d_tasks, d_tiles, d_t0, d_g, partial, res;
-        upload_list(d_tasks, tasks, s());
-        upload_list(d_tiles, tiles, s());
-        upload_list(d_t0, t0, s());
-        upload_list(d_g, g_of, s());
+        const SegDot *d_tasks;
+        const SegTile *d_tiles;
+        const int32_t *d_t0, *d_g;
+        ListStage st;   // one copy for all: four of them take longer than the products
+        st.add(d_tasks, tasks);
+        st.add(d_tiles, tiles);
+        st.add(d_t0, t0);
+        st.add(d_g, g_of);
+        ListBuf lists;
+        st.flush(lists, s());
+        DevBuf partial, res;
         partial.ensure(tiles.size() * sizeof(double));
         res.ensure(tasks.size() * sizeof(double));
-        launch_seg_dot_partials(d_tasks.as<SegDot>(), d_tiles.as<SegTile>(), (int)tiles.size(), partial.as<double>(),
-                                s());
-        launch_dot_reduce(partial.as<double>(), d_t0.as<int32_t>(), d_g.as<int32_t>(), (int)tasks.size(),
-                          res.as<double>(), s());
+        launch_seg_dot_partials(d_tasks, d_tiles, (int)tiles.size(), partial.as<double>(), s());
+        launch_dot_reduce(partial.as<double>(), d_t0, d_g, (int)tasks.size(), res.as<double>(), s());
         std::vector<double> h(tasks.size());
         read_back({{h.data(), res.ptr, h.size() * sizeof(double)}}, s());
         for (size_t t = 0; t < tasks.size(); ++t) out[site_of[t]] += wt[t] * h[t];
@@ -968,19 +972,26 @@ int grad_couplings(pdmrg_ctx *ctx, pdmrg_mps *m, const pdmrg_mpo *mpo, double *d
     }
     t0.push_back((int32_t)tiles.size());
     PD_REQUIRE(nG < (int64_t(1) << 31), PDMRG_EINVAL, "grad_couplings: gradient too large");
-    DevBuf d_dw, d_tasks, d_tiles, d_t0, d_g, partial, out;
-    upload_list(d_dw, dWall, s);
-    upload_list(d_tasks, tasks, s);
-    upload_list(d_tiles, tiles, s);
-    upload_list(d_t0, t0, s);
-    upload_list(d_g, g_of, s);
+    const double *d_dw;
+    const DotTask *d_tasks;
+    const DotTile *d_tiles;
+    const int32_t *d_t0, *d_g;
+    ListStage st;
+    st.add(d_dw, dWall);
+    st.add(d_tasks, tasks);
+    st.add(d_tiles, tiles);
+    st.add(d_t0, t0);
+    st.add(d_g, g_of);
+    ListBuf lists;
+    st.flush(lists, s);
+    DevBuf partial, out;
     partial.ensure(std::max<size_t>(tiles.size(), 1) * sizeof(double));
     out.ensure((size_t)ncouplings * sizeof(double));
     Slots sl{};
     sl.p[0] = G.ptr;
-    sl.p[1] = d_dw.ptr;
-    launch_dot_partials(sl, 0, 1, d_tasks.as<DotTask>(), d_tiles.as<DotTile>(), (int)tiles.size(), partial.as<double>(), s);
-    launch_dot_reduce(partial.as<double>(), d_t0.as<int32_t>(), d_g.as<int32_t>(), ncouplings, out.as<double>(), s);
+    sl.p[1] = d_dw;
+    launch_dot_partials(sl, 0, 1, d_tasks, d_tiles, (int)tiles.size(), partial.as<double>(), s);
+    launch_dot_reduce(partial.as<double>(), d_t0, d_g, ncouplings, out.as<double>(), s);
     HIP_OK(hipMemcpyAsync(dE, out.ptr, (size_t)ncouplings * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     API_CATCH
