@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256) void grad_dot_kernel(const double *__restrict_
 #pragma unroll
         for (int u = 0; u < U; ++u) va[u] = e0 + 256 * u < d.n ? a[d.a_off + e0 + 256 * u] : 0.0;
         double *out = partial + d.part0 + (int64_t)tl.chunk * d.nch;
-        for (int c0 = 0; c0 < d.nch; c0 += kGradBatch) {
+        for (int c0 = kGradBatch * blockIdx.y; c0 < d.nch; c0 += kGradBatch * gridDim.y) {
             const int nc = min(kGradBatch, d.nch - c0);
             for (int c = 0; c < nc; c += J) {
                 double acc[J];
@@ -265,10 +265,12 @@ __global__ __launch_bounds__(64) void grad_sum_kernel(const double *__restrict__
 }
 
 void launch_grad_dots(const double *a, const double *r, const GradDot *dots, const DotTile *tiles, int ntiles,
-                      const int64_t *r_off, double *partial, hipStream_t s) {
+                      int max_ch, const int64_t *r_off, double *partial, hipStream_t s) {
     if (ntiles <= 0) return;
     const unsigned g = (unsigned)std::min<int64_t>(ntiles, kMaxGrid);
-    hipLaunchKernelGGL(grad_dot_kernel, dim3(g), dim3(256), 0, s, a, r, dots, tiles, ntiles, r_off, partial);
+    // few tiles: their batches of channels side by side
+    const unsigned y = (unsigned)std::max(1, std::min((max_ch + kGradBatch - 1) / kGradBatch, 1024 / (int)g));
+    hipLaunchKernelGGL(grad_dot_kernel, dim3(g, y), dim3(256), 0, s, a, r, dots, tiles, ntiles, r_off, partial);
 }
 
 void launch_grad_sums(const double *partial, const GradDot *dots, const int32_t *order, const GradSum *sums, int nsums,

@@ -220,7 +220,7 @@ void launch_dot_partials(const Slots &slots, int a_slot, int b_slot, const DotTa
 // out[g_of[k]] = sum over tiles t0[k]..t0[k+1] of partial (in order), for the
 // k = 0..ngroups-1 output entries that have tiles.
 void launch_grad_dots(const double *a, const double *r, const GradDot *dots, const DotTile *tiles, int ntiles,
-                      const int64_t *r_off, double *partial, hipStream_t s);
+                      int max_ch, const int64_t *r_off, double *partial, hipStream_t s);
 // out[g0 + w] = sum over the dots whose list has channel w (at pos[dot.pos + w] >= 0),
 // in order, left alone if there is none.
 void launch_grad_sums(const double *partial, const GradDot *dots, const int32_t *order, const GradSum *sums, int nsums,
