@@ -83,6 +83,18 @@ double GemmList::operand_bytes() const {
     return b;
 }
 
+// The quad shapes to compare: as long as the tiles of the smallest leave a CU each,
+// that one, for a larger only makes the launch longer (BF16x3, 8 x 4 cylinder, m =
+// 33, stage 3: 6.4 us with 128 x 64, 4.1 with 64 x 64).
+unsigned GemmList::quad_shapes(int parts) const {
+    int64_t kmax = 0, n = 0;
+    for (const GemmItem &it : items) kmax = std::max(kmax, item_k(*this, it));
+    const double krange = std::max(1.0, (double)kmax / std::max(parts, 1));
+    for (const GemmItem &it : items)
+        n += (int64_t)((it.M + 63) / 64) * ((it.N + 63) / 64) * (parts > 1 ? split_parts(item_k(*this, it), krange) : 1);
+    return n <= 256 ? 1u << (int)TileShape::T64x64_Q : kQuadShapes;
+}
+
 // Estimated time of a list under a register-direct (FP64) or quad (FP32, BF16x3)
 // shape, in flops of one CU at full rate: the work (dimensions rounded up to the
 // tile, register-direct ones to the 32 that a wave's edge tile keeps) spread
@@ -127,12 +139,12 @@ double GemmList::cost(TileShape ts, int parts) const {
 // tri 12 x 6, m = 3000, 1 GB, 1.05 against 1.06), and its sums run over
 // ascending k.
 //
-// FP32 and BF16x3 take the quad shape of least cost().
+// FP32 and BF16x3 take the quad shape of least cost() among quad_shapes().
 void GemmList::pick_tile(double bytes) {
     double best = 0.0;
     bool have = false;
     streams = (shapes_allowed & kR64Shapes) && bytes > 2e9;
-    const unsigned modelled = streams ? kR64Shapes : elem_bytes == 4 ? shapes_allowed & kQuadShapes : 0u;
+    const unsigned modelled = streams ? kR64Shapes : elem_bytes == 4 ? shapes_allowed & quad_shapes(1) : 0u;
     if (modelled) {
         for (int t = 0; t < kNumShapes; ++t) {
             if (!((modelled >> t) & 1u)) continue;
@@ -831,7 +843,7 @@ void HeffPlan::build(const Bond &bl_, const Bond &br_, const Phys &p_, const Mpo
         // allows: stage 3 with its reduction at 2, 4, 8 parts takes 0.365, 0.356,
         // 0.335 ms (BF16x3, tri 12 x 6, m = 3000), 0.108, 0.093, 0.090 (FP32, 24 x 8
         // cylinder, m = 2000), 0.037, 0.030, 0.032 (BF16x3, 8 x 4, m = 1024).
-        const unsigned shapes = lowp ? kQuadShapes : kR64Shapes;
+        const unsigned shapes = lowp ? g3_base.quad_shapes(8) : kR64Shapes;
         double best = 0.0;
         for (int p = lowp ? 8 : 1; p <= (lowp ? 8 : kMaxParts64); ++p)
             for (int t = 0; t < kNumShapes; ++t) {
@@ -1147,7 +1159,9 @@ void GradPlan::run(const Bond &bl_, const Bond &br_, const Phys &p_, const MpoSi
     double *partial = ws2.as<double>() + std::max<int64_t>(nZ, 1);
     sl.p[4] = ws2.ptr;
     gz.launch(GemmPrec::F64, true, sl, s);
-    launch_grad_dots(ws2.as<double>(), R, d_dots, d_dtiles, (int)dtiles.size(), d_roff, partial, s);
+    int max_ch = 0;
+    for (const GradDot &t : dots) max_ch = std::max(max_ch, t.nch);
+    launch_grad_dots(ws2.as<double>(), R, d_dots, d_dtiles, (int)dtiles.size(), max_ch, d_roff, partial, s);
     launch_grad_sums(partial, d_dots, d_order, d_sums, (int)sums.size(), d_pos, Dr, G, s);
 }
 

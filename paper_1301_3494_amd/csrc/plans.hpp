@@ -68,6 +68,7 @@ struct GemmList {
     void pick_tile(double bytes);
     double operand_bytes() const;
     bool streams = false;   // set by pick_tile(): the register-direct kernel
+    unsigned quad_shapes(int parts) const;
     // The time compared for its shapes, with the K split of split_k(parts).
     double cost(TileShape t, int parts) const;
     int ntiles_for(TileShape t) const;
