@@ -69,9 +69,11 @@ void tune_heff(pdmrg_ctx *ctx, pdmrg_heff *op, const std::string &key) {
     const size_t es = f64 ? sizeof(double) : sizeof(float);
     DevBuf xin(std::max<int64_t>(op->nX, 1) * es + kQuadPad), yout(std::max<int64_t>(op->nX, 1) * sizeof(double));
     // timed on nonzero operands (the clock of the FP64 matrix cores depends on
-    // them): the left environment stands in for x
+    // them): the left environment, repeated, stands in for x
     HIP_OK(hipMemsetAsync(xin.ptr, 0, xin.bytes, s));
-    HIP_OK(hipMemcpyAsync(xin.ptr, op->lp, std::min<int64_t>(op->nX, op->nL) * es, hipMemcpyDeviceToDevice, s));
+    for (int64_t at = 0; op->nL > 0 && at < op->nX; at += op->nL)
+        HIP_OK(hipMemcpyAsync(xin.as<char>() + at * es, op->lp, std::min<int64_t>(op->nX - at, op->nL) * es,
+                              hipMemcpyDeviceToDevice, s));
     Slots sl{};
     sl.p[0] = xin.ptr;
     sl.p[1] = yout.ptr;
@@ -90,6 +92,9 @@ void tune_heff(pdmrg_ctx *ctx, pdmrg_heff *op, const std::string &key) {
         log << " g1 " << shape_name(t) << ' ' << ms;
         if (ms < t1best) { t1best = ms; best1 = t; }
     }
+    // T1 is whole; the rest of T2, which stage 3 is timed on
+    if (op->prec == PDMRG_BF16X3) pl.w.launch_split(sl, s);
+    else pl.w.launch(f64, sl, s);
     const size_t pes = f64 ? sizeof(double) : sizeof(float);   // partial element size
     int parts3 = pl.parts3;
     for (int t = 0; t < kNumShapes; ++t) {
