@@ -153,14 +153,14 @@ int pdmrg_ctx_set_verbose(pdmrg_ctx *ctx, int level);
  * and the Appendix): with mode 1 (the default) each middle-charge block of at
  * least 64 rows (of the smaller dimension) and at most 2048 columns is
  * factored by Householder QR after ordering its rows by decreasing norm, and
- * the one-sided Jacobi iteration runs on the triangular factor, which needs
+ * the Jacobi iteration runs on the triangular factor, which needs
  * about half the sweeps on the graded blocks of a DMRG state; 2 does this for
  * every block up to 2048 columns, 0 never.  The factors are those of the same
  * block to rounding (not the same bits as mode 0); the Appendix recursion
  * runs on top unchanged.  PDMRG_EINVAL for another mode. */
 int pdmrg_ctx_set_svd_precondition(pdmrg_ctx *ctx, int mode);
-/* Device memory of the library's caching allocator (all contexts of the
- * process, bytes): in_use = handed out and not released, peak = largest
+/* Device memory of the library's caching allocator, its work lists among it
+ * (all contexts of the process, bytes): in_use = handed out and not released, peak = largest
  * in_use since the last reset, cached = released blocks held for reuse.
  * reset_peak != 0 sets peak to the current in_use afterwards.  Outputs
  * optional. */
@@ -325,7 +325,7 @@ int davidson_step(pdmrg_ctx *ctx, pdmrg_heff *op, pdmrg_heff *op64, double *psi_
 
 /* -------------------------------------------------------------------- SVD
  * Truncated SVD of the two-site Psi (Eq. eqn:svd) as the (m d) x (d m) matrix,
- * block-diagonal in the middle charge; per block a one-sided block-Jacobi SVD
+ * block-diagonal in the middle charge; per block a block-Jacobi SVD
  * followed by the Appendix recursion on singular values below eps * lambda_1
  * of that block.  Keeps the max_m largest singular values over all blocks
  * (ties: larger lambda, then smaller charge, then smaller index), dropping

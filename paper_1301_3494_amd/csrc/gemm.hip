@@ -71,6 +71,10 @@ __device__ __forceinline__ int64_t c_row(const GemmItem &it, const int64_t *__re
     return it.rmap >= 0 ? rowoff[it.rmap + r] : (int64_t)r * it.ldc;
 }
 
+// 16-byte accesses to rows of any 4-byte alignment
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned w4u __attribute__((ext_vector_type(4), aligned(4)));
+
 // Output of a tile of H_eff's stage 1 (EpiDev): its blocks that the W stage
 // would only scale and copy go to T2 from here, and to T1 only if another sum
 // reads them.  The W stage, at the rate of a copy, loses most of its traffic for
@@ -78,9 +82,6 @@ __device__ __forceinline__ int64_t c_row(const GemmItem &it, const int64_t *__re
 // 19 us and 77 -> 81; 24 x 8 FP32, m = 2000, 44 -> 19 and 101 -> 106; tri 12 x 6
 // BF16x3, m = 3000, 126 -> 58 and 387 -> 409; 98 channels, m = 4000, 1.61 -> 0.54 ms
 // and 5.30 -> 5.51.
-// 16-byte accesses to rows of any 4-byte alignment
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef unsigned w4u __attribute__((ext_vector_type(4), aligned(4)));
 // NC columns of a lane (those below N), its rows in ascending order.
 template <int NC, typename TD>
 struct EpiWriter {

@@ -140,8 +140,9 @@ enum class GemmPrec { F64, F32, BF16X3 };
 // Output tile shapes of the FP64 / FP32 kernels (4 waves).  0-7: the register-
 // staged kernel; the _K16 / _K8 variants stage a half / quarter as much K per
 // step (FP32 16 / 8 instead of 32, FP64 8 / 4 instead of 16), so less LDS and
-// more resident workgroups for short K loops.  _D: the LDS-DMA kernel (the only
-// one of BF16X3).  _R: the FP64 register-direct kernel.
+// more resident workgroups for short K loops.  _D: the LDS-DMA kernel.  _R: the
+// FP64 register-direct kernel.  _Q: the FP32 / BF16X3 quad kernel.  BF16X3 runs _D
+// and _Q only.
 enum class TileShape {
     T64x64 = 0, T128x32 = 1, T32x128 = 2, T128x128 = 3,
     T64x64_K16 = 4, T128x32_K16 = 5,   // half-depth K steps
@@ -217,14 +218,15 @@ void launch_diag_terms(const Slots &slots, const DiagTerm *terms, const int32_t 
 // partial[t] = sum over tile t's elements of a * b (fixed-order tree).
 void launch_dot_partials(const Slots &slots, int a_slot, int b_slot, const DotTask *tasks, const DotTile *tiles,
                          int ntiles, double *partial, hipStream_t s);
-// out[g_of[k]] = sum over tiles t0[k]..t0[k+1] of partial (in order), for the
-// k = 0..ngroups-1 output entries that have tiles.
+// partial of every dot's tiles (GradDot); max_ch: most channels of a dot.
 void launch_grad_dots(const double *a, const double *r, const GradDot *dots, const DotTile *tiles, int ntiles,
                       int max_ch, const int64_t *r_off, double *partial, hipStream_t s);
 // out[g0 + w] = sum over the dots whose list has channel w (at pos[dot.pos + w] >= 0),
 // in order, left alone if there is none.
 void launch_grad_sums(const double *partial, const GradDot *dots, const int32_t *order, const GradSum *sums, int nsums,
                       const int32_t *pos, int width, double *out, hipStream_t s);
+// out[g_of[k]] = sum over tiles t0[k]..t0[k+1] of partial (in order), for the
+// k = 0..ngroups-1 output entries that have tiles.
 void launch_dot_reduce(const double *partial, const int32_t *t0, const int32_t *g_of, int ngroups, double *out,
                        hipStream_t s);
 void launch_convert_f64_f32(const double *x, float *y, int64_t n, hipStream_t s);

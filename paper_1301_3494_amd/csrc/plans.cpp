@@ -134,10 +134,13 @@ double GemmList::cost(TileShape ts, int parts) const {
 
 // Past 2 GB of operands (each item's counted once) FP64 lists stream from memory
 // and run the register-direct kernel: H_eff at m = 4000, 98 channels, 7.8 GB,
-// stage 1 5.9 -> 5.3 ms, stage 3 10.0 -> 6.0.  Below, the LDS kernel is as fast
-// or faster (24 x 8 cylinder, m = 2000, 0.4 GB, stage 1 0.148 ms against 0.160;
-// tri 12 x 6, m = 3000, 1 GB, 1.05 against 1.06), and its sums run over
-// ascending k.
+// stage 1 5.9 -> 5.3 ms, stage 3 10.0 -> 6.0.  Below, the staged kernel is kept for
+// its order of sums (over ascending k, with the splits it has always had), not for
+// speed: an eigensolver stopped early can amplify a change of rounding.  What that
+// costs, against the plans that the autotuner takes (which follow their own order
+// of sums), us a product: 16-site chain, m = 64, 19.5 / 15.5; 8 x 4 cylinder, m =
+// 1024, 168 / 151; 24 x 8, m = 2000, 422 / 410; tri 12 x 6, m = 3000, 2268 / 2001; 98
+// channels, m = 500, 131 / 92.
 //
 // FP32 and BF16x3 take the quad shape of least cost() among quad_shapes().
 void GemmList::pick_tile(double bytes) {

@@ -20,7 +20,8 @@
 // time goes down with the cost of one inner round and with the launches and
 // loads around them.  Blocks of 32 rows have a quarter of the launches of
 // blocks of 8 and need fewer sweeps.
-// Matrices of at most 64 rows run whole in one workgroup (jac_small_kernel).
+// Matrices of at most 64 rows run whole in one workgroup (jac_small_kernel),
+// except very long rows.
 //
 // Also here: the Householder QR that preconditions the iteration (panel and
 // reflector-application kernels, below) and the copy / norm helpers.
@@ -890,7 +891,7 @@ void launch_copies(const CopyTask *tasks, int ntasks, int64_t max_elems, hipStre
 
 
 // ---------------------------------------------------------------------------
-// Householder QR preconditioning of the one-sided Jacobi iteration.
+// Householder QR preconditioning of the Jacobi iteration.
 //
 // Panel kernel: one workgroup of NT threads factors the 16 rows of a panel.
 // Thread t holds positions j0 + t + NT u (u < UQ) of all 16 rows in
