@@ -798,13 +798,15 @@ __global__ __launch_bounds__(eig_threads(P)) void jac_small_kernel(const JacSmal
             break;
         }
         __syncthreads();
-        // W <- J^T W, then Z: a wave takes kCols times 16 columns at a time
+        // W <- J^T W, then Z: a wave takes up to kCols times 16 columns at a time
         const int cw = (it.len + 15) / 16, cz = (it.nv + 15) / 16;
-        for (int t0 = w * kCols; t0 < cw + cz; t0 += kWaves * kCols) {
+        const int per = kCols == 1 ? 1 : min(kCols, (cw + cz + kWaves - 1) / kWaves);
+        for (int t0 = w * per; t0 < cw + cz; t0 += kWaves * per) {
             double b[kCols][kT][4];
 #pragma unroll
             for (int u = 0; u < kCols; ++u) {
                 const int t = t0 + u;
+                if (u >= per) break;
                 const double *X = t < cw ? it.W : it.Z;
                 const int len = t < cw ? it.len : it.nv, col = 16 * (t < cw ? t : t - cw) + r16;
 #pragma unroll
@@ -818,7 +820,7 @@ __global__ __launch_bounds__(eig_threads(P)) void jac_small_kernel(const JacSmal
 #pragma unroll
             for (int u = 0; u < kCols; ++u) {
                 const int t = t0 + u;
-                if (t >= cw + cz) break;
+                if (u >= per || t >= cw + cz) break;
                 double *X = t < cw ? it.W : it.Z;
                 const int len = t < cw ? it.len : it.nv, col = 16 * (t < cw ? t : t - cw) + r16;
                 for (int ti = 0; ti < nt16; ++ti) {
