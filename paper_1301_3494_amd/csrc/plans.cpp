@@ -83,16 +83,16 @@ double GemmList::operand_bytes() const {
     return b;
 }
 
-// The quad shapes to compare: as long as the tiles of the smallest leave a CU each,
-// that one, for a larger only makes the launch longer (BF16x3, 8 x 4 cylinder, m =
-// 33, stage 3: 6.4 us with 128 x 64, 4.1 with 64 x 64).
+// The quad shapes to compare: as long as the 64 x 64 tiles leave a CU each, those,
+// for a larger one only makes the launch longer (BF16x3, 8 x 4 cylinder, m = 33,
+// stage 3: 6.4 us with 128 x 64, 4.1 with 64 x 64).
 unsigned GemmList::quad_shapes(int parts) const {
     int64_t kmax = 0, n = 0;
     for (const GemmItem &it : items) kmax = std::max(kmax, item_k(*this, it));
     const double krange = std::max(1.0, (double)kmax / std::max(parts, 1));
     for (const GemmItem &it : items)
         n += (int64_t)((it.M + 63) / 64) * ((it.N + 63) / 64) * (parts > 1 ? split_parts(item_k(*this, it), krange) : 1);
-    return n <= 256 ? 1u << (int)TileShape::T64x64_Q : kQuadShapes;
+    return n <= 256 ? 1u << (int)TileShape::T64x64_Q | 1u << (int)TileShape::T64x64_Q32 : kQuadShapes;
 }
 
 // Estimated time of a list under a register-direct (FP64) or quad (FP32, BF16x3)
