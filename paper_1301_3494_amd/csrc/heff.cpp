@@ -71,8 +71,10 @@ void tune_heff(pdmrg_ctx *ctx, pdmrg_heff *op, const std::string &key) {
     // timed on nonzero operands (the clock of the FP64 matrix cores depends on
     // them): the left environment, repeated, stands in for x
     HIP_OK(hipMemsetAsync(xin.ptr, 0, xin.bytes, s));
-    for (int64_t at = 0; op->nL > 0 && at < op->nX; at += op->nL)
-        HIP_OK(hipMemcpyAsync(xin.as<char>() + at * es, op->lp, std::min<int64_t>(op->nX - at, op->nL) * es,
+    int64_t at = std::min<int64_t>(op->nX, op->nL);
+    HIP_OK(hipMemcpyAsync(xin.ptr, op->lp, at * es, hipMemcpyDeviceToDevice, s));
+    for (; at > 0 && at < op->nX; at *= 2)
+        HIP_OK(hipMemcpyAsync(xin.as<char>() + at * es, xin.ptr, std::min<int64_t>(op->nX - at, at) * es,
                               hipMemcpyDeviceToDevice, s));
     Slots sl{};
     sl.p[0] = xin.ptr;
